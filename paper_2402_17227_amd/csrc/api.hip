@@ -64,9 +64,9 @@ vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int
                              hipStream_t st);
 vcas_status wgrad_bf16_batch(const WgradItem *items, int n, int tile, hipStream_t st);
 vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const float *p, const int32_t *idxA,
-                      const int32_t *cntA, void *dX, const void *J, bool fill, hipStream_t st);
+                      const int32_t *cntA, void *dX, const void *J, bool fill, int64_t expected_rows, hipStream_t st);
 vcas_status wgrad_f32(const vcas_shape &s, const void *G, const void *X, const float *row_scale, const int32_t *idxW,
-                      const int32_t *cntW, float *dW, float *partials, int splits, hipStream_t st);
+                      const int32_t *cntW, float *dW, float *partials, int max_splits, int fill, hipStream_t st);
 
 // Split-K slices of the weight gradient: about one and a half workgroups per CU (a second one
 // hides the first one's waits; more splits cost reduction traffic), at most 8, and never so many
@@ -161,7 +161,7 @@ static vcas_status dispatch_dgrad(const vcas_shape &s, const void *G, const void
                                   int64_t expected_rows, hipStream_t st, float *sq_blocks = nullptr)
 {
     if (s.dtype == VCAS_BF16) return dgrad_bf16(s, G, W, p, idxA, cntA, dX, J, fill, expected_rows, nullptr, sq_blocks, st);
-    return sq_blocks ? VCAS_EDTYPE : dgrad_f32(s, G, W, p, idxA, cntA, dX, J, fill, st);
+    return sq_blocks ? VCAS_EDTYPE : dgrad_f32(s, G, W, p, idxA, cntA, dX, J, fill, expected_rows, st);
 }
 
 // Tile edge and split-K slices of bf16 weight gradients.  `fill` = the workgroups a launch should
@@ -215,10 +215,10 @@ static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const
                                        const int32_t *idxW, const int32_t *cntW, float *dW, float *partials,
                                        uint16_t *packed, hipStream_t st, int fill = kWgradFill)
 {
+    fill = fill_or_default(fill);
     if (s.dtype != VCAS_BF16)
         return wgrad_f32(s, G, X, scale, idxW, cntW, dW, partials, wgrad_split_for(&s, wgrad_tiles_f32(s.K_out, s.K_in), fill),
-                         st);
-    fill = fill_or_default(fill);
+                         fill, st);
     const int tile = wgrad_tile_choice(wgrad_tiles_bf16(s.K_out, s.K_in, 256), wgrad_tiles_bf16(s.K_out, s.K_in, 128), fill);
     WgradItem it = wgrad_item(s, G, X, scale, idxW, cntW, dW, partials, packed);
     it.splits = wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), fill);

@@ -10,25 +10,9 @@
 // and ds_read_b64_tr_b16 transposes it on the way out.  The per-row 1/p goes into the epilogue.
 #include <type_traits>
 
-#include "mfma_bf16.hpp"
+#include "mfma_common.hpp"
 
 namespace vcas {
-
-__device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 7); }
-// byte offset of 16-byte slot `slot` (0..7) of tile row `row`
-__device__ __forceinline__ int lds_off(int row, int slot) { return row * 128 + ((slot ^ swz(row)) << 4); }
-
-// The j-th sample (0-based) that is NOT in the ascending list idx[0..cnt).
-__device__ __forceinline__ int nth_missing(const int32_t *idx, int cnt, int j)
-{
-    int lo = 0, hi = cnt;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (idx[mid] - mid > j) hi = mid;
-        else lo = mid + 1;
-    }
-    return j + lo;
-}
 
 // ------------------------------------------------------------------ dgrad
 //
@@ -43,13 +27,6 @@ __device__ __forceinline__ int nth_missing(const int32_t *idx, int cnt, int j)
 // barrier per step: before it every wavefront waits until its own loads of the
 // step have landed (s_waitcnt vmcnt, the counter is in order), after it the
 // stage computed in the previous step is free.
-template <int N>
-__device__ __forceinline__ void wait_loads_outstanding()
-{
-    // s_waitcnt vmcnt(N) only: expcnt and lgkmcnt fields left at "no wait"
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
 constexpr int kIdxStaged = 1024;   // kept-sample indices a workgroup stages in LDS ahead of the count
 
 // grid: 1-D, tiles_n * (ceil(R/BM) + 1) + 8 workgroups.  The first ceil8(compute

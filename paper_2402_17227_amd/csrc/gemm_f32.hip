@@ -1,53 +1,20 @@
-// fp32 gather-GEMMs of the VCAS backward pass (the fp32 configuration):
-// dgrad (Eq. 2, upper line) and wgrad (Sec. 4.2) on v_mfma_f32_32x32x2_f32.
-// 64x64 output tile per workgroup of 4 wavefronts (2x2, one 32x32 MFMA block
-// each), contraction in steps of 16.  LDS tiles are k-major ([k][row], pitch
-// 68 floats) so that fragment reads are 32 consecutive floats; only dgrad's G
-// operand (contiguous along the contraction) is transposed on its way in.
-#include "common.hpp"
+// fp32 gather-GEMMs of the VCAS backward pass (the fp32 configuration) on v_mfma_f32_32x32x2_f32:
+// dgrad (Eq. 2, upper line) here, wgrad (Sec. 4.2) in wgrad_gather.hpp.
+// The *_far kernels at the end serve tensors that 32-bit buffer offsets do not reach: 64x64 output
+// tiles, four wavefronts, operands staged through registers into k-major LDS tiles ([k][row], pitch 68
+// floats, so that fragment reads are 32 consecutive floats), contraction in steps of 16.
+#include "wgrad_gather.hpp"
 
 namespace vcas {
-
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // gemm_bf16.hip
 vcas_status splitk_reduce(const float *partials, const int32_t *cntW, float *dW, int64_t R, int64_t elems, int splits,
                           int min_steps, int step, hipStream_t st);
 
-// same rule as the bf16 kernels use (kept in step with it by the shared reduction kernel's tests)
-__host__ __device__ inline int wgrad_active_splits(int steps_all, int splits, int min_steps, int &per)
-{
-    int active = splits < steps_all / min_steps ? splits : steps_all / min_steps;
-    if (active < 1) active = 1;
-    per = (steps_all + active - 1) / active;
-    if (per < 1) per = 1;
-    active = (steps_all + per - 1) / per;
-    return active < 1 ? 1 : active;
-}
-
 namespace f32gemm {
 
 constexpr int BM = 64, BN = 64, BKF = 16, PITCH = 68, NT = 256;
 constexpr int TILE_FLOATS = BKF * PITCH;
-
-__device__ __forceinline__ int acc_row(int v) { return (v >> 2) * 8 + ((threadIdx.x & 63) >> 5) * 4 + (v & 3); }
-
-__device__ __forceinline__ int xcd_remap(int id, int total)
-{
-    const int per = (total + 7) / 8;
-    return (id & 7) * per + (id >> 3);
-}
-
-__device__ __forceinline__ int nth_missing(const int32_t *idx, int cnt, int j)
-{
-    int lo = 0, hi = cnt;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (idx[mid] - mid > j) hi = mid;
-        else lo = mid + 1;
-    }
-    return j + lo;
-}
 
 __device__ __forceinline__ void mma_step(const float *As, const float *Bs, int wm0, int wn0, f32x16 &acc)
 {
@@ -63,10 +30,204 @@ __device__ __forceinline__ void mma_step(const float *As, const float *Bs, int w
 
 }  // namespace f32gemm
 
+// ------------------------------------------------------------------ dgrad
+//
+// BM x BN output tile, WM x WN x WK wavefronts of one 32x32 block each.  The operand tiles go straight
+// into LDS (buffer_load ... lds), NS stages of KSUB sub-tiles of 32 contraction elements.  Bound by the
+// matrix cores (64 cycles for 2 elements of a 32x32 block); what keeps them busy is long steps (64
+// elements between barriers) and several workgroups per CU, so two shallow stages beat a deep pipeline
+// (768->3072, 4096 rows: 157 us = 123 TFLOP/s of 157 with two stages of 64, 179 with four of 32; the
+// register-staged kernel with steps of 16 took 201).
+// A sub-tile is
+//   G: [row][32 k] rows of 128 bytes, slots swizzled by lds_off.  Lane half h of chunk c (8 elements)
+//      reads slot 2c + h, four elements k = 8c + 4h + e, with one 16-byte read; the order of the
+//      contraction is free, so MFMA e of the chunk takes element e of both halves.
+//   W: [32 k][BN columns] as in memory; the two halves read rows k and k + 4 at once, which are put
+//      into different banks by exchanging the halves of a 64-column row (BN = 64) or neighbouring
+//      32-column rows (BN = 32) wherever bit 2 of k is set.
+// WK > 1: the WK wavefronts of a block take different chunks of every step and their sums meet in LDS
+// at the end, in wavefront order: a wavefront alone on its SIMD would be bound by its own chain of MFMAs.
+template <int BM, int BN, int WM, int WN, int WK, int KSUB, int NS>
+__global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(const float *__restrict__ G,
+                                                                    const float *__restrict__ W,
+                                                                    const float *__restrict__ p,
+                                                                    const int32_t *__restrict__ idxA,
+                                                                    const int32_t *__restrict__ cntA,
+                                                                    float *__restrict__ dX, int N, int T, int K_in,
+                                                                    int K_out, int tiles_n,
+                                                                    const float *__restrict__ J, int fill_dropped)
+{
+    constexpr int NW = WM * WN * WK, NT = NW * 64, BKF = 32 * KSUB;
+    static_assert(BM == WM * 32 && BN == WN * 32 && (BN == 32 || BN == 64), "one 32x32 block per wavefront");
+    constexpr int AI = KSUB * BM / (8 * NW), BI = KSUB * BN / (8 * NW);   // LDS-direct loads per wavefront and step
+    constexpr int B_ROWS = 256 / BN, B_SLOTS = BN / 4;         // k rows per W load, 16-byte slots per W row
+    constexpr int SUB = (BM + BN) * 128, STAGE = KSUB * SUB, B_AT = BM * 128, B_PITCH = BN * 4;
+    constexpr int LOADS = AI + BI, CHUNKS = 4 * KSUB / WK;
+    static_assert(AI >= 1 && BI >= 1 && CHUNKS >= 1, "tile/wave mismatch");
+    static_assert((WK - 1) * WM * WN * 4096 <= NS * STAGE, "the partial blocks meet in the operand stages");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int32_t *row_of = reinterpret_cast<int32_t *>(smem + NS * STAGE);
+    float *scale_of = reinterpret_cast<float *>(row_of + BM);
+
+    const int cnt = min(max(*cntA, 0), N);
+    const int64_t M = (int64_t)cnt * T, R = (int64_t)N * T;
+    const int compute = (int)((M + BM - 1) / BM) * tiles_n;
+    const int compute8 = (compute + 7) / 8 * 8;
+    if ((int)blockIdx.x >= compute8) {
+        if (!fill_dropped) return;
+        const int z = blockIdx.x - compute8;
+        const int64_t d0 = (int64_t)(z / tiles_n) * BM;
+        const int n0 = (z % tiles_n) * BN;
+        if (d0 >= R - M) return;
+        for (int r = threadIdx.x; r < BM; r += NT) {
+            const int64_t d = d0 + r;
+            row_of[r] = d < R - M ? nth_missing(idxA, cnt, (int)(d / T)) * T + (int)(d % T) : -1;
+        }
+        __syncthreads();
+        for (int u = threadIdx.x; u < BM * (BN / 4); u += NT) {
+            const int r = u / (BN / 4), col = n0 + (u % (BN / 4)) * 4;
+            if (row_of[r] >= 0 && col < K_in)
+                *reinterpret_cast<float4 *>(dX + (int64_t)row_of[r] * K_in + col) = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        return;
+    }
+    const int tile = xcd_remap(blockIdx.x, compute);
+    if (tile >= compute) return;
+    const int64_t m0 = (int64_t)(tile / tiles_n) * BM;
+    const int n0 = (tile % tiles_n) * BN;
+    float p_row = 0.0f;   // of row threadIdx.x: fetched here, needed in the epilogue only
+    static_assert(NT >= BM, "a thread per row");
+    if (threadIdx.x < BM) {
+        const int64_t m = m0 + threadIdx.x;
+        int32_t dst = -1;
+        if (m < M) {
+            const int s = idxA[m / T];
+            if (s >= 0 && s < N) {
+                dst = s * T + (int)(m % T);
+                p_row = p[s];
+            }
+        }
+        row_of[threadIdx.x] = dst;
+    }
+    __syncthreads();
+
+    const i32x4 descG = raw_descriptor(G, (uint32_t)(R * K_out * 4));
+    const i32x4 descW = raw_descriptor(W, (uint32_t)((int64_t)K_out * K_in * 4));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    // LDS row of k row k of W and slot XOR within it: involutions, so the lane that fills LDS row r,
+    // slot s fetches k row place(r), slot s ^ flip(place(r))
+    // load j of this wavefront: sub-tile and first row (of 8 rows of G, of B_ROWS k rows of W) within it
+    auto a_sub = [&](int j) { return (wave * AI + j) / (BM / 8); };
+    auto a_row = [&](int j) { return (wave * AI + j) % (BM / 8) * 8; };
+    auto b_sub = [&](int j) { return (wave * BI + j) / (BN / 8); };
+    auto b_row = [&](int j) { return (wave * BI + j) % (BN / 8) * B_ROWS; };
+    auto place = [](int k) { return BN == 32 ? k ^ ((k >> 2) & 1) : k; };
+    auto flip = [](int k) { return BN == 64 ? ((k >> 2) & 1) * 8 : 0; };
+    uint32_t a_off[AI], b_off[BI];
+#pragma unroll
+    for (int j = 0; j < AI; ++j) {
+        const int row = a_row(j) + (lane >> 3);
+        const int32_t src = row_of[row];
+        a_off[j] = src >= 0 ? (uint32_t)src * (uint32_t)K_out * 4u + (uint32_t)(a_sub(j) * 128 + ((lane & 7) ^ swz(row)) * 16) : kOutside;
+    }
+#pragma unroll
+    for (int j = 0; j < BI; ++j) {
+        const int krow = place(b_row(j) + lane / B_SLOTS);
+        const int col = n0 + ((lane % B_SLOTS) ^ flip(krow)) * 4;
+        b_off[j] = col < K_in ? ((uint32_t)(b_sub(j) * 32 + krow) * (uint32_t)K_in + (uint32_t)col) * 4u : kOutside;
+    }
+    const int steps = (K_out + BKF - 1) / BKF;
+    const int tail_pieces = (K_out - (steps - 1) * BKF + 3) / 4;   // pieces of a G row that the last step still owns
+    auto issue = [&](int stage, int step) {   // a step past the end fills a stage nobody reads and keeps the counts uniform
+        const uint32_t kb = __builtin_amdgcn_readfirstlane(step * BKF * 4);
+        const uint32_t wb = __builtin_amdgcn_readfirstlane(step * BKF * K_in * 4);
+        const int pieces = step < steps - 1 ? 8 * KSUB : step == steps - 1 ? tail_pieces : 0;
+#pragma unroll
+        for (int j = 0; j < AI; ++j) {
+            const int piece = a_sub(j) * 8 + ((lane & 7) ^ swz(a_row(j) + (lane >> 3)));
+            const uint32_t dst = lds0 + stage * STAGE + a_sub(j) * SUB + a_row(j) * 128;
+            lds_direct_load16(descG, __builtin_amdgcn_readfirstlane(dst), piece < pieces ? a_off[j] : kOutside, kb);
+        }
+#pragma unroll
+        for (int j = 0; j < BI; ++j) {
+            const uint32_t dst = lds0 + stage * STAGE + b_sub(j) * SUB + B_AT + b_row(j) * B_PITCH;
+            lds_direct_load16(descW, __builtin_amdgcn_readfirstlane(dst), pieces ? b_off[j] : kOutside, wb);
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < NS - 1; ++d) issue(d, d);
+
+    const int wk = wave / (WM * WN), blk = wave % (WM * WN);
+    const int wm0 = (blk / WN) * 32, wn0 = (blk % WN) * 32;
+    const int r32 = lane & 31, h = lane >> 5;
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    int stage = 0;
+    for (int s = 0; s < steps; ++s) {
+        wait_loads_outstanding<(NS - 2) * LOADS>();   // step s has landed, the younger ones may stay in flight
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(stage == 0 ? NS - 1 : stage - 1, s + NS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        float4 a[CHUNKS];
+        float b[CHUNKS][4];
+#pragma unroll
+        for (int q = 0; q < CHUNKS; ++q) {
+            const int c = (wk * CHUNKS + q) & 3;
+            const unsigned char *tileA = smem + stage * STAGE + ((wk * CHUNKS + q) >> 2) * SUB, *tileB = tileA + B_AT;
+            a[q] = *reinterpret_cast<const float4 *>(tileA + lds_off(wm0 + r32, 2 * c + h));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 8 * c + 4 * h + e, col = wn0 + r32;
+                b[q][e] = *reinterpret_cast<const float *>(tileB + place(k) * B_PITCH + (((col >> 2) ^ flip(k)) << 4) + (col & 3) * 4);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < CHUNKS; ++q) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].x, b[q][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].y, b[q][1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].z, b[q][2], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].w, b[q][3], acc, 0, 0, 0);
+        }
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+    wait_loads_outstanding<0>();
+    if (threadIdx.x < BM) scale_of[threadIdx.x] = 1.0f / p_row;
+    __syncthreads();   // ... and every wavefront is done with the stages
+    if (WK > 1) {
+        float *part = reinterpret_cast<float *>(smem);
+        if (wk > 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) part[(((wk - 1) * WM * WN + blk) * 16 + v) * 64 + lane] = acc[v];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int w = 1; w < WK; ++w)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = acc[v] + part[(((w - 1) * WM * WN + blk) * 16 + v) * 64 + lane];
+    }
+    const int col = n0 + wn0 + r32;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = wm0 + acc_row(v);
+        if (row_of[r] >= 0 && col < K_in) {
+            const int64_t at = (int64_t)row_of[r] * K_in + col;
+            float val = acc[v] * scale_of[r];
+            if (J) val = val * J[at];   // elementwise Jacobian of the layer below (App. E, proof of unbiasedness)
+            dX[at] = val;
+        }
+    }
+}
+
+// dgrad for tensors of 2 GiB and more.
 // grid: tiles_n * (ceil(R/64) + 1) + 8 workgroups.  The first ceil8(compute
 // tiles) ids compute (spread over the XCDs), the next ones zero the rows of
 // dropped samples, the rest exit.
-__global__ __launch_bounds__(256) void dgrad_f32_kernel(const float *__restrict__ G, const float *__restrict__ W,
+__global__ __launch_bounds__(256) void dgrad_f32_far_kernel(const float *__restrict__ G, const float *__restrict__ W,
                                                         const float *__restrict__ p,
                                                         const int32_t *__restrict__ idxA,
                                                         const int32_t *__restrict__ cntA, float *__restrict__ dX,
@@ -185,9 +346,10 @@ __global__ __launch_bounds__(256) void dgrad_f32_kernel(const float *__restrict_
     }
 }
 
+// wgrad for tensors of 2 GiB and more.
 // grid: splits * tiles workgroups rounded up to 8, split-major; see the bf16
 // kernel for the split-K protocol (same partial buffers and reduction kernel).
-__global__ __launch_bounds__(256) void wgrad_f32_kernel(const float *__restrict__ G, const float *__restrict__ X,
+__global__ __launch_bounds__(256) void wgrad_f32_far_kernel(const float *__restrict__ G, const float *__restrict__ X,
                                                         const float *__restrict__ row_scale,
                                                         const int32_t *__restrict__ idxW,
                                                         const int32_t *__restrict__ cntW, float *__restrict__ dW,
@@ -289,29 +451,93 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(const float *__restrict_
 
 int wgrad_tiles_f32(int K_out, int K_in) { return ((K_out + 63) / 64) * ((K_in + 63) / 64); }
 
-vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const float *p, const int32_t *idxA,
-                      const int32_t *cntA, void *dX, const void *J, bool fill, hipStream_t st)
+template <int BM, int BN, int WM, int WN, int WK, int KSUB, int NS>
+static vcas_status launch_dgrad_f32(const vcas_shape &s, const void *G, const void *W, const float *p, const int32_t *idxA,
+                                    const int32_t *cntA, void *dX, const void *J, bool fill, hipStream_t st)
 {
     const int64_t R = (int64_t)s.N * s.T;
-    const int tiles_n = (s.K_in + 63) / 64;
-    const int64_t grid = tiles_n * ((R + 63) / 64 + 1) + 8;
+    const int tiles_n = (s.K_in + BN - 1) / BN;
+    const int64_t grid = tiles_n * ((R + BM - 1) / BM + 1) + 8;
     if (grid > (int64_t)1 << 30) return VCAS_EINVAL;
-    launch_timed(0, dgrad_f32_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const float *>(G),
-                       static_cast<const float *>(W), p, idxA, cntA, static_cast<float *>(dX), s.N, s.T, s.K_in,
-                       s.K_out, tiles_n, static_cast<const float *>(J), fill ? 1 : 0);
+    const size_t lds = NS * KSUB * (BM + BN) * 128 + BM * 8;
+    auto kern = dgrad_f32_kernel<BM, BN, WM, WN, WK, KSUB, NS>;
+    static bool allowed = false;
+    if (!allowed) {
+        if (!allow_lds(kern, lds)) return VCAS_EHIP;
+        allowed = true;
+    }
+    launch_timed(0, kern, dim3((unsigned)grid), dim3(WM * WN * WK * 64), lds, st, static_cast<const float *>(G),
+                 static_cast<const float *>(W), p, idxA, cntA, static_cast<float *>(dX), s.N, s.T, s.K_in, s.K_out, tiles_n,
+                 static_cast<const float *>(J), fill ? 1 : 0);
     return launch_status();
 }
 
+vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const float *p, const int32_t *idxA,
+                      const int32_t *cntA, void *dX, const void *J, bool fill, int64_t expected_rows, hipStream_t st)
+{
+    const int64_t R = (int64_t)s.N * s.T;
+    if (!offsets_fit(s)) {   // larger tensors than 32-bit buffer offsets reach, which the fp32 calls have always taken
+        const int tiles_n = (s.K_in + 63) / 64;
+        const int64_t grid = tiles_n * ((R + 63) / 64 + 1) + 8;
+        if (grid > (int64_t)1 << 30) return VCAS_EINVAL;
+        launch_timed(0, dgrad_f32_far_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const float *>(G),
+                     static_cast<const float *>(W), p, idxA, cntA, static_cast<float *>(dX), s.N, s.T, s.K_in, s.K_out,
+                     tiles_n, static_cast<const float *>(J), fill ? 1 : 0);
+        return launch_status();
+    }
+    // A tile's time is that of its MFMAs on one CU, and the launch ends with the CU that got one tile
+    // more: the tile for which ceil(tiles / CUs) * (tile size) is least.  A 32x64 tile costs 0.55 of a
+    // 64x64 one (768->3072: 2048 kept rows, 384 or 768 tiles, 105 and 87 us; 4096 kept rows, 157 and
+    // 174 us; 1024->1024, 2048 rows: 42 and 46 us).  When even 32x32 tiles leave CUs empty, eight
+    // wavefronts share each tile's contraction (344->2888, 36 kept rows: 23 us against 34 with 32x64
+    // tiles; the kernel with register-staged loads took 85, and 143 us in the first case above).
+    const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
+    auto per_cu = [&](int bm, int bn) { return (((rows + bm - 1) / bm) * ((s.K_in + bn - 1) / bn) + 255) / 256; };
+    if (per_cu(32, 32) <= 1) return launch_dgrad_f32<32, 32, 1, 1, 8, 2, 3>(s, G, W, p, idxA, cntA, dX, J, fill, st);
+    if (55 * per_cu(32, 64) < 100 * per_cu(64, 64))
+        return launch_dgrad_f32<32, 64, 1, 2, 2, 2, 2>(s, G, W, p, idxA, cntA, dX, J, fill, st);
+    return launch_dgrad_f32<64, 64, 2, 2, 2, 2, 2>(s, G, W, p, idxA, cntA, dX, J, fill, st);
+}
+
+// max_splits: partial matrices there is room for; fill: workgroups the launch should have
 vcas_status wgrad_f32(const vcas_shape &s, const void *G, const void *X, const float *row_scale, const int32_t *idxW,
-                      const int32_t *cntW, float *dW, float *partials, int splits, hipStream_t st)
+                      const int32_t *cntW, float *dW, float *partials, int max_splits, int fill, hipStream_t st)
 {
     constexpr int MIN_STEPS = 8;
     const int64_t R = (int64_t)s.N * s.T;
+    if (offsets_fit(s)) {
+        GatherTask q = {};
+        q.G = G;
+        q.X = X;
+        q.row_scale = row_scale;
+        q.idx = idxW;
+        q.cnt = cntW;
+        q.dst = dW;
+        q.partials = partials;
+        q.R = (int32_t)R;
+        q.K_in = s.K_in;
+        q.K_out = s.K_out;
+        // 64x64 tiles with 32-token steps, four to a CU, where there are many tiles and a tile's own
+        // latency is what has to be hidden (4096x4096, 32 tokens: 28 us against 80; 3464->2408, 122
+        // tokens: 36 against 54); else 32x32 tiles, whose four wavefronts share each contraction, so
+        // that small weight gradients fill the chip without slices and their reduction launch
+        // (768x768, 256 tokens: 11 us, register-staged 64x64 tiles in slices 17; 768x3072, 1024
+        // tokens: 70 and 79 us).
+        const bool large = gather_tiles(VCAS_F32, s.K_out, s.K_in, true) >= 768;
+        const int tiles = gather_tiles(VCAS_F32, s.K_out, s.K_in, large);
+        q.splits = large ? 1 : (fill + fill / 3 + tiles - 1) / tiles;
+        if (q.splits > max_splits) q.splits = max_splits;
+        const vcas_status rc = wgrad_gather(&q, 1, VCAS_F32, large, false, st);
+        if (rc != VCAS_OK) return rc;
+        return splitk_reduce(partials, cntW, dW, R, (int64_t)s.K_out * s.K_in, q.splits, kGatherMinSteps,
+                             gather_step(VCAS_F32, large), st);
+    }
+    int splits = max_splits;
     const int tiles_n = (s.K_in + 63) / 64;
     const int tiles = ((s.K_out + 63) / 64) * tiles_n;
     if (splits > 8) splits = 8;
     const int grid = (tiles * splits + 7) / 8 * 8;
-    launch_timed(1, wgrad_f32_kernel, dim3(grid), dim3(256), 0, st, static_cast<const float *>(G),
+    launch_timed(1, wgrad_f32_far_kernel, dim3(grid), dim3(256), 0, st, static_cast<const float *>(G),
                        static_cast<const float *>(X), row_scale, idxW, cntW, dW, partials, R, s.K_in, s.K_out, tiles_n,
                        tiles, splits, MIN_STEPS);
     if (hipGetLastError() != hipSuccess) return VCAS_EHIP;

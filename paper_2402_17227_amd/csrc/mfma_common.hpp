@@ -1,5 +1,5 @@
-// Device helpers shared by the bf16 MFMA kernels (dgrad in gemm_bf16.hip, wgrad in wgrad_bf16.hip):
-// fragment types, the LDS-direct load, buffer descriptors, tile orders.
+// Device helpers shared by the MFMA kernels (gemm_bf16.hip, wgrad_bf16.hip, gemm_f32.hip):
+// fragment types, the LDS-direct load, buffer descriptors, tile layouts and orders.
 #pragma once
 
 #include <type_traits>
@@ -81,6 +81,30 @@ __device__ __forceinline__ void panel_order_rt(int tile, int tiles_m, int tiles_
     const int width = min(panel_w, tiles_n - panel * panel_w);
     tile_m = in_panel / width;
     tile_n = panel * panel_w + in_panel % width;
+}
+
+// A tile of 128-byte rows (64 bf16 or 32 fp32 along the contraction): slot XOR of a row, and the byte
+// offset of 16-byte slot `slot` (0..7) of tile row `row`
+__device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 7); }
+__device__ __forceinline__ int lds_off(int row, int slot) { return row * 128 + ((slot ^ swz(row)) << 4); }
+
+// The j-th sample (0-based) that is NOT in the ascending list idx[0..cnt).
+__device__ __forceinline__ int nth_missing(const int32_t *idx, int cnt, int j)
+{
+    int lo = 0, hi = cnt;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (idx[mid] - mid > j) hi = mid;
+        else lo = mid + 1;
+    }
+    return j + lo;
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads_outstanding()
+{
+    // s_waitcnt vmcnt(N) only: expcnt and lgkmcnt fields left at "no wait"
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
 template <typename Kern>

@@ -21,24 +21,11 @@
 // block of layers do not depend on each other): workgroup ids are cut into per-layer ranges, so
 // small weight gradients fill the chip together instead of being cut into split-K slices one by
 // one.
-#include "mfma_bf16.hpp"
+#include "wgrad_gather.hpp"
 
 namespace vcas {
 
 // ------------------------------------------------------------------ split-K
-
-// How many of the launched split-K slices do work for a given number of
-// contraction steps, and how many steps each takes.  Used by the GEMM and by
-// the reduction so that both agree.
-__host__ __device__ inline int wgrad_active_splits(int steps_all, int splits, int min_steps, int &per)
-{
-    int active = splits < steps_all / min_steps ? splits : steps_all / min_steps;
-    if (active < 1) active = 1;
-    per = (steps_all + active - 1) / active;
-    if (per < 1) per = 1;
-    active = (steps_all + per - 1) / per;
-    return active < 1 ? 1 : active;
-}
 
 // dW = partial[0] + partial[1] + ... in that order; does nothing when only one
 // split was active (the GEMM wrote dW itself).  `step` is the GEMM's
@@ -88,17 +75,6 @@ vcas_status splitk_reduce(const float *partials, const int32_t *cntW, float *dW,
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, partials, cntW, dW, R, elems,
                        splits, min_steps, step);
     return launch_status();
-}
-
-// Slot XOR of row k of a [64 tokens][columns] tile with SL 16-byte slots per row.  A half-wave's
-// transposing read takes 32 bytes from each of four consecutive rows; the XOR puts them into four
-// different 64-byte bank groups.  Rows of 256 bytes or more all start at bank 0: shift row k by
-// (k mod 4) * 64 bytes.  Rows of 128 bytes alternate between the two halves of the banks already:
-// shift every second pair of rows by 64 bytes.
-template <int SL>
-__device__ __forceinline__ int tile_swz(int k)
-{
-    return SL >= 16 ? (k & 3) * 4 : ((k >> 1) & 1) * 4;
 }
 
 // ------------------------------------------------------------------ batch

@@ -1,0 +1,80 @@
+"""One case on each side of every line at which a launch picks another GEMM kernel, at sizes where that kernel can go
+wrong (ragged edges of its tiles, contraction remainders, a single step, nothing kept): the whole path against the
+oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from workloads import BF16, F32
+
+pytestmark = pytest.mark.gpu
+TOL = {F32: 1e-5, BF16: 1e-2}
+
+
+@pytest.fixture(scope="module")
+def vb():
+    from paper_2402_17227_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+F32_CASES = [
+    # dgrad with 32x32 tiles (at most 256 of them), eight wavefronts per tile; wgrad with 32x32 tiles in slices
+    (3, 11, 8, 8, 0.5, 0.5), (3, 33, 264, 72, 0.7, 0.6), (7, 40, 96, 520, 0.6, 0.5), (40, 64, 64, 136, 1.0, 1.0),
+    # dgrad with 32x64 tiles
+    (5, 131, 552, 200, 1.0, 0.3),
+    # dgrad with 64x64 tiles
+    (9, 233, 456, 72, 1.0, 0.5),
+    # wgrad with 64x64 tiles (768 of them and more): full, remainder and single steps of 32 tokens, nothing kept
+    (4, 47, 1608, 1928, 0.5, 0.5), (2, 16, 1608, 1928, 1.0, 1.0), (2, 5, 1608, 1928, 0.02, 0.02),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fp32_kernels_at_their_edges(vb, case):
+    _against_oracle(F32, *case)
+
+
+def _against_oracle(dtype, N, T, K_in, K_out, rho, nu):
+    from tests.gpu_util import compare_plan, rel_l2, rel_l2_rows, rel_l2_tiles, run_layer_gpu
+    sp = workloads.LayerSpec("edge", dtype, N, T, K_in, K_out, rho, nu, layer=5, seed=31, gen_seed=N + T, token_sigma=0.5)
+    G, X, W = workloads.make_layer(sp)
+    want, want_dX, want_dW = oracle.linear_backward(G, X, W, dtype, N, T, rho, nu, sp.seed, sp.layer, 0)
+    plan, dX, dW = run_layer_gpu(sp, G, X, W)
+    compare_plan(plan, want)
+    assert rel_l2(dX, want_dX) <= TOL[dtype] and rel_l2(dW, want_dW) <= TOL[dtype]
+    assert rel_l2_rows(dX, want_dX) <= 2 * TOL[dtype] and rel_l2_tiles(dW, want_dW) <= 2 * TOL[dtype]
+
+
+def test_fp32_tensors_beyond_32_bit_offsets(vb):
+    """G of more than 2 GiB: rows at both ends of it against a product in double precision."""
+    N, T, K_in, K_out = 16, 4096, 8, 8200
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_F32)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    G = torch.randn((R, K_out), generator=gen, device="cuda")
+    X = torch.randn((R, K_in), generator=gen, device="cuda")
+    W = torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02
+    p = torch.full((N,), 0.5, device="cuda")
+    idxA = torch.tensor([0, N - 1] + [0] * (N - 2), dtype=torch.int32, device="cuda")
+    cntA = torch.tensor([2], dtype=torch.int32, device="cuda")
+    dX = torch.full((R, K_in), float("nan"), device="cuda")
+    vb.vcas_sampled_dgrad(shape, G, W, p, idxA, cntA, dX)
+    kept = torch.cat([torch.arange(T, device="cuda"), torch.arange(R - T, R, device="cuda")])
+    want = 2.0 * (G[kept].double() @ W.double())
+    assert float((dX[kept].double() - want).norm() / want.norm()) <= 1e-5
+    assert float(dX[T:R - T].abs().max()) == 0.0
+    tokens = torch.cat([kept[:200], kept[-57:]]).to(torch.int32)
+    idxW = torch.zeros(R, dtype=torch.int32, device="cuda")
+    idxW[:tokens.numel()] = tokens
+    cntW = torch.tensor([tokens.numel()], dtype=torch.int32, device="cuda")
+    scale = torch.rand(R, generator=gen, device="cuda") + 1.0
+    dW = torch.full((K_out, K_in), float("nan"), device="cuda")
+    ws = vb.make_workspace(shape)
+    vb.vcas_sampled_wgrad(shape, G, X, scale, idxW, cntW, dW, ws)
+    t = tokens.long()
+    want = (G[t].double() * scale[t].double()[:, None]).t() @ X[t].double()
+    assert float((dW.double() - want).norm() / want.norm()) <= 1e-5
