@@ -497,7 +497,7 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
 static bool shares_weight_half(const vcas_layer_args &a, const vcas_layer_args &b)
 {
     const vcas_shape &s = a.shape;
-    return b.sibling != 0 && same_shape(s, b.shape) && (int64_t)s.N * s.T <= 16384 && !a.xsq_forward &&
+    return b.sibling != 0 && same_shape(s, b.shape) && (int64_t)s.N * s.T <= 65536 && !a.xsq_forward &&
            !b.xsq_forward && (a.token_sampling != 0) == (b.token_sampling != 0);
 }
 
