@@ -39,9 +39,6 @@ vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq
 vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int K, int T,
                                             hipStream_t st);
 vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *u, hipStream_t st);
-vcas_status sampler_w(const float *gsq, float *xsq, int zero_dropped_xsq, const float *p, const uint8_t *maskA,
-                      const float *u, int N, int T, double budget, int token_sampling, int prepared, float *score,
-                      float *q, uint8_t *maskW, float *scaleW, int32_t *idxW, int32_t *cntW, hipStream_t st);
 vcas_status row_sumsq_pair(const void *G, int K_out, float *gsq, const void *X, int K_in, float *xsq, int dtype,
                            int64_t R, const vcas_rng &rng, uint32_t stream_id, float *uniforms, float *root_g,
                            float *root_x, int T, const uint8_t *keep_g, hipStream_t st);
@@ -300,6 +297,28 @@ static bool norms_together(const vcas_shape &s)
     return (int64_t)s.N * s.T * s.K_in * elem_bytes(s.dtype) <= ((int64_t)16 << 20);
 }
 
+// SampleW's arguments of one layer.
+static SampleWProblem sample_w_problem(const vcas_shape &s, double rho, double nu, const vcas_plan &pl, void *workspace)
+{
+    const WorkspaceLayout l = workspace_layout(&s);
+    unsigned char *base = static_cast<unsigned char *>(workspace);
+    SampleWProblem w;
+    w.gsq = pl.gsq;
+    w.xsq = pl.xsq;
+    w.p = pl.p;
+    w.maskA = pl.maskA;
+    w.u = reinterpret_cast<float *>(base + l.uniforms);
+    w.budget = (double)((int64_t)s.N * s.T) * rho * nu;
+    w.score = pl.score;
+    w.q = pl.q;
+    w.maskW = pl.maskW;
+    w.scaleW = pl.scaleW;
+    w.idxW = pl.idxW;
+    w.cntW = pl.cntW;
+    w.rule = reinterpret_cast<double *>(base + l.rule);
+    return w;
+}
+
 static float *uniforms_of(const vcas_shape &s, void *workspace)
 {
     return reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + workspace_layout(&s).uniforms);
@@ -398,8 +417,9 @@ static vcas_status weight_half(const vcas_shape &s, const void *G, const void *X
         VCAS_TRY(row_sumsq_scores_uniforms(X, s.dtype, R, s.K_in, s.T, pl.maskA, pl.xsq, pl.gsq, pl.p, pl.score, rng, 1u,
                                            token_sampling ? u : nullptr, st));
     // what the norm passes have left in score and q: roots (together) or the scores themselves
-    VCAS_TRY(sampler_w(pl.gsq, pl.xsq, together ? 1 : 0, pl.p, pl.maskA, u, s.N, s.T, (double)R * rho * nu,
-                       token_sampling, together ? 1 : 2, pl.score, pl.q, pl.maskW, pl.scaleW, pl.idxW, pl.cntW, st));
+    SampleWGroup sampler = {};
+    sampler.prob[0] = sample_w_problem(s, rho, nu, pl, workspace);
+    VCAS_TRY(sampler_w_group(sampler, 1, together ? 1 : 0, s.N, s.T, token_sampling, together ? 1 : 2, st));
     if (dW)
         VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st));
     return VCAS_OK;
@@ -492,12 +512,11 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
 }
 
 // Can layer b share the SampleW launches of layer a in front of it?  Siblings of one shape and
-// dtype with the same kind of token sampling, the rows of X still to be swept, and few enough
-// rows for the one-workgroup sampler.
+// dtype with the same kind of token sampling and the rows of X still to be swept.
 static bool shares_weight_half(const vcas_layer_args &a, const vcas_layer_args &b)
 {
     const vcas_shape &s = a.shape;
-    return b.sibling != 0 && same_shape(s, b.shape) && (int64_t)s.N * s.T <= 65536 && !a.xsq_forward &&
+    return b.sibling != 0 && same_shape(s, b.shape) && !a.xsq_forward &&
            !b.xsq_forward && (a.token_sampling != 0) == (b.token_sampling != 0);
 }
 
@@ -519,19 +538,7 @@ static vcas_status weight_half_siblings(const vcas_layer_args *layers, int n, hi
         norms.out[i] = a.plan.xsq;
         norms.job[i] = {token_sampling ? u : nullptr, a.rng.seed, a.rng.layer, 1u, a.rng.draw, a.rng.draw_offset};
         norms.sj[i] = {a.plan.gsq, a.plan.p, a.plan.score};
-        SampleWProblem &w = samplers.prob[i];
-        w.gsq = a.plan.gsq;
-        w.xsq = a.plan.xsq;
-        w.p = a.plan.p;
-        w.maskA = a.plan.maskA;
-        w.u = u;
-        w.budget = (double)R * a.rho * a.nu;
-        w.score = a.plan.score;
-        w.q = a.plan.q;
-        w.maskW = a.plan.maskW;
-        w.scaleW = a.plan.scaleW;
-        w.idxW = a.plan.idxW;
-        w.cntW = a.plan.cntW;
+        samplers.prob[i] = sample_w_problem(s, a.rho, a.nu, a.plan, a.workspace);
     }
     VCAS_TRY(row_sumsq_scores_uniforms_group(norms, n, s.dtype, R, s.K_in, s.T, st));
     return sampler_w_group(samplers, n, 0, s.N, s.T, token_sampling, 2, st);

@@ -57,6 +57,7 @@ struct SampleWProblem {
     uint8_t *maskW;
     float *scaleW;
     int32_t *idxW, *cntW;
+    double *rule;   // [2], scratch of the workspace: the keep rule of a long vector
 };
 struct SampleWGroup {
     SampleWProblem prob[kMaxSiblings];

@@ -83,7 +83,7 @@ __device__ __forceinline__ void plan_tail(const PlanArgs &a, uint32_t draw)
             a.score[t] = sc[j];
         }
     }
-    sample_w_finish<E, false>(sc, uu, nullptr, &table, a.p, a.maskA, R, T, a.budget_w, a.token_sampling, a.q, a.maskW,
+    sample_w_finish<E>(sc, uu, &table, a.p, a.maskA, R, T, a.budget_w, a.token_sampling, a.q, a.maskW,
                               a.scaleW, a.idxW, a.cntW);
 }
 

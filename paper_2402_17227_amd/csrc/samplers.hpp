@@ -51,6 +51,7 @@ __device__ __forceinline__ int ballot_count(bool c) { return __builtin_popcountl
 // fixed at one in some round exactly if the largest c any round has tried pushes it to one (the
 // product is monotone in c and in the score, rounding included), and the others get the last round's c.
 // So two numbers stand for the whole vector, and no element carries a state from round to round.
+// (Turning c_cap into the smallest float it caps, for a fp32 compare, costs a round more than it saves.)
 struct KeepRule {
     double c_cap, c;
 };
@@ -86,7 +87,7 @@ __device__ __forceinline__ KeepRule keep_rule_regs(const float (&a)[E], double b
     double S;
     int nonzero;
     block_totals_1024(part, cnt, sd[0], si[0], S, nonzero);
-    if (budget >= (double)nonzero) return {__builtin_inf(), 0.0};
+    if (budget >= (double)nonzero) return {__builtin_inf(), 0.0};   // every positive score is kept
     KeepRule k = {0.0, 0.0};
     int ncap = 0;
     cnt = 0;
@@ -125,12 +126,60 @@ __device__ __forceinline__ KeepRule keep_rule_regs(const float (&a)[E], double b
     }
 }
 
+// The same from memory: every round reads the n scores again.
+__device__ __forceinline__ KeepRule keep_rule_memory(const float *__restrict__ score, int n, double budget)
+{
+    __shared__ double sd[2][16];
+    __shared__ int si[2][16];
+    // the sum over what c_cap does not fix, and how many it fixes (c_cap = 0: how many scores are positive)
+    auto pass = [&](double c_cap, double &part, int &cnt) {
+        part = 0.0;
+        cnt = 0;
+        for (int i0 = threadIdx.x; i0 < n; i0 += 8 * 1024) {
+            float a[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[j] = score[min(i0 + 1024 * j, n - 1)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool pos = i0 + 1024 * j < n && a[j] > 0.0f;
+                const bool cap = pos && c_cap * (double)a[j] >= 1.0;
+                part += pos && !cap ? (double)a[j] : 0.0;
+                cnt += c_cap == 0.0 ? pos : cap;
+            }
+        }
+    };
+    double part, S;
+    int cnt, nonzero;
+    pass(0.0, part, cnt);
+    block_sum_pair_1024(part, cnt, sd[0], si[0], S, nonzero);
+    if (budget >= (double)nonzero) return {__builtin_inf(), 0.0};   // every positive score is kept
+    KeepRule k = {0.0, 0.0};
+    int ncap = 0, flip = 1;
+    for (;;) {
+        const double rem = budget - (double)ncap;
+        if (!(S > 0.0) || !(rem > 0.0)) {
+            k.c = 0.0;
+            return k;
+        }
+        k.c = rem / S;
+        k.c_cap = k.c > k.c_cap ? k.c : k.c_cap;
+        pass(k.c_cap, part, cnt);
+        double S_next;
+        int capped;
+        block_sum_pair_1024(part, cnt, sd[flip], si[flip], S_next, capped);
+        flip ^= 1;
+        if (capped == ncap) return k;
+        ncap = capped;
+        S = S_next;
+    }
+}
+
 // Ascending list of the kept indices and their count.  Bit j of `kept` = element j of this thread, index
 // tid + 1024 j, so ascending order is j, then wavefront, then lane.  Every wavefront counts its kept
 // lanes per j with a ballot; the first wavefront turns the 16 E counts into bases; a lane's position is
 // its base plus the kept lanes below it.
 template <int E>
-__device__ __forceinline__ void compact_regs(uint64_t kept, int32_t *__restrict__ idx, int32_t *__restrict__ count)
+__device__ __forceinline__ void compact_regs(uint32_t kept, int32_t *__restrict__ idx, int32_t *__restrict__ count)
 {
     constexpr int CNT = 16 * E, PER = (CNT + 63) / 64;
     __shared__ int counts[CNT + 1];
@@ -252,49 +301,38 @@ __device__ __forceinline__ int sample_of(int t, int T, uint32_t magic)
     return T > 1 ? (int)__umulhi((uint32_t)t, magic) : t;
 }
 
-// From the scores on: q, mask, scale and kept list.  a: this thread's scores (zero past the end).  LOOK:
-// uniforms are read here, eight at a time, instead of being handed over in uu (longer vectors).
-template <int E, bool LOOK>
-__device__ __forceinline__ void sample_w_finish(const float (&a)[E], const float *uu, const float *__restrict__ u,
-                                                const SampleTable *table, const float *__restrict__ p,
-                                                const uint8_t *__restrict__ maskA, int R, int T, double budget,
-                                                int token_sampling, float *__restrict__ q, uint8_t *__restrict__ maskW,
-                                                float *__restrict__ scaleW, int32_t *__restrict__ idxW,
-                                                int32_t *__restrict__ cntW)
+// From the scores on: q, mask, scale and kept list.  a: this thread's scores (zero past the end), uu: its uniforms.
+template <int E>
+__device__ __forceinline__ void sample_w_finish(const float (&a)[E], const float (&uu)[E], const SampleTable *table,
+                                                const float *__restrict__ p, const uint8_t *__restrict__ maskA, int R, int T,
+                                                double budget, int token_sampling, float *__restrict__ q,
+                                                uint8_t *__restrict__ maskW, float *__restrict__ scaleW,
+                                                int32_t *__restrict__ idxW, int32_t *__restrict__ cntW)
 {
     const int tid = threadIdx.x;
     const uint32_t magic = sample_magic(T);
     KeepRule rule = {0.0, 0.0};
     if (token_sampling) rule = keep_rule_regs<E>(a, budget);
-    uint64_t kept = 0;
-    constexpr int B = LOOK ? 8 : E;
+    uint32_t kept = 0;
 #pragma unroll
-    for (int j0 = 0; j0 < E; j0 += B) {
-        float ub[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j)
-            ub[j] = LOOK ? (token_sampling ? u[min(tid + 1024 * (j0 + j), R - 1)] : 0.0f) : uu[j];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int t = tid + 1024 * (j0 + j);
-            if (t < R) {
-                const int i = sample_of(t, T, magic);
-                bool m;
-                float qv;
-                if (token_sampling) {
-                    qv = keep_prob(a[j0 + j], rule);
-                    m = ub[j] < qv;
-                } else {
-                    m = table ? table->keep[i] != 0 : maskA[i] != 0;
-                    qv = m ? 1.0f : 0.0f;
-                }
-                kept |= (uint64_t)(m ? 1 : 0) << (j0 + j);
-                q[t] = qv;
-                maskW[t] = m ? 1 : 0;
-                scaleW[t] = m ? 1.0f / ((table ? table->p[i] : p[i]) * qv) : 0.0f;
+    for (int j = 0; j < E; ++j) {
+        const int t = tid + 1024 * j;
+        if (t < R) {
+            const int i = sample_of(t, T, magic);
+            bool m;
+            float qv;
+            if (token_sampling) {
+                qv = keep_prob(a[j], rule);
+                m = uu[j] < qv;
+            } else {
+                m = table ? table->keep[i] != 0 : maskA[i] != 0;
+                qv = m ? 1.0f : 0.0f;
             }
+            kept |= (m ? 1u : 0u) << j;
+            q[t] = qv;
+            maskW[t] = m ? 1 : 0;
+            scaleW[t] = m ? 1.0f / ((table ? table->p[i] : p[i]) * qv) : 0.0f;
         }
-        if (LOOK) __builtin_amdgcn_sched_barrier(0);   // a batch at a time: the scores fill half the registers
     }
     compact_regs<E>(kept, idxW, cntW);
 }
@@ -313,65 +351,57 @@ __device__ __forceinline__ void sampler_w_fast_body(const float *__restrict__ gs
                                                     int32_t *__restrict__ idxW, int32_t *__restrict__ cntW)
 {
     __shared__ SampleTable table;
-    // up to 16 elements a thread: every load of the vectors first, with no condition on a loaded value
-    // in between, so that they are all in flight together; longer: in batches of eight
-    constexpr bool LONG = E > 16;
-    constexpr int B = LONG ? 8 : E;
     const int tid = threadIdx.x;
     const int R = N * T;
     const bool tabled = N <= 1024;
     const uint32_t magic = sample_magic(T);
-    float a[E], uu[LONG ? 1 : E];
+    // Every load of the vectors first, with no condition on a loaded value in between, so that
+    // they are all in flight together (rows past the end re-read the last row and are ignored).
+    float a[E], rx[E], uu[E];
 #pragma unroll
-    for (int j0 = 0; j0 < E; j0 += B) {
-        float rx[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {   // rows past the end re-read the last row and are ignored
-            const int t = min(tid + 1024 * (j0 + j), R - 1);
-            if (!LONG) uu[j] = token_sampling ? u[t] : 0.0f;
-            if (prepared == kFromSquares) {
-                a[j0 + j] = gsq[t];
-                rx[j] = xsq[t];
-            } else {
-                a[j0 + j] = score[t];
-                rx[j] = prepared == kRootsGiven ? q[t] : 0.0f;
-            }
+    for (int j = 0; j < E; ++j) {
+        const int t = min(tid + 1024 * j, R - 1);
+        uu[j] = token_sampling ? u[t] : 0.0f;
+        if (prepared == kFromSquares) {
+            a[j] = gsq[t];
+            rx[j] = xsq[t];
+        } else {
+            a[j] = score[t];
+            rx[j] = prepared == kRootsGiven ? q[t] : 0.0f;
         }
-        if (j0 == 0) {
-            if (tabled && tid < N) {
-                const float pi = p[tid];
-                const uint8_t k = maskA[tid];
-                table.p[tid] = pi;
-                table.keep[tid] = k;
-                table.pinv[tid] = k ? 1.0f / pi : 0.0f;
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int t = tid + 1024 * (j0 + j);
-            if (t >= R) {
-                a[j0 + j] = 0.0f;
-            } else if (prepared != kScoresGiven) {
-                const int i = sample_of(t, T, magic);
-                const bool keep = tabled ? table.keep[i] != 0 : maskA[i] != 0;
-                const float rg = prepared == kRootsGiven ? a[j0 + j] : __builtin_sqrtf(a[j0 + j]);
-                const float rxx = prepared == kRootsGiven ? rx[j] : __builtin_sqrtf(rx[j]);
-                a[j0 + j] = 0.0f;
-                if (keep) {
-                    const float inv = tabled ? table.pinv[i] : 1.0f / p[i];
-                    const float s1 = inv * rg;
-                    a[j0 + j] = s1 * rxx;
-                } else if (zero_dropped_xsq) {
-                    xsq[t] = 0.0f;
-                }
-                score[t] = a[j0 + j];
-            }
-        }
-        if (LONG) __builtin_amdgcn_sched_barrier(0);
     }
-    sample_w_finish<E, LONG>(a, uu, u, tabled ? &table : nullptr, p, maskA, R, T, budget, token_sampling, q, maskW, scaleW,
-                             idxW, cntW);
+    if (tabled) {
+        if (tid < N) {
+            const float pi = p[tid];
+            const uint8_t k = maskA[tid];
+            table.p[tid] = pi;
+            table.keep[tid] = k;
+            table.pinv[tid] = k ? 1.0f / pi : 0.0f;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const int t = tid + 1024 * j;
+        if (t >= R) {
+            a[j] = 0.0f;
+        } else if (prepared != kScoresGiven) {
+            const int i = sample_of(t, T, magic);
+            const bool keep = tabled ? table.keep[i] != 0 : maskA[i] != 0;
+            const float rg = prepared == kRootsGiven ? a[j] : __builtin_sqrtf(a[j]);
+            const float rxx = prepared == kRootsGiven ? rx[j] : __builtin_sqrtf(rx[j]);
+            a[j] = 0.0f;
+            if (keep) {
+                const float inv = tabled ? table.pinv[i] : 1.0f / p[i];
+                const float s1 = inv * rg;
+                a[j] = s1 * rxx;
+            } else if (zero_dropped_xsq) {
+                xsq[t] = 0.0f;
+            }
+            score[t] = a[j];
+        }
+    }
+    sample_w_finish<E>(a, uu, tabled ? &table : nullptr, p, maskA, R, T, budget, token_sampling, q, maskW, scaleW, idxW, cntW);
 }
 
 }  // namespace vcas

@@ -203,21 +203,6 @@ __global__ __launch_bounds__(1024) void sampler_a_group_kernel(SampleAGroup grp,
     sampler_a_fast_body(q.gsq, N, T, q.budget, q.seed, q.layer, draw, q.gnorm, q.p, q.maskA, q.idxA, q.cntA, nullptr);
 }
 
-template <int E>
-__global__ __launch_bounds__(1024) void sampler_w_fast_kernel(const float *__restrict__ gsq,
-                                                              float *__restrict__ xsq, int zero_dropped_xsq,
-                                                              const float *__restrict__ p,
-                                                              const uint8_t *__restrict__ maskA,
-                                                              const float *__restrict__ u, int N, int T, double budget,
-                                                              int token_sampling, int prepared,
-                                                              float *__restrict__ score, float *__restrict__ q,
-                                                              uint8_t *__restrict__ maskW, float *__restrict__ scaleW,
-                                                              int32_t *__restrict__ idxW, int32_t *__restrict__ cntW)
-{
-    sampler_w_fast_body<E>(gsq, xsq, zero_dropped_xsq, p, maskA, u, N, T, budget, token_sampling, prepared, score, q,
-                           maskW, scaleW, idxW, cntW);
-}
-
 // SampleW of up to kMaxSiblings layers of one shape, one workgroup per layer.
 template <int E>
 __global__ __launch_bounds__(1024) void sampler_w_group_kernel(SampleWGroup grp, int zero_dropped_xsq, int N, int T,
@@ -264,54 +249,113 @@ __global__ __launch_bounds__(256) void uniforms_kernel(int64_t R, uint64_t seed,
     if (r < R) u[r] = philox_uniform(seed, layer, stream_id, draw, (uint32_t)r);
 }
 
-// SampleW: leverage scores, q, Bernoulli mask over tokens (uniforms given),
-// per-token scale, kept list.  With token_sampling == 0 every token of a kept
-// sample is kept with q = 1.
-__global__ __launch_bounds__(1024) void sampler_w_kernel(const float *__restrict__ gsq, float *__restrict__ xsq,
-                                                         int zero_dropped_xsq, const float *__restrict__ p,
-                                                         const uint8_t *__restrict__ maskA,
-                                                         const float *__restrict__ u, int N, int T, double budget,
-                                                         int token_sampling, int prepared,
-                                                         float *__restrict__ score, float *__restrict__ q,
-                                                         uint8_t *__restrict__ maskW, float *__restrict__ scaleW,
-                                                         int32_t *__restrict__ idxW, int32_t *__restrict__ cntW)
+// ---- SampleW of more rows than one workgroup's registers hold comfortably ----------------------
+// Only the rounds of the keep probabilities need the whole vector in one place.  Launches: scores
+// (many workgroups, where the norm pass has not written them), the rounds (one workgroup: reads R
+// floats and writes the two numbers of a KeepRule), what is elementwise given the rule (many
+// workgroups), the kept list (many workgroups).  One workgroup for all of it took 227 us at R = 65536 from memory and 132 us with
+// the scores in (spilling) registers; see sampler_w_group for the line.
+
+__global__ __launch_bounds__(256) void sampler_w_scores_kernel(SampleWGroup grp, int R, int T, int prepared,
+                                                               int zero_dropped_xsq)
 {
+    const SampleWProblem &w = grp.prob[blockIdx.y];
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= R) return;
+    const int i = t / T;
+    float s = 0.0f;
+    if (w.maskA[i]) {
+        const float inv = 1.0f / w.p[i];
+        const float a = inv * (prepared == kRootsGiven ? w.score[t] : __builtin_sqrtf(w.gsq[t]));
+        s = a * (prepared == kRootsGiven ? w.q[t] : __builtin_sqrtf(w.xsq[t]));
+    } else if (zero_dropped_xsq) {
+        w.xsq[t] = 0.0f;
+    }
+    w.score[t] = s;
+}
+
+// E elements per thread in registers, or (E = 0) every round reads the scores again.
+template <int E>
+__global__ __launch_bounds__(1024) void sampler_w_rule_kernel(SampleWGroup grp, int R)
+{
+    const SampleWProblem &w = grp.prob[blockIdx.x];
     const int tid = threadIdx.x;
-    const int R = N * T;
-    for (int t = tid; t < R && prepared != kScoresGiven; t += 1024) {
-        const int i = t / T;
-        float s = 0.0f;
-        if (maskA[i]) {
-            const float inv = 1.0f / p[i];
-            const float a = inv * (prepared == kRootsGiven ? score[t] : __builtin_sqrtf(gsq[t]));
-            s = a * (prepared == kRootsGiven ? q[t] : __builtin_sqrtf(xsq[t]));
-        } else if (zero_dropped_xsq) {
-            xsq[t] = 0.0f;
-        }
-        score[t] = s;
+    KeepRule rule;
+    if constexpr (E > 0) {
+        float a[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) a[j] = w.score[min(tid + 1024 * j, R - 1)];
+#pragma unroll
+        for (int j = 0; j < E; ++j) a[j] = tid + 1024 * j < R ? a[j] : 0.0f;
+        rule = keep_rule_regs<E>(a, w.budget);
+    } else {
+        rule = keep_rule_memory(w.score, R, w.budget);
     }
-    __syncthreads();
+    if (tid == 0) {
+        w.rule[0] = rule.c_cap;
+        w.rule[1] = rule.c;
+    }
+}
+
+// q, mask and scale of every row.
+__global__ __launch_bounds__(256) void sampler_w_apply_kernel(SampleWGroup grp, int R, int T, int token_sampling)
+{
+    const SampleWProblem &w = grp.prob[blockIdx.y];
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= R) return;
+    const int i = t / T;
+    float qv;
+    bool m;
     if (token_sampling) {
-        keep_probs_block(score, R, budget, q);
-        __syncthreads();
+        const KeepRule rule = {w.rule[0], w.rule[1]};
+        qv = keep_prob(w.score[t], rule);
+        m = w.u[t] < qv;
+    } else {
+        m = w.maskA[i] != 0;
+        qv = m ? 1.0f : 0.0f;
     }
-    for (int t = tid; t < R; t += 1024) {
-        const int i = t / T;
-        uint8_t m;
-        float qt;
-        if (token_sampling) {
-            qt = q[t];
-            m = u[t] < qt ? 1 : 0;
-        } else {
-            m = maskA[i] ? 1 : 0;
-            qt = m ? 1.0f : 0.0f;
-            q[t] = qt;
-        }
-        maskW[t] = m;
-        scaleW[t] = m ? 1.0f / (p[i] * qt) : 0.0f;
+    w.q[t] = qv;
+    w.maskW[t] = m ? 1 : 0;
+    w.scaleW[t] = m ? 1.0f / (w.p[i] * qv) : 0.0f;
+}
+
+// Kept list of 1024 rows per workgroup.  The place of a row in the ascending list is the number of kept
+// rows in front of it: every workgroup adds up the mask bytes before its own rows again (a few 16-byte
+// loads per thread), which is cheaper than an exchange between workgroups.
+__global__ __launch_bounds__(1024) void sampler_w_list_kernel(SampleWGroup grp, int R)
+{
+    __shared__ int wave_count[16], wave_before[16];
+    const SampleWProblem &w = grp.prob[blockIdx.y];
+    const uint8_t *mask = w.maskW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int first = blockIdx.x * 1024;
+    // [0, head) and [head + 16 * vecs, first) byte by byte, the aligned part in between by 16
+    const int head = min(first, (int)(-reinterpret_cast<uintptr_t>(mask) & 15u));
+    const int vecs = (first - head) / 16, tail = head + 16 * vecs;
+    int before = 0;
+    for (int v = tid; v < vecs; v += 1024) {
+        const uint4 b = *reinterpret_cast<const uint4 *>(mask + head + 16 * v);   // bytes of 0 and 1: a popcount adds them
+        before += __builtin_popcount(b.x) + __builtin_popcount(b.y) + __builtin_popcount(b.z) + __builtin_popcount(b.w);
+    }
+    if (tid < head) before += mask[tid];
+    if (tid < first - tail) before += mask[tail + tid];
+    before = wave_sum_int(before);
+    const int t = first + tid;
+    const bool m = t < R && mask[t] != 0;
+    const uint64_t b = __ballot(m);
+    if (lane == 0) {
+        wave_before[wave] = before;
+        wave_count[wave] = __builtin_popcountll(b);
     }
     __syncthreads();
-    compact_block(maskW, R, idxW, cntW);
+    int base = 0, total = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        base += wave_before[v] + (v < wave ? wave_count[v] : 0);
+        total += wave_before[v] + wave_count[v];
+    }
+    if (m) w.idxW[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = t;
+    if (tid == 0 && first + 1024 >= R) *w.cntW = total;
 }
 
 // ---- host launchers ---------------------------------------------------------
@@ -390,38 +434,15 @@ vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *
     return launch_status();
 }
 
-vcas_status sampler_w(const float *gsq, float *xsq, int zero_dropped_xsq, const float *p, const uint8_t *maskA,
-                      const float *u, int N, int T, double budget, int token_sampling, int prepared, float *score,
-                      float *q, uint8_t *maskW, float *scaleW, int32_t *idxW, int32_t *cntW, hipStream_t st)
-{
-    const int64_t R = (int64_t)N * T;
-#define VCAS_SAMPLER_W_ARGS                                                                                      \
-    gsq, xsq, zero_dropped_xsq, p, maskA, u, N, T, budget, token_sampling, prepared, score, q, maskW, scaleW, idxW, \
-        cntW
-    // elements per thread: the smallest power of two that holds the vector in one workgroup's registers
-#define VCAS_SAMPLER_W(E) \
-    if (R <= 1024 * (E)) { \
-        hipLaunchKernelGGL(sampler_w_fast_kernel<E>, dim3(1), dim3(1024), 0, st, VCAS_SAMPLER_W_ARGS); \
-        return launch_status(); \
-    }
-    VCAS_SAMPLER_W(1)
-    VCAS_SAMPLER_W(4)
-    VCAS_SAMPLER_W(8)
-    VCAS_SAMPLER_W(16)
-    VCAS_SAMPLER_W(32)
-    VCAS_SAMPLER_W(64)
-#undef VCAS_SAMPLER_W
-    hipLaunchKernelGGL(sampler_w_kernel, dim3(1), dim3(1024), 0, st, VCAS_SAMPLER_W_ARGS);
-#undef VCAS_SAMPLER_W_ARGS
-    return launch_status();
-}
-
-// sampler_w for n <= kMaxSiblings layers with at most 65536 rows each in one launch
+// SampleW of n <= kMaxSiblings layers with one N and T in one set of launches.  Up to 16384 rows one
+// workgroup per layer does everything; beyond, see sampler_w_rule_kernel and what
+// follows it.
 vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq, int N, int T, int token_sampling,
                             int prepared, hipStream_t st)
 {
-    const int64_t R = (int64_t)N * T;
-    if (n < 1 || n > kMaxSiblings || R > 65536) return VCAS_EINVAL;
+    const int64_t R64 = (int64_t)N * T;
+    if (n < 1 || n > kMaxSiblings || R64 > (int64_t)1 << 30) return VCAS_EINVAL;
+    const int R = (int)R64;
 #define VCAS_SAMPLER_W(E) \
     if (R <= 1024 * (E)) { \
         hipLaunchKernelGGL(sampler_w_group_kernel<E>, dim3(n), dim3(1024), 0, st, grp, zero_dropped_xsq, N, T, \
@@ -432,10 +453,17 @@ vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq
     VCAS_SAMPLER_W(4)
     VCAS_SAMPLER_W(8)
     VCAS_SAMPLER_W(16)
-    VCAS_SAMPLER_W(32)
-    VCAS_SAMPLER_W(64)
 #undef VCAS_SAMPLER_W
-    return VCAS_EINVAL;
+    if (prepared != kScoresGiven)
+        hipLaunchKernelGGL(sampler_w_scores_kernel, dim3((R + 255) / 256, n), dim3(256), 0, st, grp, R, T, prepared, zero_dropped_xsq);
+    if (token_sampling) {
+        if (R <= 32768) hipLaunchKernelGGL(sampler_w_rule_kernel<32>, dim3(n), dim3(1024), 0, st, grp, R);
+        else if (R <= 65536) hipLaunchKernelGGL(sampler_w_rule_kernel<64>, dim3(n), dim3(1024), 0, st, grp, R);
+        else hipLaunchKernelGGL(sampler_w_rule_kernel<0>, dim3(n), dim3(1024), 0, st, grp, R);
+    }
+    hipLaunchKernelGGL(sampler_w_apply_kernel, dim3((R + 255) / 256, n), dim3(256), 0, st, grp, R, T, token_sampling);
+    hipLaunchKernelGGL(sampler_w_list_kernel, dim3((R + 1023) / 1024, n), dim3(1024), 0, st, grp, R);
+    return launch_status();
 }
 
 }  // namespace vcas

@@ -68,7 +68,7 @@ __device__ __forceinline__ void lds_direct_load4(i32x4 desc, uint32_t lds_base, 
 template <bool BF16, int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF, bool SCALED>
 __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local_id)
 {
-    constexpr int NW = WM * WN * WK, NT = NW * 64, E = BF16 ? 2 : 4;
+    constexpr int NW = WM * WN * WK, E = BF16 ? 2 : 4;
     constexpr int BM = PA / E, BN = PB / E;                       // columns of a tile
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int AI = SK * PA / 1024 / NW, BI = SK * PB / 1024 / NW;   // LDS-direct loads per wavefront and step
