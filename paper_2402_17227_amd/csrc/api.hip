@@ -1,6 +1,7 @@
 // C ABI of the VCAS gfx950 library: argument checks on the host, then kernel
 // launches on the caller's stream.  See include/vcas.h for the contract.
-#include "groups.hpp"
+#include "probe.hpp"
+#include "wgrad_gather.hpp"
 
 namespace vcas {
 
@@ -95,59 +96,6 @@ __global__ void fill_zero_kernel(uint32_t *p, size_t n)
 {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
-}
-
-// ---- variance probe reductions (fp64) ---------------------------------------
-
-// out[slot] (+)= weight * sum_i (1-p_i)/p_i * n_i^2 over p_i > 0; one block.
-__global__ __launch_bounds__(256) void var_closed_kernel(const float *__restrict__ prob, const float *__restrict__ val,
-                                                         int64_t n, int square_val, double weight, int accumulate,
-                                                         double *__restrict__ out)
-{
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) {
-        const double pr = prob[i];
-        if (pr > 0.0) {
-            const double v = val[i];
-            acc += (1.0 - pr) / pr * (square_val ? v * v : v);
-        }
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 128; h >= 1; h >>= 1) {
-        if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = (accumulate ? *out : 0.0) + weight * sh[0];
-}
-
-// per-block partial sums of (a-b)^2, then a one-block pass adds them in order
-__global__ __launch_bounds__(256) void sq_diff_partial_kernel(const float *__restrict__ a, const float *__restrict__ b,
-                                                              int64_t n, double *__restrict__ partial)
-{
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const double d = (double)a[i] - (double)b[i];
-        acc += d * d;
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 128; h >= 1; h >>= 1) {
-        if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
-}
-
-__global__ __launch_bounds__(64) void sq_diff_final_kernel(const double *__restrict__ partial, int blocks,
-                                                           double weight, double *__restrict__ out)
-{
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int i = 0; i < blocks; ++i) s += partial[i];
-    *out += weight * s;
 }
 
 // J: elementwise Jacobian [R, K_in] in the layer dtype, multiplied into dX (null: none);
@@ -264,7 +212,7 @@ static size_t wgrad_partial_bytes(const vcas_shape &s)
 static size_t wgrad_scratch_bytes(const vcas_shape &s)
 {
     const WorkspaceLayout w = workspace_layout(&s);
-    return wgrad_partial_bytes(s) + (w.total - w.packed);
+    return wgrad_partial_bytes(s) + w.packed_bytes;
 }
 
 static bool plan_complete(const vcas_plan *pl)
@@ -630,6 +578,158 @@ static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, cons
     if (!ev || hipEventRecord(ev, st) != hipSuccess || hipStreamWaitEvent(side, ev, 0) != hipSuccess) return VCAS_EHIP;
     if (dX) VCAS_TRY(dispatch_dgrad(s, G, W, pl.p, pl.idxA, pl.cntA, dX, nullptr, true, (int64_t)((double)R * rho + 0.5), st));
     return weight_half(s, G, X, rho, nu, rng, token_sampling, pl, dW, workspace, side);
+}
+
+// The probe in chunks of up to kProbeDraws mask draws (see probe.hip).  The row norms and the exact gradient
+// come first, once; the vectors of a chunk's draws lie in the workspace, those of the very last draw
+// in the plan.
+static vcas_status variance_probe(const vcas_shape &s, const void *G, const void *X, double rho, double nu,
+                                  const vcas_rng &base, int M, const vcas_plan &pl, double *out, unsigned char *ws,
+                                  hipStream_t st)
+{
+    const WorkspaceLayout w = workspace_layout(&s);
+    const int64_t R = (int64_t)s.N * s.T, elems = (int64_t)s.K_out * s.K_in;
+    float *exact = reinterpret_cast<float *>(ws + w.probe_exact);
+
+    // dW at keep ratio one: every token with scale one
+    VCAS_TRY(probe_begin(pl.scaleW, pl.idxW, pl.cntW, out, R, st));
+    VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, exact, ws, st));
+    VCAS_TRY(row_sumsq_pair(G, s.K_out, pl.gsq, X, s.K_in, pl.xsq, s.dtype, R, base, 1u, nullptr, nullptr, nullptr, s.T,
+                            nullptr, st));
+
+    // scratch, over the packed operand of the exact gradient
+    unsigned char *at = ws + w.packed;
+    auto take = [&](size_t bytes) {
+        unsigned char *here = at;
+        at += probe_pad(bytes);
+        return here;
+    };
+    float *scale_a = reinterpret_cast<float *>(take(4 * R));
+    const bool fits = offsets_fit(s);
+    // per-tile sums where the Monte-Carlo gradients of the earlier form were: 16 doubles per tile of at least
+    // 32x32 floats
+    double *tile_sums = reinterpret_cast<double *>(ws + w.probe_draw);
+    unsigned char *const chunk_at = at;
+    for (int j0 = 0; j0 < M; j0 += kProbeDraws) {
+        const int n = M - j0 < kProbeDraws ? M - j0 : kProbeDraws;
+        at = chunk_at;
+        ProbeDraws draws = {};
+        SampleAGroup group_a = {};
+        SampleWGroup group_w = {};
+        GatherTask tasks[2 * kProbeDraws] = {};
+        for (int k = 0; k < n; ++k) {
+            const bool last = j0 + k == M - 1;
+            float *gnorm = pl.gnorm, *p = pl.p, *score = pl.score, *q = pl.q, *scale = pl.scaleW, *u;
+            uint8_t *maskA = pl.maskA, *maskW = pl.maskW;
+            int32_t *idxA = pl.idxA, *cntA = pl.cntA, *idxW = pl.idxW, *cntW = pl.cntW;
+            unsigned char *words = take(256);   // small results of this draw
+            int32_t *list_a = reinterpret_cast<int32_t *>(take(4 * R));
+            if (last) {
+                u = reinterpret_cast<float *>(ws + w.uniforms);
+            } else {
+                unsigned char *const first = at;
+                u = reinterpret_cast<float *>(take(4 * R));
+                score = reinterpret_cast<float *>(take(4 * R));
+                q = reinterpret_cast<float *>(take(4 * R));
+                scale = reinterpret_cast<float *>(take(4 * R));
+                idxW = reinterpret_cast<int32_t *>(take(4 * R));
+                maskW = take(R);
+                gnorm = reinterpret_cast<float *>(take(4 * s.N));
+                p = reinterpret_cast<float *>(take(4 * s.N));
+                idxA = reinterpret_cast<int32_t *>(take(4 * s.N));
+                maskA = take(s.N);
+                cntA = reinterpret_cast<int32_t *>(words + 16);
+                cntW = reinterpret_cast<int32_t *>(words + 20);
+                at = first + probe_draw_bytes(s.N, R);
+            }
+            ProbeDraw &d = draws.draw[k];
+            d.index = base.draw + (uint32_t)(j0 + k);
+            d.p = p;
+            d.maskA = maskA;
+            d.idxA = idxA;
+            d.cntA = cntA;
+            d.u = u;
+            d.score = score;
+            d.q = q;
+            d.list_a = list_a;
+            d.rows_a = reinterpret_cast<int32_t *>(words + 24);
+            d.eq3 = reinterpret_cast<double *>(words);
+            InlineSampleA &a = group_a.prob[k];
+            a.gsq = pl.gsq;
+            a.budget = (double)s.N * rho;
+            a.seed = base.seed;
+            a.layer = base.layer;
+            a.draw = d.index;
+            a.draw_offset = base.draw_offset;
+            a.gnorm = gnorm;
+            a.p = p;
+            a.maskA = maskA;
+            a.idxA = idxA;
+            a.cntA = cntA;
+            SampleWProblem &sw = group_w.prob[k];
+            sw.gsq = pl.gsq;
+            sw.xsq = pl.xsq;
+            sw.p = p;
+            sw.maskA = maskA;
+            sw.u = u;
+            sw.budget = (double)R * rho * nu;
+            sw.score = score;
+            sw.q = q;
+            sw.maskW = maskW;
+            sw.scaleW = scale;
+            sw.idxW = idxW;
+            sw.cntW = cntW;
+            sw.rule = reinterpret_cast<double *>(words + 32);
+            for (int both = 0; both < 2; ++both) {
+                GatherTask &t = tasks[both ? n + k : k];
+                t.G = G;
+                t.X = X;
+                t.row_scale = both ? scale : scale_a;
+                t.idx = both ? idxW : list_a;
+                t.cnt = both ? cntW : d.rows_a;
+                t.exact = exact;
+                t.R = (int32_t)R;
+                t.K_in = s.K_in;
+                t.K_out = s.K_out;
+                t.scale_g = s.K_out < s.K_in;
+                t.splits = 1;
+            }
+        }
+        const int last = j0 + n == M ? n - 1 : -1;
+        if (s.N <= 1024) {
+            VCAS_TRY(sampler_a_group(group_a, n, s.N, s.T, st));
+        } else {
+            for (int k = 0; k < n; ++k) {
+                const InlineSampleA &a = group_a.prob[k];
+                vcas_rng rng = base;
+                rng.draw = a.draw;
+                VCAS_TRY(sampler_a(a.gsq, s.N, s.T, a.budget, rng, a.gnorm, a.p, a.maskA, a.idxA, a.cntA, st));
+            }
+        }
+        VCAS_TRY(probe_draws(draws, n, pl.gsq, pl.xsq, scale_a, R, s.T, base, st));
+        VCAS_TRY(sampler_w_group(group_w, n, 0, s.N, s.T, 1, 2, st));
+        VCAS_TRY(probe_eq3(draws, n, R, s.T, pl.xsq, last, st));
+        const double weight = 1.0 / (double)M;
+        bool large = true;
+        if (fits) {
+            // the larger tile moves half the bytes per product; the smaller one where that would leave CUs
+            // empty (768x768, rho 0.3, nu 0.5: 8 draws 226 and 312 us, 2 draws 146 and 142 us a probe)
+            large = 2 * n * gather_tiles(s.dtype, s.K_out, s.K_in, true) >= 192;
+            const int tiles = gather_tiles(s.dtype, s.K_out, s.K_in, large);
+            for (int i = 0; i < 2 * n; ++i) tasks[i].sq_out = tile_sums + (int64_t)i * tiles;
+            VCAS_TRY(wgrad_gather(tasks, 2 * n, s.dtype, large, true, st));
+        } else {
+            // a product too large for the gathering kernel: one draw after the other, stored and compared
+            float *draw = reinterpret_cast<float *>(ws + w.probe_draw);
+            for (int i = 0; i < 2 * n; ++i) {
+                VCAS_TRY(dispatch_wgrad(s, G, X, tasks[i].row_scale, tasks[i].idx, tasks[i].cnt, draw, ws, st));
+                VCAS_TRY(sq_diff_add(draw, exact, elems, weight, reinterpret_cast<double *>(ws + w.probe_acc), out + 2 + i / n, st));
+            }
+        }
+        VCAS_TRY(probe_finish(draws, n, fits ? tile_sums : nullptr, gather_tiles(s.dtype, s.K_out, s.K_in, large), weight,
+                              draws.draw[0].p, group_a.prob[0].gnorm, s.N, j0 == 0, out, st));
+    }
+    return VCAS_OK;
 }
 
 }  // namespace vcas
@@ -1004,38 +1104,7 @@ vcas_status vcas_variance_probe(const vcas_shape *shape, const void *G, const vo
     if (!workspace) return VCAS_EWORKSPACE;
     if (!ratio_ok(rho) || !ratio_ok(nu) || M <= 0) return VCAS_EINVAL;
     if (!aligned16(G) || !aligned16(X) || !aligned16(workspace)) return VCAS_EINVAL;
-    const vcas_shape &s = *shape;
-    hipStream_t st = as_stream(stream);
-    const WorkspaceLayout w = workspace_layout(&s);
-    unsigned char *ws = static_cast<unsigned char *>(workspace);
-    float *exact = reinterpret_cast<float *>(ws + w.probe_exact);
-    float *draw = reinterpret_cast<float *>(ws + w.probe_draw);
-    double *partial = reinterpret_cast<double *>(ws + w.probe_acc);  // 32 doubles
-    const int64_t R = (int64_t)s.N * s.T, nW = (int64_t)s.K_out * s.K_in;
-    const int blocks = 32;
-    const double wgt = 1.0 / (double)M;
-
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(out), (size_t)8);
-    if (hipGetLastError() != hipSuccess) return VCAS_EHIP;
-    vcas_rng rng = *base;
-    VCAS_TRY(linear_backward_impl(s, G, X, nullptr, 1.0, 1.0, rng, 1, *plan, nullptr, exact, workspace, st, nullptr));
-    for (int j = 0; j < M; ++j) {
-        rng.draw = base->draw + (uint32_t)j;
-        // SampleA only
-        VCAS_TRY(linear_backward_impl(s, G, X, nullptr, rho, nu, rng, 0, *plan, nullptr, draw, workspace, st, nullptr));
-        hipLaunchKernelGGL(sq_diff_partial_kernel, dim3(blocks), dim3(256), 0, st, draw, exact, nW, partial);
-        hipLaunchKernelGGL(sq_diff_final_kernel, dim3(1), dim3(64), 0, st, partial, blocks, wgt, out + 2);
-        // SampleA and SampleW
-        VCAS_TRY(linear_backward_impl(s, G, X, nullptr, rho, nu, rng, 1, *plan, nullptr, draw, workspace, st, nullptr));
-        hipLaunchKernelGGL(sq_diff_partial_kernel, dim3(blocks), dim3(256), 0, st, draw, exact, nW, partial);
-        hipLaunchKernelGGL(sq_diff_final_kernel, dim3(1), dim3(64), 0, st, partial, blocks, wgt, out + 3);
-        if (j == 0)
-            hipLaunchKernelGGL(var_closed_kernel, dim3(1), dim3(256), 0, st, plan->p, plan->gnorm, (int64_t)s.N, 1,
-                               1.0, 0, out + 0);
-        hipLaunchKernelGGL(var_closed_kernel, dim3(1), dim3(256), 0, st, plan->q, plan->score, R, 1, wgt, 1, out + 1);
-        if (hipGetLastError() != hipSuccess) return VCAS_EHIP;
-    }
-    return VCAS_OK;
+    return variance_probe(*shape, G, X, rho, nu, *base, M, *plan, out, static_cast<unsigned char *>(workspace), as_stream(stream));
 }
 
 vcas_status vcas_profile_begin(void)

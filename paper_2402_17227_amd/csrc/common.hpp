@@ -54,10 +54,13 @@ inline int elem_bytes(int dtype) { return dtype == VCAS_BF16 ? 2 : 4; }
 // kernel), zero between calls; then splits * K_out * K_in fp32: split-K partial tiles of
 // the weight gradient, then two K_out*K_in fp32 matrices and 32 doubles for the
 // variance probe, two more for the keep rule of SampleW, then R floats: the SampleW uniforms of vcas_linear_backward, then (bf16) up to
-// R rows of min(K_in, K_out) elements: the packed operand of the weight gradient
+// R rows of min(K_in, K_out) elements: the packed operand of the weight gradient, over which the variance
+// probe lays its own vectors
+
+size_t probe_scratch_bytes(int64_t N, int64_t R);   // host: probe.hip
 
 struct WorkspaceLayout {
-    size_t control, partials, probe_exact, probe_draw, probe_acc, rule, uniforms, packed, total;
+    size_t control, partials, probe_exact, probe_draw, probe_acc, rule, uniforms, packed, packed_bytes, total;
 };
 
 constexpr size_t kPlanTicketBytes = 8192;   // 33 counters, one 128-byte line each, rounded up
@@ -77,7 +80,10 @@ inline WorkspaceLayout workspace_layout(const vcas_shape *s)
     w.packed = w.uniforms + (((size_t)s->N * s->T * sizeof(float) + 255) & ~(size_t)255);
     // bf16: the narrower of G and X over the kept tokens, gathered and multiplied by the token scales
     const size_t packed_bytes = s->dtype == VCAS_BF16 ? (size_t)s->N * s->T * (s->K_in < s->K_out ? s->K_in : s->K_out) * 2 : 0;
-    w.total = w.packed + ((packed_bytes + 255) & ~(size_t)255);
+    w.packed_bytes = (packed_bytes + 255) & ~(size_t)255;
+    // the variance probe's vectors lie over the packed operand, which it is done with when it needs them
+    const size_t probe = probe_scratch_bytes(s->N, (int64_t)s->N * s->T);
+    w.total = w.packed + (w.packed_bytes > probe ? w.packed_bytes : probe);
     return w;
 }
 

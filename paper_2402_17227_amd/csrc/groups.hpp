@@ -10,6 +10,7 @@
 namespace vcas {
 
 constexpr int kMaxSiblings = 4;
+constexpr int kMaxSamplers = 8;   // samplers in one launch: siblings, or mask draws of the variance probe
 
 // One layer of a grouped dgrad launch (layers of one shape that do not depend on each other):
 // the pointer arguments of the bf16 dgrad kernel.
@@ -28,7 +29,7 @@ struct DgradGroup {
 
 // SampleA of several layers in one launch: one workgroup each, the fields of InlineSampleA.
 struct SampleAGroup {
-    InlineSampleA prob[kMaxSiblings];
+    InlineSampleA prob[kMaxSamplers];
 };
 
 // One layer of a batched bf16 weight-gradient launch (host view): the arguments of
@@ -60,7 +61,7 @@ struct SampleWProblem {
     double *rule;   // [2], scratch of the workspace: the keep rule of a long vector
 };
 struct SampleWGroup {
-    SampleWProblem prob[kMaxSiblings];
+    SampleWProblem prob[kMaxSamplers];
 };
 
 // The same for the row-norm launch: matrix, where its row sums go, and (null: all) the samples

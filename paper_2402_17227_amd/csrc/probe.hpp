@@ -1,0 +1,41 @@
+// Argument blocks and launchers of the variance probe (probe.hip).
+#pragma once
+
+#include "common.hpp"
+
+namespace vcas {
+
+constexpr int kProbeDraws = 8;   // mask draws that go through the launches together
+
+// One mask draw: what SampleA has decided, and where SampleW's inputs and the lists go.
+struct ProbeDraw {
+    uint32_t index;            // rng.draw of this draw
+    const float *p;
+    const uint8_t *maskA;
+    const int32_t *idxA, *cntA;
+    float *u, *score;          // [R]
+    const float *q;            // [R], SampleW's outcome
+    int32_t *list_a, *rows_a;  // [R] rows of kept samples, and how many
+    double *eq3;
+};
+struct ProbeDraws {
+    ProbeDraw draw[kProbeDraws];
+};
+
+// Scratch of one draw in bytes (a multiple of 256): its SampleA and SampleW vectors.
+inline size_t probe_pad(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+inline size_t probe_draw_bytes(int64_t N, int64_t R)
+{
+    return 5 * probe_pad(4 * R) + probe_pad(R) + 3 * probe_pad(4 * N) + probe_pad(N) + 256;
+}
+vcas_status probe_begin(float *ones, int32_t *iota, int32_t *cnt, double *out, int64_t R, hipStream_t st);
+vcas_status probe_draws(const ProbeDraws &d, int n, const float *gsq, const float *xsq, float *scale_a, int64_t R, int T,
+                        const vcas_rng &rng, hipStream_t st);
+// last: which of the n draws is the probe's last one (-1: none)
+vcas_status probe_eq3(const ProbeDraws &d, int n, int64_t R, int T, float *xsq, int last, hipStream_t st);
+vcas_status probe_finish(const ProbeDraws &d, int n, const double *sq, int tiles, double weight, const float *p,
+                         const float *gnorm, int N, bool first, double *out, hipStream_t st);
+// out += weight * ||a - b||^2; partial: 32 doubles
+vcas_status sq_diff_add(const float *a, const float *b, int64_t n, double weight, double *partial, double *out, hipStream_t st);
+
+}  // namespace vcas

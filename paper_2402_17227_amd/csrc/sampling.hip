@@ -195,7 +195,7 @@ __global__ __launch_bounds__(1024) void sampler_a_fast_kernel(const float *__res
     sampler_a_fast_body(gsq, N, T, budget, seed, layer, draw, gnorm, p, maskA, idxA, cntA, nullptr);
 }
 
-// SampleA of up to kMaxSiblings layers with the same N and T, one workgroup per layer.
+// SampleA of up to kMaxSamplers layers with the same N and T, one workgroup per layer.
 __global__ __launch_bounds__(1024) void sampler_a_group_kernel(SampleAGroup grp, int N, int T)
 {
     const InlineSampleA &q = grp.prob[blockIdx.x];
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(1024) void sampler_a_group_kernel(SampleAGroup grp,
     sampler_a_fast_body(q.gsq, N, T, q.budget, q.seed, q.layer, draw, q.gnorm, q.p, q.maskA, q.idxA, q.cntA, nullptr);
 }
 
-// SampleW of up to kMaxSiblings layers of one shape, one workgroup per layer.
+// SampleW of up to kMaxSamplers layers of one shape, one workgroup per layer.
 template <int E>
 __global__ __launch_bounds__(1024) void sampler_w_group_kernel(SampleWGroup grp, int zero_dropped_xsq, int N, int T,
                                                                int token_sampling, int prepared)
@@ -419,10 +419,10 @@ vcas_status sampler_a(const float *gsq, int N, int T, double budget, const vcas_
     return launch_status();
 }
 
-// sampler_a for n <= kMaxSiblings layers of N <= 1024 samples in one launch
+// sampler_a for n <= kMaxSamplers layers of N <= 1024 samples in one launch
 vcas_status sampler_a_group(const SampleAGroup &grp, int n, int N, int T, hipStream_t st)
 {
-    if (n < 1 || n > kMaxSiblings || N > 1024) return VCAS_EINVAL;
+    if (n < 1 || n > kMaxSamplers || N > 1024) return VCAS_EINVAL;
     hipLaunchKernelGGL(sampler_a_group_kernel, dim3(n), dim3(1024), 0, st, grp, N, T);
     return launch_status();
 }
@@ -434,14 +434,14 @@ vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *
     return launch_status();
 }
 
-// SampleW of n <= kMaxSiblings layers with one N and T in one set of launches.  Up to 16384 rows one
+// SampleW of n <= kMaxSamplers layers with one N and T in one set of launches.  Up to 16384 rows one
 // workgroup per layer does everything; beyond, see sampler_w_rule_kernel and what
 // follows it.
 vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq, int N, int T, int token_sampling,
                             int prepared, hipStream_t st)
 {
     const int64_t R64 = (int64_t)N * T;
-    if (n < 1 || n > kMaxSiblings || R64 > (int64_t)1 << 30) return VCAS_EINVAL;
+    if (n < 1 || n > kMaxSamplers || R64 > (int64_t)1 << 30) return VCAS_EINVAL;
     const int R = (int)R64;
 #define VCAS_SAMPLER_W(E) \
     if (R <= 1024 * (E)) { \

@@ -21,7 +21,7 @@ int gather_tiles(int dtype, int K_out, int K_in, bool large)
     return ((K_out + edge - 1) / edge) * ((K_in + edge - 1) / edge);
 }
 
-int gather_step(int, bool large) { return large ? 32 : 64; }
+int gather_step(int dtype, bool large) { return dtype == VCAS_F32 && large ? 32 : 64; }
 
 template <bool BF16, int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF>
 static vcas_status launch_gather(const GatherBatch &batch, int grid, hipStream_t st)
@@ -54,7 +54,12 @@ vcas_status wgrad_gather(GatherTask *tasks, int n, int dtype, bool large, bool d
         batch.task[i] = q;
     }
     if (grid > (int64_t)1 << 30) return VCAS_EINVAL;
-    if (dtype == VCAS_BF16) return VCAS_EINVAL;
+    if (dtype == VCAS_BF16) {
+        if (large) return diff ? launch_gather<true, 256, 256, 64, 2, 4, 1, true>(batch, (int)grid, st)
+                               : launch_gather<true, 256, 256, 64, 2, 4, 1, false>(batch, (int)grid, st);
+        return diff ? launch_gather<true, 128, 128, 64, 2, 2, 2, true>(batch, (int)grid, st)
+                    : launch_gather<true, 128, 128, 64, 2, 2, 2, false>(batch, (int)grid, st);
+    }
     if (large) return diff ? launch_gather<false, 256, 256, 32, 2, 2, 1, true>(batch, (int)grid, st)
                            : launch_gather<false, 256, 256, 32, 2, 2, 1, false>(batch, (int)grid, st);
     return diff ? launch_gather<false, 128, 128, 64, 1, 1, 4, true>(batch, (int)grid, st)

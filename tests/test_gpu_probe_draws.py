@@ -1,0 +1,36 @@
+"""The variance probe over one draw, a chunk of eight, and more than one chunk, with both output tiles of the comparing
+kernel, more samples than a workgroup has threads and rows beyond the one-workgroup samplers, against the oracle; and the
+plan it leaves: that of the last draw."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from workloads import BF16, F32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", [
+    (F32, 8, 24, 72, 64, 1), (BF16, 8, 24, 72, 64, 8), (F32, 5, 37, 264, 136, 9), (BF16, 5, 37, 264, 136, 17),
+    (BF16, 3, 40, 776, 1032, 2), (F32, 3, 40, 776, 392, 2), (BF16, 1100, 2, 16, 24, 3), (F32, 7, 2400, 8, 8, 9),
+], ids=lambda c: "x".join(map(str, c)))
+def test_probe_over_chunks_of_draws(case):
+    from paper_2402_17227_amd import binding as vb
+    from tests.gpu_util import compare_plan, plan_to_numpy, to_device
+    dtype, N, T, K_in, K_out, M = case
+    sp = workloads.LayerSpec("probe", dtype, N, T, K_in, K_out, 0.5, 0.5, layer=4, seed=5, gen_seed=M, token_sigma=0.5)
+    G, X, _ = workloads.make_layer(sp)
+    shape = vb.shape_of(N, T, K_in, K_out, dtype)
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    out = torch.full((4,), float("nan"), dtype=torch.float64, device="cuda")
+    vb.vcas_variance_probe(shape, to_device(G, dtype), to_device(X, dtype), 0.5, 0.5, vb.Rng(5, 4, 10), M, plan, out, ws)
+    torch.cuda.synchronize()
+    want = oracle.variance_probe(G, X, dtype, N, T, 0.5, 0.5, 5, 4, 10, M)
+    got = out.cpu().numpy()
+    # closed forms: the same fp32 inputs, fp64 sums; squared differences of dW: the rounding of dW (fp32 sums; in bf16 also
+    # of its scaled operand, 2^-9) against differences that are sampling noise, of the size of dW itself
+    np.testing.assert_allclose(got[:2], want[:2], rtol=1e-9)
+    np.testing.assert_allclose(got[2:], want[2:], rtol=1e-4 if dtype == F32 else 3e-2)
+    compare_plan(plan_to_numpy(plan), oracle.sampling_plan(G, X, dtype, N, T, 0.5, 0.5, 5, 4, 10 + M - 1))
