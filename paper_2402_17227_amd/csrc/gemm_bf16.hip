@@ -27,6 +27,20 @@ namespace vcas {
 // barrier per step: before it every wavefront waits until its own loads of the
 // step have landed (s_waitcnt vmcnt, the counter is in order), after it the
 // stage computed in the previous step is free.
+constexpr int kWholeStep = -100;   // SPQ: see below
+
+// f(0), f(1), ... f(N-1) with the index as a constant
+template <typename F, int... I>
+__device__ __forceinline__ void for_constants_of(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_constants(F &&f)
+{
+    for_constants_of(f, std::make_integer_sequence<int, N>());
+}
+
 constexpr int kIdxStaged = 1024;   // kept-sample indices a workgroup stages in LDS ahead of the count
 
 // grid: 1-D, tiles_n * (ceil(R/BM) + 1) + 8 workgroups.  The first ceil8(compute
@@ -38,6 +52,7 @@ constexpr int kIdxStaged = 1024;   // kept-sample indices a workgroup stages in 
 // step after next go out one per -SPQ MFMAs from there, and the next step's first fragments are
 // read under the last slice's MFMAs (256x256, one workgroup per CU: nothing else covers the
 // wait for LDS behind a barrier there).
+// SPQ = kWholeStep: all fragments of a step are read one step ahead.
 template <int BM, int BN, int WM, int WN, int NS, int SPQ>
 __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, const uint16_t *__restrict__ W,
                                                 const float *__restrict__ p, const int32_t *__restrict__ idxA,
@@ -201,6 +216,46 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
             }
         }
     };
+    // The same inside the unrolled part of a loop, where every load is whole and the stage is a constant: one
+    // scalar add and the load.  With one or two wavefronts per SIMD a loop is bound by what it issues; the
+    // lane reads, multiplies and selects of issue_nth for eight loads cost a 256x256 step 5 %, the steps
+    // of smaller tiles up to a third.
+    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(lds0 + wave * AI * 1024);
+    const uint32_t b_lds = __builtin_amdgcn_readfirstlane(lds0 + B_AT + wave * BI * 1024);
+    auto issue_whole = [&](auto stage_, auto d_, uint32_t kb, uint32_t wb) {
+        constexpr int d = decltype(d_)::value, AT = decltype(stage_)::value * STAGE, LO = AI < BI ? AI : BI;
+        // G and W alternate while both have loads left, then the rest of the longer one
+        constexpr bool of_g = d < 2 * LO ? d % 2 == 0 : AI > BI;
+        constexpr int j = d < 2 * LO ? d / 2 : d - LO;
+        if constexpr (of_g) lds_direct_load16_at<AT + j * 1024>(descG, a_lds, a_off[j], kb);
+        else lds_direct_load16_at<AT + j * 1024>(descW, b_lds, b_off[j], wb);
+    };
+    const uint32_t w_step = (uint32_t)BK * K_in * 2;   // bytes from a step of W to the next (of G: 2 BK)
+    const int whole = steps - (tail_pieces < 8 ? 1 : 0);   // steps that fetch all of their 16-byte pieces
+    // One k-slice's fragments out of a stage
+    const int r32 = lane & 31, h = lane >> 5;
+    const int blk = lane >> 4, sl = lane & 15;    // 16-lane block and lane within it
+    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
+    auto read_slice = [&](int stage, int ks, bf16x8(&fa)[TM], bf16x8(&fb)[TN]) {
+        const unsigned char *tileA = smem + stage * STAGE;
+        const unsigned char *tileB = tileA + B_AT;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            fa[i] = *reinterpret_cast<const bf16x8 *>(tileA + lds_off(wm0 + i * 32 + r32, ks * 2 + h));
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+            bf16x4 half[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int k = ks * 16 + (blk >> 1) * 8 + e * 4 + (sl >> 2);
+                const int col = wn0 + i * 32 + (blk & 1) * 16 + (sl & 3) * 4;
+                const unsigned char *src = tileB + k * B_PITCH + (((col >> 3) ^ wswz(k)) << 4) + (col & 7) * 2;
+                half[e] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                    (__attribute__((address_space(3))) bf16x4 *)(src));
+            }
+            fb[i] = __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
     // prologue: steps 0 .. NS-2 in flight (a step past the end fills a stage nobody reads and keeps the counts uniform)
 #pragma unroll
     for (int d = 0; d < NS - 1; ++d)
@@ -212,7 +267,6 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
         scale_of[r] = dst >= 0 ? 1.0f / p[dst / T] : 0.0f;
     }
 
-    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -221,40 +275,22 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    const int r32 = lane & 31, h = lane >> 5;
-    const int blk = lane >> 4, sl = lane & 15;    // 16-lane block and lane within it
     constexpr int KS = BK / 16, MM = TM * TN, SPAN = KS * MM * (SPQ > 0 ? SPQ : 0) / 4;
-    // One contraction step on stage `stage`; the loads of step `nstep` go to stage `nstage`.
-    // Fragments of two k-slices are read ahead; load d goes out after MFMA number d*SPAN/LOADS.
-    auto step_body = [&](int stage, int nstage, int nstep) {
-        const unsigned char *tileA = smem + stage * STAGE;
-        const unsigned char *tileB = tileA + B_AT;
+    // One contraction step on stage `stage`; the loads of step `nstep` go to stage `nstage` (fast: whole
+    // ones, at kb and wb).  Fragments of two k-slices are read ahead; load d goes out after MFMA number
+    // d*SPAN/LOADS.
+    auto step_body = [&](int stage, auto nstage_, int nstep, auto fast_, uint32_t kb, uint32_t wb) {
         bf16x8 a[2][TM], b[2][TN];
-        auto read_frags = [&](int ks, bf16x8(&fa)[TM], bf16x8(&fb)[TN]) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[i] = *reinterpret_cast<const bf16x8 *>(tileA + lds_off(wm0 + i * 32 + r32, ks * 2 + h));
-#pragma unroll
-            for (int i = 0; i < TN; ++i) {
-                bf16x4 half[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int k = ks * 16 + (blk >> 1) * 8 + e * 4 + (sl >> 2);
-                    const int col = wn0 + i * 32 + (blk & 1) * 16 + (sl & 3) * 4;
-                    const unsigned char *src = tileB + k * B_PITCH + (((col >> 3) ^ wswz(k)) << 4) + (col & 7) * 2;
-                    half[e] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                        (__attribute__((address_space(3))) bf16x4 *)(src));
-                }
-                fb[i] = __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7);
-            }
+        auto issue = [&](auto d_) {
+            if (decltype(fast_)::value) issue_whole(nstage_, d_, kb, wb);
+            else issue_nth(decltype(d_)::value, decltype(nstage_)::value, nstep);
         };
         if (SPQ == 0) {
-#pragma unroll
-            for (int d = 0; d < LOADS; ++d) issue_nth(d, nstage, nstep);
+            for_constants<LOADS>([&](auto d_) { issue(d_); });
             __builtin_amdgcn_sched_barrier(0);
         }
-        read_frags(0, a[0], b[0]);
-        if (KS > 1) read_frags(1, a[1], b[1]);
+        read_slice(stage, 0, a[0], b[0]);
+        if (KS > 1) read_slice(stage, 1, a[1], b[1]);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -264,59 +300,88 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks & 1][i], b[ks & 1][j], acc[i][j], 0, 0, 0);
                     if (SPQ > 0) {
                         const int m = ks * MM + i * TN + j;
-#pragma unroll
-                        for (int d = 0; d < LOADS; ++d)
-                            if (d * SPAN / LOADS == m) {
+                        for_constants<LOADS>([&](auto d_) {
+                            if (decltype(d_)::value * SPAN / LOADS == m) {
                                 __builtin_amdgcn_sched_barrier(0);
-                                issue_nth(d, nstage, nstep);
+                                issue(d_);
                                 __builtin_amdgcn_sched_barrier(0);
                             }
+                        });
                     }
                 }
-            if (ks + 2 < KS) read_frags(ks + 2, a[ks & 1], b[ks & 1]);
+            if (ks + 2 < KS) read_slice(stage, ks + 2, a[ks & 1], b[ks & 1]);
         }
     };
 
-    if constexpr (SPQ < 0) {
-        // Two stages, the barrier ahead of the step's LAST k-slice.  By then every wavefront holds that
-        // slice's fragments in registers, so the stage is free: the loads of step s+2 start there (one
-        // per -SPQ MFMAs, running on into the next step's slices), and the first fragments of step s+1
-        // are read under the last slice's MFMAs, so that no wavefront sits behind the barrier waiting for LDS.
-        constexpr int EVERY = -SPQ;
-        static_assert(NS == 2 && KS >= 2 && KS % 2 == 0, "two fragment sets alternate over an even number of slices");
-        static_assert(LOADS * EVERY <= KS * MM, "a step's loads are all issued before its barrier");
-        constexpr int AT_ONCE = MM / EVERY < LOADS ? MM / EVERY : LOADS;   // loads that go out during a last slice
-        bf16x8 a[2][TM], b[2][TN];
-        auto read_frags = [&](int stage, int ks, bf16x8(&fa)[TM], bf16x8(&fb)[TN]) {
-            const unsigned char *tileA = smem + stage * STAGE;
-            const unsigned char *tileB = tileA + B_AT;
+    if constexpr (SPQ == kWholeStep) {
+        // Every fragment of a step is in registers before its first MFMA: the fragments of step s + 1 are read
+        // while step s is on the matrix cores, and its stage is free for the loads of step s + NS as soon as
+        // the barrier says that everybody holds it.
+        static_assert(NS % 2 == 0, "fragment sets and stages repeat together");
+        bf16x8 a[2][KS][TM], b[2][KS][TN];
+        wait_loads_outstanding<(NS - 2) * LOADS>();
+        __syncthreads();   // step 0 has landed (and nobody needs the staged kept list any more)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[i] = *reinterpret_cast<const bf16x8 *>(tileA + lds_off(wm0 + i * 32 + r32, ks * 2 + h));
+        for (int q = 0; q < LOADS; ++q) issue_nth(q, NS - 1, NS - 1 < steps ? NS - 1 : steps + 64);
 #pragma unroll
-            for (int i = 0; i < TN; ++i) {
-                bf16x4 half[2];
+        for (int ks = 0; ks < KS; ++ks) read_slice(0, ks, a[0][ks], b[0][ks]);
+        uint32_t kb = NS * BK * 2, wb = NS * w_step;   // where step s + NS starts in G and W
+        auto step = [&](int s, auto t_, auto fast_) {
+            constexpr int t = decltype(t_)::value, P = t & 1;   // t = s mod NS
+            constexpr bool fast = decltype(fast_)::value;
+            wait_loads_outstanding<(NS - 2) * LOADS>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            const int after = s + NS < steps ? s + NS : steps + 64;
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int k = ks * 16 + (blk >> 1) * 8 + e * 4 + (sl >> 2);
-                    const int col = wn0 + i * 32 + (blk & 1) * 16 + (sl & 3) * 4;
-                    const unsigned char *src = tileB + k * B_PITCH + (((col >> 3) ^ wswz(k)) << 4) + (col & 7) * 2;
-                    half[e] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                        (__attribute__((address_space(3))) bf16x4 *)(src));
-                }
-                fb[i] = __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7);
+            for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][ks][i], b[P][ks][j], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                read_slice((t + 1) % NS, ks, a[P ^ 1][ks], b[P ^ 1][ks]);
+                for_constants<LOADS>([&](auto q_) {
+                    constexpr int q = decltype(q_)::value;
+                    if (q * KS / LOADS == ks) {
+                        if (fast) issue_whole(t_, q_, kb, wb);
+                        else issue_nth(q, t, after);
+                    }
+                });
+                __builtin_amdgcn_sched_barrier(0);
             }
+            kb += BK * 2;
+            wb += w_step;
         };
+        int s = 0;
+        for (; s + 2 * NS <= whole; s += NS)
+            for_constants<NS>([&](auto t_) { step(s + decltype(t_)::value, t_, std::true_type{}); });
+        for (; s < steps; s += NS)
+            for_constants<NS>([&](auto t_) {
+                if (s + decltype(t_)::value < steps) step(s + decltype(t_)::value, t_, std::false_type{});
+            });
+    } else if constexpr (SPQ < 0) {
+        // Two stages, the barrier ahead of the step's LAST k-slice.  By then every wavefront holds that
+        // slice's fragments in registers, so the stage is free: the loads of step s+2 go out there, one
+        // per MFMA, and the first fragments of step s+1 are read under the last slice's MFMAs, so that no wavefront sits behind the barrier waiting for LDS.
+        static_assert(NS == 2 && KS >= 2 && KS % 2 == 0, "two fragment sets alternate over an even number of slices");
+        static_assert(MM >= LOADS, "all of a step's loads go out during one slice");
+        bf16x8 a[2][TM], b[2][TN];
         wait_loads_outstanding<0>();
         __syncthreads();                           // step 0 has landed
 #pragma unroll
-        for (int d = 0; d < AT_ONCE; ++d) issue_nth(d, 1, 1 < steps ? 1 : steps + 64);
-        read_frags(0, 0, a[0], b[0]);
-        for (int s = 0; s < steps; ++s) {
-            const int cur = s & 1;
-            const int after = s + 1 < steps ? s + 1 : steps + 64, after2 = s + 2 < steps ? s + 2 : steps + 64;
+        for (int d = 0; d < LOADS; ++d) issue_nth(d, 1, 1 < steps ? 1 : steps + 64);
+        read_slice(0, 0, a[0], b[0]);
+        uint32_t kb = 2 * BK * 2, wb = 2 * w_step;   // where step s + 2 starts in G and W
+        auto step = [&](int s, auto t_, auto fast_) {
+            constexpr int cur = decltype(t_)::value;   // s mod 2
+            constexpr bool fast = decltype(fast_)::value;
+            const int after2 = s + 2 < steps ? s + 2 : steps + 64;
             __builtin_amdgcn_sched_barrier(0);
-            read_frags(cur, 1, a[1], b[1]);
+            read_slice(cur, 1, a[1], b[1]);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 if (ks == KS - 1) {
@@ -326,27 +391,43 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_sched_barrier(0);
-                    read_frags(cur ^ 1, 0, a[0], b[0]);
+                    read_slice(cur ^ 1, 0, a[0], b[0]);
                 }
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks & 1][i], b[ks & 1][j], acc[i][j], 0, 0, 0);
-                        // MFMAs counted from the start of a last slice: that slice, then the slices of the next step
-                        const int m = (ks == KS - 1 ? 0 : (ks + 1) * MM) + i * TN + j;
-                        if (m % EVERY == 0 && m / EVERY < LOADS) {
+                        const int q = i * TN + j;   // one load per MFMA of the last slice
+                        if (ks == KS - 1 && q < LOADS) {
                             __builtin_amdgcn_sched_barrier(0);
-                            if (ks == KS - 1) issue_nth(m / EVERY, cur, after2);
-                            else issue_nth(m / EVERY, cur ^ 1, after);
+                            if (fast)
+                                for_constants<LOADS>([&](auto q_) {
+                                    if (decltype(q_)::value == q) issue_whole(t_, q_, kb, wb);
+                                });
+                            else
+                                issue_nth(q, cur, after2);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
-                if (ks + 2 < KS) read_frags(cur, ks + 2, a[ks & 1], b[ks & 1]);
+                if (ks + 2 < KS) read_slice(cur, ks + 2, a[ks & 1], b[ks & 1]);
             }
+            kb += BK * 2;
+            wb += w_step;
+        };
+        int s = 0;
+        for (; s + 4 <= whole; s += 2) {
+            step(s, std::integral_constant<int, 0>(), std::true_type{});
+            step(s + 1, std::integral_constant<int, 1>(), std::true_type{});
+        }
+        for (; s < steps; s += 2) {
+            step(s, std::integral_constant<int, 0>(), std::false_type{});
+            if (s + 1 < steps) step(s + 1, std::integral_constant<int, 1>(), std::false_type{});
         }
     } else {
-        for (int s = 0; s < steps; ++s) {
+        uint32_t kb = (NS - 1) * BK * 2, wb = (NS - 1) * w_step;   // where step s + NS - 1 starts in G and W
+        auto step = [&](int s, auto t_, auto fast_) {
+            constexpr int t = decltype(t_)::value;   // s mod NS
             // the NS-2 younger steps may stay in flight; step s must have landed
             wait_loads_outstanding<(NS - 2) * LOADS>();
             asm volatile("" ::: "memory");
@@ -354,9 +435,18 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
             asm volatile("" ::: "memory");
             const int nxt = s + NS - 1;
             __builtin_amdgcn_sched_barrier(0);
-            step_body(s % NS, nxt % NS, nxt < steps ? nxt : steps + 64);
+            step_body(t, std::integral_constant<int, (t + NS - 1) % NS>(), nxt < steps ? nxt : steps + 64, fast_, kb, wb);
             __builtin_amdgcn_sched_barrier(0);
-        }
+            kb += BK * 2;
+            wb += w_step;
+        };
+        int s = 0;
+        for (; s + 2 * NS - 1 <= whole; s += NS)
+            for_constants<NS>([&](auto t_) { step(s + decltype(t_)::value, t_, std::true_type{}); });
+        for (; s < steps; s += NS)
+            for_constants<NS>([&](auto t_) {
+                if (s + decltype(t_)::value < steps) step(s + decltype(t_)::value, t_, std::false_type{});
+            });
     }
     wait_loads_outstanding<0>();
 
@@ -549,6 +639,29 @@ static vcas_status launch_dgrad_group(const vcas_shape &s, const DgradGroup &grp
     return launch_status();
 }
 
+enum DgradTile { kTile256, kTile128, kTile64, kTile128Whole, kTile64Whole };
+
+// Which kernel for n layers of `rows` kept rows each.  The larger tile moves fewer operand bytes per
+// flop (loads into LDS and fragment reads out of it, not MFMAs, bound the smaller ones), so the largest
+// that still fills the chip wins:
+//  - 256x256 (one workgroup of eight wavefronts per CU) from 128 tiles up, half the CUs: inside a stack
+//    other kernels take the rest (192 made a step 1-3 % longer).  Where the kept count is known on the
+//    device only, the tiles of ALL rows are counted and half of them may be empty: 192.
+//  - one tile per CU and nothing else to hide its latencies: the kernels that read whole steps ahead
+//    (kWholeStep), 64x128 up to 200 tiles, 128x128 up to 224.  768->3072 transposed, i.e. K_out 3072 and
+//    K_in 768: 2048 rows, 192 or 96 tiles, 18 and 21 us (64x128 without reading ahead 23); 4096 rows,
+//    384 or 192 tiles, 35 and 24 us (30 with two 64x128 workgroups per CU).
+//  - two workgroups per CU: 64x128 up to 256 tiles of 128x128, 128x128 beyond (1024->1024: 4096 rows,
+//    512 or 256 tiles, 18 us both, 22 reading ahead; 8192 rows, 30 and 24 us).
+static DgradTile dgrad_tile(int64_t rows, int K_in, int n, bool rows_known)
+{
+    auto tiles = [&](int bm, int bn) { return n * ((rows + bm - 1) / bm) * ((K_in + bn - 1) / bn); };
+    if (tiles(256, 256) >= (rows_known ? 128 : 192)) return kTile256;
+    if (tiles(64, 128) <= 200) return kTile64Whole;
+    if (tiles(128, 128) <= 224) return kTile128Whole;
+    return tiles(128, 128) > 256 ? kTile128 : kTile64;
+}
+
 // dgrad of n <= kMaxSiblings layers of shape s in one launch (see dgrad_bf16_group_kernel); the
 // tile choice looks at the tiles of all of them together.
 vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int n, bool fill, int64_t expected_rows,
@@ -562,13 +675,13 @@ vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int
     }
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    const int64_t tiles256 = n * ((rows + 255) / 256) * ((s.K_in + 255) / 256);
-    const int64_t tiles128 = n * ((rows + 127) / 128) * ((s.K_in + 127) / 128);
-    if (tiles256 >= 128) return launch_dgrad_group<256, 256, 2, 4, 2, 1, -1>(s, grp, n, fill, st);
-    if (tiles128 > 256) return launch_dgrad_group<128, 128, 2, 2, 2, 2, 4>(s, grp, n, fill, st);
-    const int64_t tiles64 = n * ((rows + 63) / 64) * ((s.K_in + 127) / 128);
-    if (tiles64 > 256) return launch_dgrad_group<64, 128, 2, 2, 2, 2, 0>(s, grp, n, fill, st);
-    return launch_dgrad_group<64, 128, 2, 2, 4, 1, 0>(s, grp, n, fill, st);
+    switch (dgrad_tile(rows, s.K_in, n, true)) {
+    case kTile256: return launch_dgrad_group<256, 256, 2, 4, 2, 1, -1>(s, grp, n, fill, st);
+    case kTile64Whole: return launch_dgrad_group<64, 128, 2, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
+    case kTile128Whole: return launch_dgrad_group<128, 128, 4, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
+    case kTile128: return launch_dgrad_group<128, 128, 2, 2, 2, 2, 4>(s, grp, n, fill, st);
+    default: return launch_dgrad_group<64, 128, 2, 2, 2, 2, 0>(s, grp, n, fill, st);
+    }
 }
 
 // expected_rows: how many of the R rows the caller expects to be kept (R if unknown); it only
@@ -587,26 +700,15 @@ vcas_status dgrad_bf16(const vcas_shape &s, const void *G, const void *W, const 
         if (s.N > 64) return VCAS_EINVAL;
         sa = *sample_a;
     }
-    // The loads into LDS run at about 40 bytes per clock and CU, so the largest tile that still
-    // fills the chip wins: 256x256 (one 8-wave workgroup per CU) from 128 tiles up (half the CUs:
-    // inside a stack other kernels take the rest; 192 made a step 1-3 % longer); else 128x128
-    // (two per CU) while more than 256 of them exist; else 64x128, twice as many workgroups with
-    // half the serial work each.  Measured, R=16384, 1024->4096: 123 / 137 / 191 us; R=4096,
-    // 768->3072: 68 / 37 / 33 us.  When even the 64x128 tiles leave CUs with a single workgroup,
-    // nothing overlaps a tile's own load latency, so the pipeline goes four stages deep instead
-    // (2048 kept rows, 768->3072: 22 vs 29 us).
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    const int64_t tiles256 = ((rows + 255) / 256) * ((s.K_in + 255) / 256);
-    const int64_t tiles128 = ((rows + 127) / 128) * ((s.K_in + 127) / 128);
-    // without an expectation (the kept count is known on the device only) the tiles of ALL rows are counted, and a
-    // kernel picked for them may find half of them empty: the larger tile then needs more of them to pay
-    if (tiles256 >= (expected_rows > 0 ? 128 : 192))
-        return launch_dgrad<256, 256, 2, 4, 2, 1, -1>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
-    if (tiles128 > 256) return launch_dgrad<128, 128, 2, 2, 2, 2, 4>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
-    const int64_t tiles64 = ((rows + 63) / 64) * ((s.K_in + 127) / 128);
-    if (tiles64 > 256) return launch_dgrad<64, 128, 2, 2, 2, 2, 0>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
-    return launch_dgrad<64, 128, 2, 2, 4, 1, 0>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    switch (dgrad_tile(rows, s.K_in, 1, expected_rows > 0)) {
+    case kTile256: return launch_dgrad<256, 256, 2, 4, 2, 1, -1>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    case kTile64Whole: return launch_dgrad<64, 128, 2, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    case kTile128Whole: return launch_dgrad<128, 128, 4, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    case kTile128: return launch_dgrad<128, 128, 2, 2, 2, 2, 4>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    default: return launch_dgrad<64, 128, 2, 2, 2, 2, 0>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
+    }
 }
 
 }  // namespace vcas

@@ -61,6 +61,16 @@ __device__ __forceinline__ void lds_direct_load16(i32x4 desc, uint32_t lds_base,
                  : "memory", "m0");
 }
 
+// The same to LDS byte address lds_base + AT.
+template <int AT>
+__device__ __forceinline__ void lds_direct_load16_at(i32x4 desc, uint32_t lds_base, uint32_t voffset, uint32_t soffset)
+{
+    asm volatile("s_add_u32 m0, %0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+                 :
+                 : "s"(lds_base), "i"(AT), "v"(voffset), "s"(desc), "s"(soffset)
+                 : "memory", "m0", "scc");
+}
+
 // Row of the 32x32 accumulator block that register v of this lane holds; the column is lane % 32.
 __device__ __forceinline__ int acc_row(int v) { return (v >> 2) * 8 + ((threadIdx.x & 63) >> 5) * 4 + (v & 3); }
 
