@@ -16,12 +16,6 @@ vcas_status row_sumsq(const void *A, int dtype, int64_t R, int K, int T, const u
                       hipStream_t st);
 vcas_status sample_norms(const float *gsq, int N, int T, float *gnorm, hipStream_t st);
 vcas_status row_sumsq_group(const RowNormGroup &grp, int n, int dtype, int64_t R, int K, int T, hipStream_t st);
-vcas_status row_sumsq_scores_uniforms(const void *X, int dtype, int64_t R, int K, int T, const uint8_t *keep,
-                                      float *xsq, const float *gsq, const float *p, float *score, const vcas_rng &rng,
-                                      uint32_t stream_id, float *uniforms, hipStream_t st);
-vcas_status cached_xsq_scores_uniforms(const float *xsq_forward, int64_t R, int T, const uint8_t *keep, float *xsq,
-                                       const float *gsq, const float *p, float *score, const vcas_rng &rng,
-                                       uint32_t stream_id, float *uniforms, hipStream_t st);
 // sampling.hip
 vcas_status keep_probs(const float *score, int n, double budget, float *prob, hipStream_t st);
 vcas_status sample_compact(const float *prob, int n, const vcas_rng &rng, uint32_t stream_id, uint8_t *mask,
@@ -37,8 +31,7 @@ vcas_status sampler_a(const float *gsq, int N, int T, double budget, const vcas_
 vcas_status sampler_a_group(const SampleAGroup &grp, int n, int N, int T, hipStream_t st);
 vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq, int N, int T, int token_sampling,
                             int prepared, hipStream_t st);
-vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int K, int T,
-                                            hipStream_t st);
+vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int T, hipStream_t st);
 vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *u, hipStream_t st);
 vcas_status row_sumsq_pair(const void *G, int K_out, float *gsq, const void *X, int K_in, float *xsq, int dtype,
                            int64_t R, const vcas_rng &rng, uint32_t stream_id, float *uniforms, float *root_g,
@@ -55,9 +48,8 @@ vcas_status dgrad_bf16(const vcas_shape &s, const void *G, const void *W, const 
                        const InlineSampleA *sample_a, float *sq_blocks, hipStream_t st);
 vcas_status rows_from_blocks(const float *blocks, int64_t R, int K, int T, const uint8_t *keep, float *const *outs,
                              int n_out, hipStream_t st);
-bool sample_norms_from_blocks_fits(int N, int T);
-vcas_status sample_norms_from_blocks(const float *blocks, int N, int T, int K, const uint8_t *keep, float *const *outs,
-                                     float *const *gnorms, int n_out, hipStream_t st);
+vcas_status lane_sums_from_blocks(const float *blocks, int N, int T, int K, const uint8_t *keep, float *const *outs,
+                                  int n_out, float *lanes, hipStream_t st);
 vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int n, bool fill, int64_t expected_rows,
                              hipStream_t st);
 vcas_status wgrad_bf16_batch(const WgradItem *items, int n, int tile, hipStream_t st);
@@ -267,9 +259,28 @@ static SampleWProblem sample_w_problem(const vcas_shape &s, double rho, double n
     return w;
 }
 
+// The pass over X of one layer (or over its cached row norms), SampleA done: slot i of a grouped launch.
+static void put_row_job(RowJobGroup &grp, int i, const vcas_shape &s, const void *X, const float *xsq_forward,
+                        const vcas_rng &rng, int token_sampling, const vcas_plan &pl, void *workspace)
+{
+    float *u = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + workspace_layout(&s).uniforms);
+    grp.A[i] = static_cast<const uint4 *>(X);
+    grp.norms[i] = xsq_forward;
+    grp.keep[i] = pl.maskA;
+    grp.out[i] = pl.xsq;
+    grp.job[i] = {token_sampling ? u : nullptr, rng.seed, rng.layer, 1u, rng.draw, rng.draw_offset};
+    grp.sj[i] = {pl.gsq, pl.p, pl.score};
+    grp.groups[i] = s.K_in / (16 / elem_bytes(s.dtype));
+}
+
 static float *uniforms_of(const vcas_shape &s, void *workspace)
 {
     return reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + workspace_layout(&s).uniforms);
+}
+
+static float *lanes_of(const vcas_shape &s, void *workspace)
+{
+    return reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + workspace_layout(&s).lanes);
 }
 
 // Data half: row norms of G (and of X, with the SampleW uniforms, on small layers), SampleA, dX.
@@ -301,14 +312,14 @@ static vcas_status data_half(const vcas_shape &s, const void *G, const void *X, 
     float *uw = token_sampling ? uniforms_of(s, workspace) : nullptr;
     // together: the square roots SampleW needs travel in the plan's score and q arrays until
     // SampleW overwrites them with their final contents
-    // Inside a stack, with the block sums of G at hand: one workgroup per sample adds them to row
-    // sums and the sample's norm, and the dgrad workgroups decide SampleA themselves from the N
-    // norms, so that the chain row norms -> SampleA -> dX is two launches instead of three.
-    const bool norms_for_dgrad = sample_a_in_dgrad && chain.g_sq_blocks && dX && s.dtype == VCAS_BF16 && s.N <= 64 &&
-                                 sample_norms_from_blocks_fits(s.N, s.T);
-    if (norms_for_dgrad) {
-        float *outs[1] = {pl.gsq}, *gnorms[1] = {pl.gnorm};
-        VCAS_TRY(sample_norms_from_blocks(chain.g_sq_blocks, s.N, s.T, s.K_out, chain.kept_above, outs, gnorms, 1, st));
+    // Inside a stack, with the block sums of G at hand: one launch adds them to row sums and lane sums,
+    // and the dgrad workgroups decide SampleA themselves from the 64 N lane sums, so that the chain row
+    // norms -> SampleA -> dX is two launches instead of three.
+    const bool lanes_for_dgrad = sample_a_in_dgrad && chain.g_sq_blocks && dX && s.dtype == VCAS_BF16 && s.N <= 64;
+    if (lanes_for_dgrad) {
+        float *outs[1] = {pl.gsq};
+        VCAS_TRY(lane_sums_from_blocks(chain.g_sq_blocks, s.N, s.T, s.K_out, chain.kept_above, outs, 1,
+                                       lanes_of(s, workspace), st));
     } else if (chain.g_sq_blocks) {
         // the norms of G come from the launch that wrote G; those of X are left to the weight half
         float *outs[1] = {pl.gsq};
@@ -320,13 +331,13 @@ static vcas_status data_half(const vcas_shape &s, const void *G, const void *X, 
         VCAS_TRY(row_sumsq(G, s.dtype, R, s.K_out, s.T, chain.kept_above, pl.gsq, st));
     // SampleA keeps about N*rho samples (Sec. 4.1): the row count the dgrad tile choice plans for
     const int64_t rows_expected = (int64_t)((double)R * rho + 0.5);
-    if (norms_for_dgrad || (sample_a_in_dgrad && dX && s.dtype == VCAS_BF16 && s.N <= 64 && R <= 4096)) {
+    if (lanes_for_dgrad || (sample_a_in_dgrad && dX && s.dtype == VCAS_BF16 && s.N <= 64 && R <= 4096)) {
         // one launch and its gap less on the chain row norms -> SampleA -> dX: the dgrad workgroups
         // decide SampleA themselves.  Worth it only while the vector of row norms is short: every
         // workgroup reads all of it (BERT-base, R = 4096: step 2.78 -> 2.70 ms; ViT, N = 64,
         // R = 12608: 3.93 -> 4.44 ms)
         InlineSampleA sa = {};
-        if (norms_for_dgrad) sa.norms = pl.gnorm;
+        if (lanes_for_dgrad) sa.lanes = lanes_of(s, workspace);
         else sa.gsq = pl.gsq;
         sa.budget = (double)s.N * rho;
         sa.seed = rng.seed;
@@ -355,15 +366,13 @@ static vcas_status weight_half(const vcas_shape &s, const void *G, const void *X
                                const float *xsq_forward = nullptr)
 {
     const int64_t R = (int64_t)s.N * s.T;
-    float *u = uniforms_of(s, workspace);
     // cached norms of X: whatever the data half may have left in score and q is not used
     const bool together = !xsq_forward && together_for(s, xnorms);
-    if (xsq_forward)
-        VCAS_TRY(cached_xsq_scores_uniforms(xsq_forward, R, s.T, pl.maskA, pl.xsq, pl.gsq, pl.p, pl.score, rng, 1u,
-                                            token_sampling ? u : nullptr, st));
-    else if (!together)
-        VCAS_TRY(row_sumsq_scores_uniforms(X, s.dtype, R, s.K_in, s.T, pl.maskA, pl.xsq, pl.gsq, pl.p, pl.score, rng, 1u,
-                                           token_sampling ? u : nullptr, st));
+    if (!together) {
+        RowJobGroup norms = {};
+        put_row_job(norms, 0, s, X, xsq_forward, rng, token_sampling, pl, workspace);
+        VCAS_TRY(row_sumsq_scores_uniforms_group(norms, 1, s.dtype, R, s.T, st));
+    }
     // what the norm passes have left in score and q: roots (together) or the scores themselves
     SampleWGroup sampler = {};
     sampler.prob[0] = sample_w_problem(s, rho, nu, pl, workspace);
@@ -397,8 +406,8 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
     const vcas_shape &s = layers[0].shape;
     const int64_t R = (int64_t)s.N * s.T;
     const bool in_dgrad = s.N <= 64 && R <= 4096;
-    // with the block sums of G at hand the sample norms come with the row sums and dgrad decides from those (see data_half)
-    const bool norms_for_dgrad = layers[0].g_sq_blocks && s.N <= 64 && sample_norms_from_blocks_fits(s.N, s.T);
+    // with the block sums of G at hand lane sums come with the row sums and dgrad decides from those (see data_half)
+    const bool lanes_for_dgrad = layers[0].g_sq_blocks && s.N <= 64;
     RowNormGroup norms = {};
     SampleAGroup samplers = {};
     DgradProblem probs[kMaxSiblings];
@@ -430,8 +439,7 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
         q.dX = static_cast<uint16_t *>(a.dX);
         q.J = static_cast<const uint16_t *>(a.J);
         q.sa = sa;
-        if (!in_dgrad || norms_for_dgrad) q.sa.gsq = nullptr;
-        if (norms_for_dgrad) q.sa.norms = a.plan.gnorm;
+        if (!in_dgrad || lanes_for_dgrad) q.sa.gsq = nullptr;
         q.sq_blocks = a.dx_sq_blocks;
         if (a.rho > rho_max) rho_max = a.rho;
     }
@@ -439,57 +447,48 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
         // norms of G from the launch that wrote it: one pass over the block sums serves every
         // sibling that was handed the same G; the others take a pass of their own
         for (int i = 0; i < n;) {
-            float *outs[kMaxSiblings], *gnorms[kMaxSiblings];
+            float *outs[kMaxSiblings], *lanes = lanes_of(s, layers[i].workspace);
             int m = 0;
             for (; i + m < n && layers[i + m].g_sq_blocks == layers[i].g_sq_blocks &&
                    layers[i + m].kept_above == layers[i].kept_above; ++m) {
                 outs[m] = layers[i + m].plan.gsq;
-                gnorms[m] = layers[i + m].plan.gnorm;
+                if (lanes_for_dgrad) probs[i + m].sa.lanes = lanes;
             }
-            if (norms_for_dgrad)
-                VCAS_TRY(sample_norms_from_blocks(layers[i].g_sq_blocks, s.N, s.T, s.K_out, layers[i].kept_above, outs,
-                                                  gnorms, m, st));
+            if (lanes_for_dgrad)
+                VCAS_TRY(lane_sums_from_blocks(layers[i].g_sq_blocks, s.N, s.T, s.K_out, layers[i].kept_above, outs, m, lanes, st));
             else
                 VCAS_TRY(rows_from_blocks(layers[i].g_sq_blocks, R, s.K_out, s.T, layers[i].kept_above, outs, m, st));
             i += m;
         }
     } else
         VCAS_TRY(row_sumsq_group(norms, n, s.dtype, R, s.K_out, s.T, st));
-    if (!in_dgrad && !norms_for_dgrad) VCAS_TRY(sampler_a_group(samplers, n, s.N, s.T, st));
+    if (!in_dgrad && !lanes_for_dgrad) VCAS_TRY(sampler_a_group(samplers, n, s.N, s.T, st));
     return dgrad_bf16_group(s, probs, n, layers[0].leave_dropped_rows == 0, (int64_t)((double)R * rho_max + 0.5), st);
 }
 
-// Can layer b share the SampleW launches of layer a in front of it?  Siblings of one shape and
-// dtype with the same kind of token sampling and the rows of X still to be swept.
+// Can layer b share the launches that precede the weight gradients with layer a?  All they need is one number
+// of rows, samples and bytes per element, and the same kind of token sampling.
 static bool shares_weight_half(const vcas_layer_args &a, const vcas_layer_args &b)
 {
-    const vcas_shape &s = a.shape;
-    return b.sibling != 0 && same_shape(s, b.shape) && !a.xsq_forward &&
-           !b.xsq_forward && (a.token_sampling != 0) == (b.token_sampling != 0);
+    return a.shape.N == b.shape.N && a.shape.T == b.shape.T && a.shape.dtype == b.shape.dtype &&
+           (a.token_sampling != 0) == (b.token_sampling != 0);
 }
 
-// What weight_half does before dW, for n sibling layers (shares_weight_half) whose data halves
-// left the norms of X to it: the row norms of X on kept samples with the SampleW scores and
-// uniforms in one launch, SampleW in one launch (a workgroup per layer).  The same bits.
-static vcas_status weight_half_siblings(const vcas_layer_args *layers, int n, hipStream_t st)
+// What weight_half does before dW, for n layers (shares_weight_half) whose data halves left the norms of X
+// to it: the norms with the SampleW scores and uniforms in one launch, SampleW in one (a workgroup per
+// layer, or see sampler_w_group).  The same bits.
+static vcas_status weight_half_group(const vcas_layer_args *layers, int n, hipStream_t st)
 {
     const vcas_shape &s = layers[0].shape;
-    const int64_t R = (int64_t)s.N * s.T;
-    const int token_sampling = layers[0].token_sampling;
     RowJobGroup norms = {};
     SampleWGroup samplers = {};
     for (int i = 0; i < n; ++i) {
         const vcas_layer_args &a = layers[i];
-        float *u = uniforms_of(a.shape, a.workspace);
-        norms.A[i] = static_cast<const uint4 *>(a.X);
-        norms.keep[i] = a.plan.maskA;
-        norms.out[i] = a.plan.xsq;
-        norms.job[i] = {token_sampling ? u : nullptr, a.rng.seed, a.rng.layer, 1u, a.rng.draw, a.rng.draw_offset};
-        norms.sj[i] = {a.plan.gsq, a.plan.p, a.plan.score};
-        samplers.prob[i] = sample_w_problem(s, a.rho, a.nu, a.plan, a.workspace);
+        put_row_job(norms, i, a.shape, a.X, a.xsq_forward, a.rng, a.token_sampling, a.plan, a.workspace);
+        samplers.prob[i] = sample_w_problem(a.shape, a.rho, a.nu, a.plan, a.workspace);
     }
-    VCAS_TRY(row_sumsq_scores_uniforms_group(norms, n, s.dtype, R, s.K_in, s.T, st));
-    return sampler_w_group(samplers, n, 0, s.N, s.T, token_sampling, 2, st);
+    VCAS_TRY(row_sumsq_scores_uniforms_group(norms, n, s.dtype, (int64_t)s.N * s.T, s.T, st));
+    return sampler_w_group(samplers, n, 0, s.N, s.T, layers[0].token_sampling, 2, st);
 }
 
 // Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched
@@ -548,6 +547,31 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
         l = next;
     }
     return VCAS_OK;
+}
+
+// Fills in dx_sq_blocks and g_sq_blocks of the entries that feed each other, where the caller has not:
+// the entry that wrote G last has the same rows, leaves its block sums somewhere, and which rows of G
+// exist at all is known from its maskA (the caller says so, or the others are zeros, which count as +0).
+static void link_norms(vcas_layer_args *layers, int L)
+{
+    for (int l = 1; l < L; ++l) {
+        vcas_layer_args &a = layers[l];
+        if (a.g_sq_blocks || a.shape.dtype != VCAS_BF16) continue;
+        int p = l - 1;
+        while (p >= 0 && layers[p].dX != a.G) --p;
+        if (p < 0) continue;
+        vcas_layer_args &b = layers[p];
+        if (b.shape.dtype != VCAS_BF16 || b.shape.N != a.shape.N || b.shape.T != a.shape.T || b.shape.K_in != a.shape.K_out) continue;
+        const uint8_t *keep = a.kept_above ? a.kept_above : b.leave_dropped_rows ? nullptr : b.plan.maskA;
+        if (keep != b.plan.maskA) continue;
+        if (!b.dx_sq_blocks) {
+            const WorkspaceLayout w = workspace_layout(&b.shape);
+            if (vcas_sq_blocks_bytes((int64_t)b.shape.N * b.shape.T, b.shape.K_in) > w.probe_acc - w.probe_exact) continue;
+            b.dx_sq_blocks = reinterpret_cast<float *>(static_cast<unsigned char *>(b.workspace) + w.probe_exact);
+        }
+        a.kept_above = keep;
+        a.g_sq_blocks = b.dx_sq_blocks;
+    }
 }
 
 static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, const void *X, const void *W, double rho,
@@ -948,6 +972,16 @@ vcas_status vcas_backward_stack(const vcas_layer_args *layers, int32_t L, int32_
             (a.dW && !aligned16(a.dW)) || !aligned16(a.workspace))
             return VCAS_EINVAL;
     }
+    // Entries whose G is the dX of an entry before them take its norms from the launch that writes it: the
+    // block sums go to the producer's workspace (where only the variance probe keeps anything).  A sweep over
+    // G, 5 to 20 us each, and where R > 4096 the SampleA launch, leave the chain of the data halves for a
+    // 3 us pass over the block sums.
+    std::vector<vcas_layer_args> linked;
+    if (s2 != st) {
+        linked.assign(layers, layers + L);
+        link_norms(linked.data(), L);
+        layers = linked.data();
+    }
     // Groups of `group` layers; the last ones shrink (half of what is left), so that the side
     // streams are not a whole group behind when the main stream reaches the end of the stack.
     std::vector<int> first;
@@ -1005,15 +1039,15 @@ vcas_status vcas_backward_stack(const vcas_layer_args *layers, int32_t L, int32_
         for (int l = l0; l < l1;) {
             const vcas_layer_args &a = layers[l];
             int n = 1;
-            if (s2 != st)
-                while (l + n < l1 && n < kMaxSiblings && shares_weight_half(a, layers[l + n])) ++n;
-            if (n > 1)
-                VCAS_TRY(weight_half_siblings(layers + l, n, s2));
-            else
+            if (s2 != st) {
+                while (l + n < l1 && n < kMaxSamplers && shares_weight_half(a, layers[l + n])) ++n;
+                VCAS_TRY(weight_half_group(layers + l, n, s2));
+            } else {
                 VCAS_TRY(weight_half(a.shape, a.G, a.X, a.rho, a.nu, a.rng, a.token_sampling, a.plan, nullptr,
                                      a.workspace, s2,
                                      a.xsq_forward || a.g_sq_blocks ? kXNormsAfterSampleA : xnorms_default,
                                      a.xsq_forward));
+            }
             l += n;
         }
         if (s3 != s2 && (hipEventRecord(events[2 * g + 1], s2) != hipSuccess ||

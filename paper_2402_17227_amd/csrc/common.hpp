@@ -53,14 +53,16 @@ inline int elem_bytes(int dtype) { return dtype == VCAS_BF16 ? 2 : 4; }
 // kPlanTicketBytes of control words (the ticket counters of the fused planning
 // kernel), zero between calls; then splits * K_out * K_in fp32: split-K partial tiles of
 // the weight gradient, then two K_out*K_in fp32 matrices and 32 doubles for the
-// variance probe, two more for the keep rule of SampleW, then R floats: the SampleW uniforms of vcas_linear_backward, then (bf16) up to
+// variance probe, two more for the keep rule of SampleW, the lane sums of up
+// to 64 samples, then R floats: the SampleW uniforms of vcas_linear_backward, then (bf16) up to
 // R rows of min(K_in, K_out) elements: the packed operand of the weight gradient, over which the variance
 // probe lays its own vectors
 
+constexpr size_t kLaneSumBytes = 64 * 64 * sizeof(float);   // lane sums of the row norms of up to 64 samples
 size_t probe_scratch_bytes(int64_t N, int64_t R);   // host: probe.hip
 
 struct WorkspaceLayout {
-    size_t control, partials, probe_exact, probe_draw, probe_acc, rule, uniforms, packed, packed_bytes, total;
+    size_t control, partials, probe_exact, probe_draw, probe_acc, rule, lanes, uniforms, packed, packed_bytes, total;
 };
 
 constexpr size_t kPlanTicketBytes = 8192;   // 33 counters, one 128-byte line each, rounded up
@@ -76,7 +78,8 @@ inline WorkspaceLayout workspace_layout(const vcas_shape *s)
     w.probe_draw = w.probe_exact + mat;
     w.probe_acc = w.probe_draw + mat;
     w.rule = w.probe_acc + 256;
-    w.uniforms = w.rule + 256;
+    w.lanes = w.rule + 256;
+    w.uniforms = w.lanes + kLaneSumBytes;
     w.packed = w.uniforms + (((size_t)s->N * s->T * sizeof(float) + 255) & ~(size_t)255);
     // bf16: the narrower of G and X over the kept tokens, gathered and multiplied by the token scales
     const size_t packed_bytes = s->dtype == VCAS_BF16 ? (size_t)s->N * s->T * (s->K_in < s->K_out ? s->K_in : s->K_out) * 2 : 0;

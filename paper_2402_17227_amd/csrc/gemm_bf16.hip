@@ -79,28 +79,39 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
     __shared__ float sa_norm[64], sa_p[64];
     __shared__ int sa_count;
     int cnt;
-    if (sa.gsq != nullptr || sa.norms != nullptr) {
+    if (sa.gsq != nullptr || sa.lanes != nullptr) {
         // SampleA decided here, by every workgroup for itself (N <= 64: a few microseconds of one
         // wavefront's work), instead of by a launch of its own in front of this one; the first
         // workgroup writes the plan's fields for everybody else.  The sample norms are either given
-        // or taken here from the row sums (4 N T bytes that sit in L2: short vectors only).
+        // or taken here from the row sums (4 N T bytes that sit in L2: short vectors only) or from
+        // their lane sums (256 N bytes).
         const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
         const uint32_t draw = sa.draw + (sa.draw_offset ? *sa.draw_offset : 0u);   // fetched beside the norms
-        const bool given = sa.norms != nullptr;
-        if (!given) {
+        if (sa.lanes != nullptr) {
+            float v[64 / NW];   // every load first
+#pragma unroll
+            for (int k = 0; k < 64 / NW; ++k) v[k] = sa.lanes[min(wave_ + k * NW, N - 1) * 64 + lane_];
+#pragma unroll
+            for (int k = 0; k < 64 / NW; ++k) {
+                if (wave_ + k * NW >= N) break;
+                const float norm = __builtin_sqrtf(wave_exchange_sum(v[k]));
+                if (lane_ == 0) sa_norm[wave_ + k * NW] = norm;
+            }
+            __syncthreads();
+        } else {
             if (T <= 128) sample_norms_batched<8, 2>(sa.gsq, wave_, NW, N, T, sa_norm);
             else sample_norms_batched<4, 8>(sa.gsq, wave_, NW, N, T, sa_norm);
             __syncthreads();
         }
         if (wave_ == 0) {
-            const float a = lane_ < N ? (given ? sa.norms[lane_] : sa_norm[lane_]) : 0.0f;
+            const float a = lane_ < N ? sa_norm[lane_] : 0.0f;
             const SampleADecision d = sample_a_wave(a, N, sa.budget, sa.seed, sa.layer, draw);
             if (lane_ < N) sa_p[lane_] = d.pr;
             if (d.keep) idx_staged[d.below] = lane_;
             if (lane_ == 0) sa_count = d.count;
             if (blockIdx.x == 0) {
                 if (lane_ < N) {
-                    if (!given) sa.gnorm[lane_] = a;
+                    sa.gnorm[lane_] = a;
                     sa.p[lane_] = d.pr;
                     sa.maskA[lane_] = d.keep ? 1 : 0;
                 }
@@ -670,7 +681,7 @@ vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int
     if (n < 1 || n > kMaxSiblings) return VCAS_EINVAL;
     DgradGroup grp = {};
     for (int i = 0; i < n; ++i) {
-        if ((probs[i].sa.gsq || probs[i].sa.norms) && s.N > 64) return VCAS_EINVAL;
+        if ((probs[i].sa.gsq || probs[i].sa.lanes) && s.N > 64) return VCAS_EINVAL;
         grp.prob[i] = probs[i];
     }
     const int64_t R = (int64_t)s.N * s.T;

@@ -72,13 +72,17 @@ struct RowNormGroup {
     const uint8_t *keep[kMaxSiblings];
 };
 
-// Row norms with their side jobs for up to kMaxSiblings matrices of one shape in one launch.
+// Row norms with their side jobs (SampleW's scores and uniforms) for up to kMaxSamplers matrices with one number
+// of rows in one launch; groups: 16-byte groups per row of each.  Where norms is set, the sums of squares of
+// every row are read there and the matrix is not.
 struct RowJobGroup {
-    const uint4 *A[kMaxSiblings];
-    const uint8_t *keep[kMaxSiblings];
-    float *out[kMaxSiblings];
-    UniformJob job[kMaxSiblings];
-    ScoreJob sj[kMaxSiblings];
+    const uint4 *A[kMaxSamplers];
+    const float *norms[kMaxSamplers];
+    const uint8_t *keep[kMaxSamplers];
+    float *out[kMaxSamplers];
+    UniformJob job[kMaxSamplers];
+    ScoreJob sj[kMaxSamplers];
+    int32_t groups[kMaxSamplers];
 };
 
 }  // namespace vcas

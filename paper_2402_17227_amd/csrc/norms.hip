@@ -51,50 +51,40 @@ __device__ __forceinline__ void row_sumsq_body(const uint4 *__restrict__ A, int6
 
 // The pass over X replaced by a pass over its cached row norms: xsq_forward holds sum_k X[t,k]^2
 // of EVERY row (taken when X was produced, e.g. in the forward pass, by the kernel above).  Writes
-// what row_sumsq_kernel with a ScoreJob writes, bit for bit: xsq (0 on dropped samples), the
+// what row_sumsq_body with a ScoreJob writes, bit for bit: xsq (0 on dropped samples), the
 // SampleW score ((1/p_i) * sqrt(gsq_t)) * sqrt(xsq_t) (0 on dropped samples), and the uniforms.
-__global__ __launch_bounds__(256) void cached_xsq_scores_kernel(const float *__restrict__ xsq_forward, int64_t R, int T,
-                                                                const uint8_t *__restrict__ sample_keep,
-                                                                float *__restrict__ xsq, UniformJob job, ScoreJob sj)
+__device__ __forceinline__ void cached_xsq_scores_body(const float *__restrict__ xsq_forward, int64_t R, int T,
+                                                       const uint8_t *__restrict__ sample_keep,
+                                                       float *__restrict__ xsq, const UniformJob &job, const ScoreJob &sj)
 {
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= R) return;
-    if (job.uniforms) {
-        const uint32_t draw = job.draw + (job.draw_offset ? *job.draw_offset : 0u);
-        job.uniforms[r] = philox_uniform(job.seed, job.layer, job.stream_id, draw, (uint32_t)r);
+    const uint32_t draw = job.draw + (job.uniforms && job.draw_offset ? *job.draw_offset : 0u);
+    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < R; r += (int64_t)gridDim.x * 256) {
+        if (job.uniforms) job.uniforms[r] = philox_uniform(job.seed, job.layer, job.stream_id, draw, (uint32_t)r);
+        const int64_t i = r / T;
+        if (sample_keep[i] == 0) {
+            xsq[r] = 0.0f;
+            sj.score[r] = 0.0f;
+            continue;
+        }
+        const float inv = 1.0f / sj.p[i];
+        const float s1 = inv * __builtin_sqrtf(sj.gsq[r]);
+        const float acc = xsq_forward[r];
+        xsq[r] = acc;
+        sj.score[r] = s1 * __builtin_sqrtf(acc);
     }
-    const int64_t i = r / T;
-    if (sample_keep[i] == 0) {
-        xsq[r] = 0.0f;
-        sj.score[r] = 0.0f;
-        return;
-    }
-    const float inv = 1.0f / sj.p[i];
-    const float s1 = inv * __builtin_sqrtf(sj.gsq[r]);
-    const float acc = xsq_forward[r];
-    xsq[r] = acc;
-    sj.score[r] = s1 * __builtin_sqrtf(acc);
 }
 
+// The same, side jobs included, for several matrices with R rows each: blockIdx.y picks the matrix.  CH covers
+// the longest rows.
 template <bool BF16, int CH>
-__global__ __launch_bounds__(256) void row_sumsq_kernel(const uint4 *__restrict__ A, int64_t R, int groups_per_row,
-                                                        int T, const uint8_t *__restrict__ sample_keep,
-                                                        float *__restrict__ out, UniformJob job, ScoreJob sj)
-{
-    row_sumsq_body<BF16, CH>(A, R, groups_per_row, T, sample_keep, out, job, sj);
-}
-
-// The same, side jobs included, for several matrices of one shape: blockIdx.y picks the matrix.
-template <bool BF16, int CH>
-__global__ __launch_bounds__(256) void row_sumsq_jobs_group_kernel(RowJobGroup grp, int64_t R, int groups_per_row,
-                                                                   int T)
+__global__ __launch_bounds__(256) void row_sumsq_jobs_group_kernel(RowJobGroup grp, int64_t R, int T)
 {
     const int z = blockIdx.y;
-    row_sumsq_body<BF16, CH>(grp.A[z], R, groups_per_row, T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
+    if (grp.norms[z]) cached_xsq_scores_body(grp.norms[z], R, T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
+    else row_sumsq_body<BF16, CH>(grp.A[z], R, grp.groups[z], T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
 }
 
-// row_sumsq_kernel (without the side jobs) for several matrices of one shape in one launch:
-// blockIdx.y picks the matrix.
+// Row sums of squares alone, for several matrices of one shape in one launch: blockIdx.y picks the matrix.
 template <bool BF16, int CH>
 __global__ __launch_bounds__(256) void row_sumsq_group_kernel(RowNormGroup grp, int64_t R, int groups_per_row, int T)
 {
@@ -158,7 +148,6 @@ __global__ __launch_bounds__(256) void row_sumsq_pair_kernel(const uint4 *__rest
 // (sibling layers share their G).
 struct RowsFromBlocks {
     float *out[kMaxSiblings];
-    float *gnorm[kMaxSiblings];   // sample norms too (sample_norms_from_blocks_kernel only)
 };
 
 // The leaves first + 4 * g0 .. of one row, groups g0 <= g < g1, pushed in order (eight loads in flight).
@@ -211,53 +200,48 @@ __global__ __launch_bounds__(256) void rows_from_blocks_kernel(const float4 *__r
     }
 }
 
-// The same, and the sample norms ||G_i||_F = sqrt(sum of the sample's row sums) (Sec. 4.1) behind
-// them: one workgroup of 1024 threads per sample (T <= 1024 rows), `parts` threads per row.  The
-// row sums stay in LDS for the norm, which one wavefront adds in the order of sample_norm_wave
-// (value t on lane t mod 64, ascending t, exchange tree).  The chain row norms -> SampleA -> dX of
-// a layer inside a stack is then this launch and a dgrad that decides SampleA itself.
-__global__ __launch_bounds__(1024) void sample_norms_from_blocks_kernel(const float4 *__restrict__ blocks4, int64_t R, int nb,
-                                                                        int T, const uint8_t *__restrict__ sample_keep,
-                                                                        RowsFromBlocks outs, int n_out)
+// The same for a stack whose dgrad decides SampleA itself: row sums, and of the sample norms what is left when
+// the rows are summed, the 64 lane sums of sample_norm_wave (lane l adds the rows t = l mod 64 of its
+// sample in ascending t); the tree over the lanes and the root are left to the reader.  A sample is
+// cut by lanes, eight to a workgroup, so that N samples are 8 N workgroups and nothing is exchanged
+// between them: with one workgroup per sample (an earlier version) a CU has to pull a whole sample's
+// block sums (128 KiB at T = 512, K = 4096) through its L1, 15-19 us.
+__global__ __launch_bounds__(256) void lane_sums_from_blocks_kernel(const float4 *__restrict__ blocks4, int64_t R, int nb,
+                                                                    int T, const uint8_t *__restrict__ sample_keep,
+                                                                    RowsFromBlocks outs, int n_out, float *__restrict__ lanes)
 {
-    __shared__ float part_sum[1024];
-    __shared__ float row_total[1024];
-    const int i = blockIdx.x, tid = threadIdx.x;
+    __shared__ float part_sum[256];
+    const int i = blockIdx.x, lane0 = blockIdx.y * 8, tid = threadIdx.x;
     const bool live = !sample_keep || sample_keep[i] != 0;
     const int groups = (nb + 3) >> 2;
     int Gp = 1;
     while (Gp < groups) Gp *= 2;
-    int parts = 1;
-    while (parts < 16 && parts * 2 * T <= 1024 && parts * 2 <= Gp) parts *= 2;
-    const int chunk = Gp / parts;
-    const int r = tid % T, part = tid / T;
-    const int64_t row = (int64_t)i * T + r;
-    float acc = 0.0f;
-    if (live && part < parts && part * chunk < groups)
-        acc = block_subtree(blocks4, R, row, part * chunk, min(groups, (part + 1) * chunk), nb);
-    part_sum[tid] = acc;
-    __syncthreads();
-    if (part == 0) {
-        // the parts of a row, pairwise (parts is a power of two, at most 16 with Gp >= parts)
-        float v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = k < parts ? part_sum[r + k * T] : 0.0f;
-#pragma unroll
-        for (int n = 16; n > 1; n /= 2)
-#pragma unroll
-            for (int k = 0; k < n / 2; ++k) v[k] = v[2 * k] + v[2 * k + 1];
-        const float total = live ? v[0] : 0.0f;
-        row_total[r] = total;
-        for (int k = 0; k < n_out; ++k) outs.out[k][row] = total;
-    }
-    __syncthreads();
-    if (tid < 64) {
+    const int parts = Gp < 4 ? Gp : 4, chunk = Gp / parts;   // threads per row, groups per thread: a subtree each
+    const int r = tid & 63, part = tid >> 6;                 // 64 rows at a time: lanes lane0 .. lane0 + 7, eight values of t / 64
+    float acc = 0.0f;                                        // of lane lane0 + tid, tid < 8
+    for (int k0 = 0; 64 * k0 < T; k0 += 8) {
+        const int t = lane0 + (r & 7) + 64 * (k0 + (r >> 3));
+        const int64_t row = (int64_t)i * T + t;
         float sum = 0.0f;
-        for (int t = tid; t < T; t += 64) sum = sum + row_total[t];
-        const float norm = __builtin_sqrtf(wave_exchange_sum(sum));
-        if (tid == 0)
-            for (int k = 0; k < n_out; ++k) outs.gnorm[k][i] = norm;
+        if (live && t < T && part < parts && part * chunk < groups)
+            sum = block_subtree(blocks4, R, row, part * chunk, min(groups, (part + 1) * chunk), nb);
+        part_sum[tid] = sum;
+        __syncthreads();
+        if (tid < 64 && t < T) {
+            float total = part_sum[tid];
+            if (parts == 2) total = part_sum[tid] + part_sum[64 + tid];
+            if (parts == 4) total = (part_sum[tid] + part_sum[64 + tid]) + (part_sum[128 + tid] + part_sum[192 + tid]);
+            for (int k = 0; k < n_out; ++k) outs.out[k][row] = total;
+            part_sum[tid] = total;
+        }
+        __syncthreads();
+        if (tid < 8)
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (lane0 + tid + 64 * (k0 + k) < T) acc = acc + part_sum[tid + 8 * k];
+        __syncthreads();
     }
+    if (tid < 8) lanes[i * 64 + lane0 + tid] = acc;
 }
 
 // outs: n_out <= kMaxSiblings arrays of R floats
@@ -272,21 +256,15 @@ vcas_status rows_from_blocks(const float *blocks, int64_t R, int K, int T, const
     return launch_status();
 }
 
-// True where sample_norms_from_blocks applies.
-bool sample_norms_from_blocks_fits(int N, int T) { return T <= 1024 && N >= 1; }
-
-// Row sums (outs) and sample norms (gnorms) of N samples of T <= 1024 rows from the block sums.
-vcas_status sample_norms_from_blocks(const float *blocks, int N, int T, int K, const uint8_t *keep, float *const *outs,
-                                     float *const *gnorms, int n_out, hipStream_t st)
+// Row sums (outs) and lane sums (lanes [N][64]) from the block sums, see lane_sums_from_blocks_kernel.
+vcas_status lane_sums_from_blocks(const float *blocks, int N, int T, int K, const uint8_t *keep, float *const *outs,
+                                  int n_out, float *lanes, hipStream_t st)
 {
-    if (n_out < 1 || n_out > kMaxSiblings || !sample_norms_from_blocks_fits(N, T)) return VCAS_EINVAL;
+    if (n_out < 1 || n_out > kMaxSiblings) return VCAS_EINVAL;
     RowsFromBlocks o = {};
-    for (int k = 0; k < n_out; ++k) {
-        o.out[k] = outs[k];
-        o.gnorm[k] = gnorms[k];
-    }
-    hipLaunchKernelGGL(sample_norms_from_blocks_kernel, dim3((unsigned)N), dim3(1024), 0, st,
-                       reinterpret_cast<const float4 *>(blocks), (int64_t)N * T, (K + 63) / 64, T, keep, o, n_out);
+    for (int k = 0; k < n_out; ++k) o.out[k] = outs[k];
+    hipLaunchKernelGGL(lane_sums_from_blocks_kernel, dim3((unsigned)N, 8), dim3(256), 0, st,
+                       reinterpret_cast<const float4 *>(blocks), (int64_t)N * T, (K + 63) / 64, T, keep, o, n_out, lanes);
     return launch_status();
 }
 
@@ -303,27 +281,6 @@ __global__ __launch_bounds__(256) void sample_norm_kernel(const float *__restric
     for (int t = lane; t < T; t += 64) acc = acc + p[t];
     acc = wave_exchange_sum(acc);
     if (lane == 0) gnorm[i] = __builtin_sqrtf(acc);
-}
-
-template <bool BF16>
-static vcas_status launch_row_sumsq(const void *A, int64_t R, int K, int T, const uint8_t *keep, float *out,
-                                    const UniformJob &job, const ScoreJob &sj, hipStream_t st)
-{
-    const int groups = K / (BF16 ? 8 : 4);
-    const int need = (groups + 63) / 64;
-    int64_t blocks64 = (R + 3) / 4;
-    const int blocks = (int)(blocks64 < 4096 ? blocks64 : 4096);
-    const uint4 *a = static_cast<const uint4 *>(A);
-#define VCAS_LAUNCH_CH(C) \
-    hipLaunchKernelGGL((row_sumsq_kernel<BF16, C>), dim3(blocks), dim3(256), 0, st, a, R, groups, T, keep, out, job, sj)
-    if (need <= 1) VCAS_LAUNCH_CH(1);
-    else if (need <= 2) VCAS_LAUNCH_CH(2);
-    else if (need <= 3) VCAS_LAUNCH_CH(3);
-    else if (need <= 4) VCAS_LAUNCH_CH(4);
-    else if (need <= 6) VCAS_LAUNCH_CH(6);
-    else VCAS_LAUNCH_CH(8);
-#undef VCAS_LAUNCH_CH
-    return launch_status();
 }
 
 template <bool BF16>
@@ -345,18 +302,19 @@ static vcas_status launch_row_sumsq_group(const RowNormGroup &grp, int n, int64_
     return launch_status();
 }
 
-// row_sumsq_scores_uniforms for n <= kMaxSiblings layers of one shape in one launch
-vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int K, int T,
-                                            hipStream_t st)
+// Row norms of X on kept samples, the SampleW scores and the uniforms of n <= kMaxSamplers layers with R rows
+// each and one dtype in one launch
+vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int T, hipStream_t st)
 {
-    if (n < 1 || n > kMaxSiblings) return VCAS_EINVAL;
+    if (n < 1 || n > kMaxSamplers) return VCAS_EINVAL;
     const bool bf = dtype == VCAS_BF16;
-    const int groups = K / (bf ? 8 : 4);
-    const int need = (groups + 63) / 64;
-    int64_t blocks64 = (R + 3) / 4;
+    int need = 0;
+    for (int i = 0; i < n; ++i)
+        if (!grp.norms[i] && (grp.groups[i] + 63) / 64 > need) need = (grp.groups[i] + 63) / 64;
+    const int64_t blocks64 = need ? (R + 3) / 4 : (R + 255) / 256;
     const int blocks = (int)(blocks64 < 4096 ? blocks64 : 4096);
 #define VCAS_LAUNCH_CH(B, C) \
-    hipLaunchKernelGGL((row_sumsq_jobs_group_kernel<B, C>), dim3(blocks, n), dim3(256), 0, st, grp, R, groups, T)
+    hipLaunchKernelGGL((row_sumsq_jobs_group_kernel<B, C>), dim3(blocks, n), dim3(256), 0, st, grp, R, T)
 #define VCAS_LAUNCH_DT(C)          \
     do {                           \
         if (bf) VCAS_LAUNCH_CH(true, C); \
@@ -384,34 +342,11 @@ vcas_status row_sumsq_group(const RowNormGroup &grp, int n, int dtype, int64_t R
 vcas_status row_sumsq(const void *A, int dtype, int64_t R, int K, int T, const uint8_t *keep, float *out,
                       hipStream_t st)
 {
-    const UniformJob none = {nullptr, 0, 0, 0, 0, nullptr};
-    const ScoreJob no_score = {nullptr, nullptr, nullptr};
-    return dtype == VCAS_BF16 ? launch_row_sumsq<true>(A, R, K, T, keep, out, none, no_score, st)
-                              : launch_row_sumsq<false>(A, R, K, T, keep, out, none, no_score, st);
-}
-
-// row norms of X on kept samples, the SampleW scores and the uniforms of sampler `stream_id`
-// (null: none) in one launch
-vcas_status row_sumsq_scores_uniforms(const void *X, int dtype, int64_t R, int K, int T, const uint8_t *keep,
-                                      float *xsq, const float *gsq, const float *p, float *score, const vcas_rng &rng,
-                                      uint32_t stream_id, float *uniforms, hipStream_t st)
-{
-    const UniformJob job = {uniforms, rng.seed, rng.layer, stream_id, rng.draw, rng.draw_offset};
-    const ScoreJob sj = {gsq, p, score};
-    return dtype == VCAS_BF16 ? launch_row_sumsq<true>(X, R, K, T, keep, xsq, job, sj, st)
-                              : launch_row_sumsq<false>(X, R, K, T, keep, xsq, job, sj, st);
-}
-
-// row_sumsq_scores_uniforms without the sweep over X: its row norms come from xsq_forward
-vcas_status cached_xsq_scores_uniforms(const float *xsq_forward, int64_t R, int T, const uint8_t *keep, float *xsq,
-                                       const float *gsq, const float *p, float *score, const vcas_rng &rng,
-                                       uint32_t stream_id, float *uniforms, hipStream_t st)
-{
-    const UniformJob job = {uniforms, rng.seed, rng.layer, stream_id, rng.draw, rng.draw_offset};
-    const ScoreJob sj = {gsq, p, score};
-    hipLaunchKernelGGL(cached_xsq_scores_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, st, xsq_forward, R, T,
-                       keep, xsq, job, sj);
-    return launch_status();
+    RowNormGroup grp = {};
+    grp.A[0] = static_cast<const uint4 *>(A);
+    grp.out[0] = out;
+    grp.keep[0] = keep;
+    return row_sumsq_group(grp, 1, dtype, R, K, T, st);
 }
 
 template <bool BF16>
