@@ -146,16 +146,53 @@ static WgradItem wgrad_item(const vcas_shape &s, const void *G, const void *X, c
     return it;
 }
 
+// Where the weight gradient of a bf16 layer on its own is computed, by the tokens it is expected to keep
+// (0: unknown, any of the R).  The gathering kernel is ONE launch that multiplies the token scales into its
+// fragments; the packed form takes two or three (pack, GEMM, reduction of slices), 4 to 6 us each however
+// short the contraction.  64x64 tiles while every CU can have one at once, 128x128 tiles beyond.  Alone on the
+// chip, gathering against packed: 264x136 with 56 tokens 9 and 13 us; 768x768 with 1891 tokens 22 and 26
+// (3782: 39 and 29); 1024x1024 with 1638 tokens 21 and 27; 768x3072 with 1024 tokens 24 and 28 (3072x768 with
+// 1891 tokens: 36 and 30); 3704x3456 with 96 tokens 20 and 24.
+enum WgradForm { kPacked, kGatherSmall, kGatherLarge };
+static WgradForm wgrad_form(const vcas_shape &s, int64_t tokens)
+{
+    if (tokens <= 0 || !offsets_fit(s)) return kPacked;
+    const int64_t small = gather_tiles(VCAS_BF16, s.K_out, s.K_in, false), large = gather_tiles(VCAS_BF16, s.K_out, s.K_in, true);
+    if (small <= 256) return tokens <= (small < 32 ? 1024 : 2048) ? kGatherSmall : kPacked;
+    return large * (tokens < 64 ? 64 : tokens) <= 160 * 1024 ? kGatherLarge : kPacked;
+}
+static int64_t expected_tokens(const vcas_shape &s, double rho, double nu, int token_sampling)
+{
+    const int64_t t = (int64_t)((double)((int64_t)s.N * s.T) * rho * (token_sampling ? nu : 1.0) + 0.5);
+    return t < 1 ? 1 : t;
+}
+
 // One layer on its own.  partials: room for wgrad_split(s) partial tiles; packed (bf16): room for
 // R rows of the narrower operand.
 static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const void *X, const float *scale,
                                        const int32_t *idxW, const int32_t *cntW, float *dW, float *partials,
-                                       uint16_t *packed, hipStream_t st, int fill = kWgradFill)
+                                       uint16_t *packed, hipStream_t st, int fill, int64_t tokens)
 {
     fill = fill_or_default(fill);
     if (s.dtype != VCAS_BF16)
         return wgrad_f32(s, G, X, scale, idxW, cntW, dW, partials, wgrad_split_for(&s, wgrad_tiles_f32(s.K_out, s.K_in), fill),
                          fill, st);
+    const WgradForm form = wgrad_form(s, tokens);
+    if (form != kPacked) {
+        GatherTask q = {};
+        q.G = G;
+        q.X = X;
+        q.row_scale = scale;
+        q.idx = idxW;
+        q.cnt = cntW;
+        q.dst = dW;
+        q.R = (int32_t)((int64_t)s.N * s.T);
+        q.K_in = s.K_in;
+        q.K_out = s.K_out;
+        q.scale_g = s.K_out < s.K_in;   // the narrower operand, as in the packed form
+        q.splits = 1;
+        return wgrad_gather(&q, 1, VCAS_BF16, form == kGatherLarge, false, st);
+    }
     const int tile = wgrad_tile_choice(wgrad_tiles_bf16(s.K_out, s.K_in, 256), wgrad_tiles_bf16(s.K_out, s.K_in, 128), fill);
     WgradItem it = wgrad_item(s, G, X, scale, idxW, cntW, dW, partials, packed);
     it.splits = wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), fill);
@@ -164,12 +201,12 @@ static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const
 
 static vcas_status dispatch_wgrad(const vcas_shape &s, const void *G, const void *X, const float *scale,
                                   const int32_t *idxW, const int32_t *cntW, float *dW, void *workspace,
-                                  hipStream_t st, int fill = kWgradFill)
+                                  hipStream_t st, int fill = kWgradFill, int64_t tokens = 0)
 {
     const WorkspaceLayout w = workspace_layout(&s);
     unsigned char *base = static_cast<unsigned char *>(workspace);
     return dispatch_wgrad_into(s, G, X, scale, idxW, cntW, dW, reinterpret_cast<float *>(base + w.partials),
-                               reinterpret_cast<uint16_t *>(base + w.packed), st, fill);
+                               reinterpret_cast<uint16_t *>(base + w.packed), st, fill, tokens);
 }
 
 // ---- the library's own scratch, for the entry point that takes no workspace --------------------
@@ -378,7 +415,8 @@ static vcas_status weight_half(const vcas_shape &s, const void *G, const void *X
     sampler.prob[0] = sample_w_problem(s, rho, nu, pl, workspace);
     VCAS_TRY(sampler_w_group(sampler, 1, together ? 1 : 0, s.N, s.T, token_sampling, together ? 1 : 2, st));
     if (dW)
-        VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st));
+        VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st, kWgradFill,
+                                expected_tokens(s, rho, nu, token_sampling)));
     return VCAS_OK;
 }
 
@@ -491,8 +529,8 @@ static vcas_status weight_half_group(const vcas_layer_args *layers, int n, hipSt
     return sampler_w_group(samplers, n, 0, s.N, s.T, layers[0].token_sampling, 2, st);
 }
 
-// Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched
-// launches, fp32 layers one by one).  A layer with wgrad_fill == 0 gets the tile and the slices a
+// Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched launches unless a
+// call on its own would gather, fp32 layers one by one).  A layer with wgrad_fill == 0 gets the tile and the slices a
 // call on its own would pick, hence that call's bits; the others are planned per launch: the
 // tiles of every layer of the batch count towards `fill`, so a block's weight gradients fill the
 // chip together and are rarely sliced at all.
@@ -504,20 +542,26 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
             ++l;
             continue;
         }
-        if (a.shape.dtype != VCAS_BF16) {
+        // fp32, or as a call on its own would gather
+        auto own = [](const vcas_layer_args &b) { return b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill; };
+        auto by_itself = [&](const vcas_layer_args &b) {
+            return b.shape.dtype != VCAS_BF16 ||
+                   (own(b) && wgrad_form(b.shape, expected_tokens(b.shape, b.rho, b.nu, b.token_sampling)) != kPacked);
+        };
+        if (by_itself(a)) {
             VCAS_TRY(dispatch_wgrad(a.shape, a.G, a.X, a.plan.scaleW, a.plan.idxW, a.plan.cntW, a.dW, a.workspace, st,
-                                    a.wgrad_fill));
+                                    a.wgrad_fill, expected_tokens(a.shape, a.rho, a.nu, a.token_sampling)));
             ++l;
             continue;
         }
         // a run of bf16 layers that plan their launch the same way
-        const bool alone = a.wgrad_fill == 0 || a.wgrad_fill >= kWgradFill;
+        const bool alone = own(a);
         int picked[kWgradBatch], n = 0, next = l;
         int tiles256 = 0, tiles128 = 0;
         for (; next < l1 && n < kWgradBatch; ++next) {
             const vcas_layer_args &b = layers[next];
             if (!b.dW) continue;
-            if (b.shape.dtype != VCAS_BF16 || (b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill) != alone) break;
+            if (by_itself(b) || own(b) != alone) break;
             const int t256 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 256), t128 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 128);
             if (alone && n > 0 &&
                 wgrad_tile_choice(t256, t128, kWgradFill) !=
@@ -589,7 +633,9 @@ static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, cons
         VCAS_TRY(plan_fused(G, s.K_out, X, s.K_in, s.dtype, s.N, s.T, (double)s.N * rho, (double)R * rho * nu,
                             token_sampling, rng, uniforms_of(s, workspace), tickets, pl, st));
         if (dX) VCAS_TRY(dispatch_dgrad(s, G, W, pl.p, pl.idxA, pl.cntA, dX, nullptr, true, (int64_t)((double)R * rho + 0.5), st));
-        if (dW) VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st));
+        if (dW)
+            VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st, kWgradFill,
+                                    expected_tokens(s, rho, nu, token_sampling)));
         return VCAS_OK;
     }
     if (!forked) {
@@ -925,7 +971,8 @@ vcas_status vcas_sampled_wgrad_static(const vcas_shape *shape, const void *G, co
     // whatever the last call left in the buffer does not matter and nothing is cleared
     unsigned char *base = static_cast<unsigned char *>(buf);
     return dispatch_wgrad_into(*shape, G, X, row_scale_, idxW, cntW, dW, reinterpret_cast<float *>(base),
-                               reinterpret_cast<uint16_t *>(base + wgrad_partial_bytes(*shape)), as_stream(stream));
+                               reinterpret_cast<uint16_t *>(base + wgrad_partial_bytes(*shape)), as_stream(stream),
+                               kWgradFill, 0);
 }
 
 vcas_status vcas_linear_backward(const vcas_shape *shape, const void *G, const void *X, const void *W, double rho,

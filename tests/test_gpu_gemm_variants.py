@@ -38,6 +38,21 @@ def test_fp32_kernels_at_their_edges(vb, case):
     _against_oracle(F32, *case)
 
 
+BF16_CASES = [
+    # wgrad gathering with 64x64 tiles: fewer than 32 of them, up to 256, ragged; G scaled, X scaled
+    (3, 11, 8, 8, 0.5, 0.5), (9, 233, 264, 136, 0.6, 0.7), (9, 233, 136, 264, 0.7, 0.7), (8, 256, 1024, 1024, 1.0, 0.99),
+    # nothing kept, one token; 1024 and 1025 tokens of fewer than 32 tiles (gathering, packed)
+    (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1024, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
+    # 128x128 tiles, ragged, either side scaled; beyond them the packed form
+    (3, 67, 1096, 1160, 0.7, 0.7), (3, 67, 1160, 1096, 0.7, 0.7), (8, 257, 1096, 1160, 1.0, 0.9),
+]
+
+
+@pytest.mark.parametrize("case", BF16_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_bf16_kernels_at_their_edges(vb, case):
+    _against_oracle(BF16, *case)
+
+
 def _against_oracle(dtype, N, T, K_in, K_out, rho, nu):
     from tests.gpu_util import compare_plan, rel_l2, rel_l2_rows, rel_l2_tiles, run_layer_gpu
     sp = workloads.LayerSpec("edge", dtype, N, T, K_in, K_out, rho, nu, layer=5, seed=31, gen_seed=N + T, token_sigma=0.5)
