@@ -43,9 +43,8 @@ __device__ __forceinline__ void for_constants(F &&f)
 
 constexpr int kIdxStaged = 1024;   // kept-sample indices a workgroup stages in LDS ahead of the count
 
-// grid: 1-D, tiles_n * (ceil(R/BM) + 1) + 8 workgroups.  The first ceil8(compute
-// tiles) ids compute (spread over the XCDs in contiguous runs), the following
-// ones write the zero rows of dropped samples, the rest exit.
+// One BM x BN output tile at (kept row m0, column n0).  idx_staged: the first `staged` entries of the kept list, in a
+// stage that the prologue does not load before the row table is built.
 // SPQ >= 0: one barrier at the top of every step; the loads of the next step are spread over the
 // MFMAs of the first SPQ quarters of the current one (0: all issued right after the barrier).
 // SPQ < 0 (two stages only): the barrier sits ahead of the step's LAST k-slice, the loads of the
@@ -54,12 +53,11 @@ constexpr int kIdxStaged = 1024;   // kept-sample indices a workgroup stages in 
 // wait for LDS behind a barrier there).
 // SPQ = kWholeStep: all fragments of a step are read one step ahead.
 template <int BM, int BN, int WM, int WN, int NS, int SPQ>
-__device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, const uint16_t *__restrict__ W,
+__device__ __forceinline__ void dgrad_bf16_tile(const uint16_t *__restrict__ G, const uint16_t *__restrict__ W,
                                                 const float *__restrict__ p, const int32_t *__restrict__ idxA,
-                                                const int32_t *__restrict__ cntA, uint16_t *__restrict__ dX, int N,
-                                                int T, int K_in, int K_out, int tiles_n,
-                                                const uint16_t *__restrict__ J, int fill_dropped,
-                                                const InlineSampleA &sa, float *__restrict__ sq_blocks)
+                                                const int32_t *idx_staged, int staged, uint16_t *__restrict__ dX,
+                                                int N, int T, int K_in, int K_out, const uint16_t *__restrict__ J,
+                                                float *__restrict__ sq_blocks, int64_t m0, int n0, int64_t M)
 {
     constexpr int NW = WM * WN, NT = NW * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -68,104 +66,10 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
     constexpr int STAGE = (BM + BN) * 128, B_AT = BM * 128, B_PITCH = BN * 2;
     constexpr int LOADS = AI + BI;
     static_assert(AI >= 1 && BI >= 1 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/wave mismatch");
-    static_assert(STAGE >= kIdxStaged * 4, "index staging area does not fit a stage");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int32_t *row_of = reinterpret_cast<int32_t *>(smem + NS * STAGE);
     float *scale_of = reinterpret_cast<float *>(row_of + BM);
-    // The last stage is not loaded before the first barrier of the main loop; until then it
-    // holds the kept-sample list, fetched together with the count instead of after it.
-    int32_t *idx_staged = reinterpret_cast<int32_t *>(smem + (NS - 1) * STAGE);
-    const int staged = min(N, kIdxStaged);
-    __shared__ float sa_norm[64], sa_p[64];
-    __shared__ int sa_count;
-    int cnt;
-    if (sa.gsq != nullptr || sa.lanes != nullptr) {
-        // SampleA decided here, by every workgroup for itself (N <= 64: a few microseconds of one
-        // wavefront's work), instead of by a launch of its own in front of this one; the first
-        // workgroup writes the plan's fields for everybody else.  The sample norms are either given
-        // or taken here from the row sums (4 N T bytes that sit in L2: short vectors only) or from
-        // their lane sums (256 N bytes).
-        const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
-        const uint32_t draw = sa.draw + (sa.draw_offset ? *sa.draw_offset : 0u);   // fetched beside the norms
-        if (sa.lanes != nullptr) {
-            float v[64 / NW];   // every load first
-#pragma unroll
-            for (int k = 0; k < 64 / NW; ++k) v[k] = sa.lanes[min(wave_ + k * NW, N - 1) * 64 + lane_];
-#pragma unroll
-            for (int k = 0; k < 64 / NW; ++k) {
-                if (wave_ + k * NW >= N) break;
-                const float norm = __builtin_sqrtf(wave_exchange_sum(v[k]));
-                if (lane_ == 0) sa_norm[wave_ + k * NW] = norm;
-            }
-            __syncthreads();
-        } else {
-            if (T <= 128) sample_norms_batched<8, 2>(sa.gsq, wave_, NW, N, T, sa_norm);
-            else sample_norms_batched<4, 8>(sa.gsq, wave_, NW, N, T, sa_norm);
-            __syncthreads();
-        }
-        if (wave_ == 0) {
-            const float a = lane_ < N ? sa_norm[lane_] : 0.0f;
-            const SampleADecision d = sample_a_wave(a, N, sa.budget, sa.seed, sa.layer, draw);
-            if (lane_ < N) sa_p[lane_] = d.pr;
-            if (d.keep) idx_staged[d.below] = lane_;
-            if (lane_ == 0) sa_count = d.count;
-            if (blockIdx.x == 0) {
-                if (lane_ < N) {
-                    sa.gnorm[lane_] = a;
-                    sa.p[lane_] = d.pr;
-                    sa.maskA[lane_] = d.keep ? 1 : 0;
-                }
-                if (d.keep) sa.idxA[d.below] = lane_;
-                if (lane_ == 0) *sa.cntA = d.count;
-            }
-        }
-        __syncthreads();
-        cnt = sa_count;
-        idxA = idx_staged;   // the kept list lives in LDS from here on (N <= 64 entries)
-        p = sa_p;
-    } else {
-        for (int j = threadIdx.x; j < staged; j += NT) idx_staged[j] = idxA[j];
-        cnt = min(max(*cntA, 0), N);
-    }
-    const int64_t M = (int64_t)cnt * T;
     const int64_t R = (int64_t)N * T;
-    const int compute = (int)((M + BM - 1) / BM) * tiles_n;
-    const int compute8 = (compute + 7) / 8 * 8;
-
-    if ((int)blockIdx.x >= compute8) {
-        // zero-fill duty: rows of the samples that are not in the kept list
-        if (!fill_dropped) return;
-        const int z = blockIdx.x - compute8;
-        const int64_t d0 = (int64_t)(z / tiles_n) * BM;
-        const int n0 = (z % tiles_n) * BN;
-        if (d0 >= R - M) return;
-        for (int r = threadIdx.x; r < BM; r += NT) {
-            const int64_t d = d0 + r;
-            int32_t dst = -1;
-            if (d < R - M) dst = nth_missing(idxA, cnt, (int)(d / T)) * T + (int)(d % T);
-            row_of[r] = dst;
-        }
-        __syncthreads();
-        constexpr int CH = BN / 8;
-        for (int u = threadIdx.x; u < BM * CH; u += NT) {
-            const int r = u / CH, col = n0 + (u % CH) * 8;
-            if (row_of[r] >= 0 && col < K_in)
-                *reinterpret_cast<uint4 *>(dX + (int64_t)row_of[r] * K_in + col) = make_uint4(0u, 0u, 0u, 0u);
-        }
-        return;
-    }
-    const int tile = xcd_remap(blockIdx.x, compute);
-    if (tile >= compute) return;
-    int tile_m, tile_n;
-    // An XCD gets a contiguous run of tile ids and has an L2 of its own: a run that spans all
-    // column tiles reads its rows of G once and W whole (W eight times in all); with the
-    // columns in `a` panels an XCD reads 1/a of W and every row of G is read by `a` XCDs.
-    // a*|G kept| + (8/a)*|W|, i.e. a*M + (8/a)*K_in, is least at a = 1, 2, 4 for M >= 4 K_in, >= K_in, below.
-    const int a_panels = M >= 4 * (int64_t)K_in ? 1 : M >= K_in ? 2 : 4;
-    const int panel = min(8, max(1, (tiles_n + a_panels - 1) / a_panels));
-    panel_order_rt(tile, compute / tiles_n, tiles_n, panel, tile_m, tile_n);
-    const int n0 = tile_n * BN;
-    const int64_t m0 = (int64_t)tile_m * BM;
     __syncthreads();   // idx_staged complete
     for (int r = threadIdx.x; r < BM; r += NT) {
         const int64_t m = m0 + r;
@@ -578,6 +482,157 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
     }
 }
 
+// 256x256 tiles run one to a CU, and a last round of few tiles costs a whole round.  The kept count is known on the device
+// only, so the kernel itself looks at the remainder: where it is at most half the CUs, its tiles go out as four 128x128
+// quarters each (the tile that reads whole steps ahead, eight wavefronts, the same LDS; a quarter takes 0.27 of a tile).
+// Measured alone, 65536 rows, without and with: 1024 <- 4096, 528 tiles 313 and 270 us, 576 tiles 329 and 278, 640 tiles 334
+// and 316; 1024 <- 2048, 528 tiles 154 and 133; 1024 <- 1536, 576 tiles 142 and 135; 96 tiles of 1024 <- 4096 77 and 62.
+// A short contraction has no rounds to speak of (prologues and epilogues let the CUs drift apart) and loses by the
+// quarters' extra operand bytes: 4096 <- 1024, 272 tiles 77 and 80 us, 320 tiles 98 and 104.
+constexpr int kTailCUs = 256, kTailContraction = 1536;
+__device__ __forceinline__ int tail_tiles(int compute, int K_out)
+{
+    const int last = compute % kTailCUs;
+    return K_out >= kTailContraction && last <= kTailCUs / 2 ? last : 0;
+}
+
+// grid: 1-D per layer, sized by dgrad_grid.  The first ceil8(compute
+// tiles) ids compute (spread over the XCDs in contiguous runs; the quarters of the last round, if any, behind the whole
+// tiles), the following ones write the zero rows of dropped samples, the rest exit.
+template <int BM, int BN, int WM, int WN, int NS, int SPQ>
+__device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, const uint16_t *__restrict__ W,
+                                                const float *__restrict__ p, const int32_t *__restrict__ idxA,
+                                                const int32_t *__restrict__ cntA, uint16_t *__restrict__ dX, int N,
+                                                int T, int K_in, int K_out, int tiles_n,
+                                                const uint16_t *__restrict__ J, int fill_dropped,
+                                                const InlineSampleA &sa, float *__restrict__ sq_blocks)
+{
+    constexpr int NW = WM * WN, NT = NW * 64, STAGE = (BM + BN) * 128;
+    constexpr bool kTail = BM == 256;   // one workgroup per CU
+    static_assert(STAGE >= kIdxStaged * 4, "index staging area does not fit a stage");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int32_t *row_of = reinterpret_cast<int32_t *>(smem + NS * STAGE);
+    // The last stage is not loaded before the first barrier of the main loop; until then it
+    // holds the kept-sample list, fetched together with the count instead of after it.
+    int32_t *idx_staged = reinterpret_cast<int32_t *>(smem + (NS - 1) * STAGE);
+    const int staged = min(N, kIdxStaged);
+    __shared__ float sa_norm[64], sa_p[64];
+    __shared__ int32_t sa_idx[64];
+    __shared__ int sa_count;
+    int cnt;
+    if (sa.gsq != nullptr || sa.lanes != nullptr) {
+        // SampleA decided here, by every workgroup for itself (N <= 64: a few microseconds of one
+        // wavefront's work), instead of by a launch of its own in front of this one; the first
+        // workgroup writes the plan's fields for everybody else.  The sample norms are either given
+        // or taken here from the row sums (4 N T bytes that sit in L2: short vectors only) or from
+        // their lane sums (256 N bytes).
+        const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
+        const uint32_t draw = sa.draw + (sa.draw_offset ? *sa.draw_offset : 0u);   // fetched beside the norms
+        if (sa.lanes != nullptr) {
+            float v[64 / NW];   // every load first
+#pragma unroll
+            for (int k = 0; k < 64 / NW; ++k) v[k] = sa.lanes[min(wave_ + k * NW, N - 1) * 64 + lane_];
+#pragma unroll
+            for (int k = 0; k < 64 / NW; ++k) {
+                if (wave_ + k * NW >= N) break;
+                const float norm = __builtin_sqrtf(wave_exchange_sum(v[k]));
+                if (lane_ == 0) sa_norm[wave_ + k * NW] = norm;
+            }
+            __syncthreads();
+        } else {
+            if (T <= 128) sample_norms_batched<8, 2>(sa.gsq, wave_, NW, N, T, sa_norm);
+            else sample_norms_batched<4, 8>(sa.gsq, wave_, NW, N, T, sa_norm);
+            __syncthreads();
+        }
+        if (wave_ == 0) {
+            const float a = lane_ < N ? sa_norm[lane_] : 0.0f;
+            const SampleADecision d = sample_a_wave(a, N, sa.budget, sa.seed, sa.layer, draw);
+            if (lane_ < N) sa_p[lane_] = d.pr;
+            if (d.keep) sa_idx[d.below] = lane_;
+            if (lane_ == 0) sa_count = d.count;
+            if (blockIdx.x == 0) {
+                if (lane_ < N) {
+                    sa.gnorm[lane_] = a;
+                    sa.p[lane_] = d.pr;
+                    sa.maskA[lane_] = d.keep ? 1 : 0;
+                }
+                if (d.keep) sa.idxA[d.below] = lane_;
+                if (lane_ == 0) *sa.cntA = d.count;
+            }
+        }
+        __syncthreads();
+        cnt = sa_count;
+        idxA = idx_staged = sa_idx;   // the kept list lives in LDS from here on (N <= 64 entries)
+        p = sa_p;
+    } else {
+        for (int j = threadIdx.x; j < staged; j += NT) idx_staged[j] = idxA[j];
+        cnt = min(max(*cntA, 0), N);
+    }
+    const int64_t M = (int64_t)cnt * T;
+    const int64_t R = (int64_t)N * T;
+    const int compute = (int)((M + BM - 1) / BM) * tiles_n;
+    // Tiles of the last round that go out as quarters (not in a launch of siblings: each knows its own count only)
+    const int tail = kTail && gridDim.y == 1 ? tail_tiles(compute, K_out) : 0;
+    // 8 ids per XCD for each quarter that an XCD gets, 32 at most (a CU each); the ones beyond 32 are second quarters
+    const int per_xcd = (4 * tail + 7) / 8;
+    const int whole8 = (compute - tail + 7) / 8 * 8, compute8 = whole8 + 8 * min(per_xcd, kTailCUs / 8);
+
+    if ((int)blockIdx.x >= compute8) {
+        // zero-fill duty: rows of the samples that are not in the kept list
+        if (!fill_dropped) return;
+        const int z = blockIdx.x - compute8;
+        const int64_t d0 = (int64_t)(z / tiles_n) * BM;
+        const int n0 = (z % tiles_n) * BN;
+        if (d0 >= R - M) return;
+        for (int r = threadIdx.x; r < BM; r += NT) {
+            const int64_t d = d0 + r;
+            int32_t dst = -1;
+            if (d < R - M) dst = nth_missing(idxA, cnt, (int)(d / T)) * T + (int)(d % T);
+            row_of[r] = dst;
+        }
+        __syncthreads();
+        constexpr int CH = BN / 8;
+        for (int u = threadIdx.x; u < BM * CH; u += NT) {
+            const int r = u / CH, col = n0 + (u % CH) * 8;
+            if (row_of[r] >= 0 && col < K_in)
+                *reinterpret_cast<uint4 *>(dX + (int64_t)row_of[r] * K_in + col) = make_uint4(0u, 0u, 0u, 0u);
+        }
+        return;
+    }
+    const bool quarters = kTail && (int)blockIdx.x >= whole8;
+    const int whole = compute - tail;
+    const int id = (int)blockIdx.x - whole8;
+    const int first = quarters ? (id & 7) * per_xcd + (id >> 3) : xcd_remap(blockIdx.x, whole);
+    if (first >= (quarters ? 4 * tail : whole)) return;
+    int tile_m, tile_n;
+    // An XCD gets a contiguous run of tile ids and has an L2 of its own: a run that spans all
+    // column tiles reads its rows of G once and W whole (W eight times in all); with the
+    // columns in `a` panels an XCD reads 1/a of W and every row of G is read by `a` XCDs.
+    // a*|G kept| + (8/a)*|W|, i.e. a*M + (8/a)*K_in, is least at a = 1, 2, 4 for M >= 4 K_in, >= K_in, below.
+    const int a_panels = M >= 4 * (int64_t)K_in ? 1 : M >= K_in ? 2 : 4;
+    const int panel = min(8, max(1, (tiles_n + a_panels - 1) / a_panels));
+    if constexpr (kTail) {
+        if (quarters) {
+            for (int q = first; q < min(4 * tail, ((id & 7) + 1) * per_xcd); q += kTailCUs / 8) {
+                panel_order_rt(whole + (q >> 2), compute / tiles_n, tiles_n, panel, tile_m, tile_n);
+                const int64_t m0 = (int64_t)tile_m * BM + (q >> 1 & 1) * 128;
+                const int n0 = tile_n * BN + (q & 1) * 128;
+                // the operand stages of the first quarter lie over the staged list (if it is not SampleA's own)
+                const int in_lds = q == first || idxA == sa_idx ? staged : 0;
+                if (m0 < M && n0 < K_in)
+                    dgrad_bf16_tile<128, 128, 4, 2, 4, kWholeStep>(G, W, p, idxA, idx_staged, in_lds, dX, N, T, K_in, K_out, J,
+                                                                   sq_blocks, m0, n0, M);
+                __syncthreads();   // the next one's row table and stages lie over this one's
+            }
+            return;
+        }
+    }
+    panel_order_rt(first, compute / tiles_n, tiles_n, panel, tile_m, tile_n);
+    const int n0 = tile_n * BN;
+    const int64_t m0 = (int64_t)tile_m * BM;
+    dgrad_bf16_tile<BM, BN, WM, WN, NS, SPQ>(G, W, p, idxA, idx_staged, staged, dX, N, T, K_in, K_out, J, sq_blocks, m0, n0, M);
+}
+
 template <int BM, int BN, int WM, int WN, int NS, int OCC, int SPQ>
 __global__ __launch_bounds__(WM *WN * 64, OCC) void dgrad_bf16_kernel(const uint16_t *__restrict__ G,
                                                                   const uint16_t *__restrict__ W,
@@ -607,6 +662,17 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void dgrad_bf16_group_kernel(Dgra
 
 // ---------------------------------------------------------- host launchers
 
+// Workgroup ids for a layer: `tiles` tiles if all rows are kept, and where the last round may go out as quarters the ids
+// that these add (4 tail - tail, 193 at most at 63 tiles).  A whole round holds the quarters: without zero-fill duty
+// behind them rounding up is enough.
+template <int BM>
+static int64_t dgrad_grid(int64_t tiles, int tiles_n, bool fill, int K_out)
+{
+    if (BM == 256 && K_out >= kTailContraction) tiles = fill ? tiles + 200 : (tiles + kTailCUs - 1) / kTailCUs * kTailCUs;
+    // without zero-fill duty the ids past the compute tiles have nothing to do
+    return tiles + (fill ? tiles_n : 0) + 8;
+}
+
 template <int BM, int BN, int WM, int WN, int NS, int OCC, int SPQ>
 static vcas_status launch_dgrad(const vcas_shape &s, const void *G, const void *W, const float *p,
                                 const int32_t *idxA, const int32_t *cntA, void *dX, const void *J, bool fill,
@@ -614,8 +680,7 @@ static vcas_status launch_dgrad(const vcas_shape &s, const void *G, const void *
 {
     const int64_t R = (int64_t)s.N * s.T;
     const int tiles_n = (s.K_in + BN - 1) / BN;
-    // without zero-fill duty the ids past the compute tiles have nothing to do
-    const int64_t grid = tiles_n * ((R + BM - 1) / BM + (fill ? 1 : 0)) + 8;
+    const int64_t grid = dgrad_grid<BM>((R + BM - 1) / BM * tiles_n, tiles_n, fill, s.K_out);
     if (grid > (int64_t)1 << 30) return VCAS_EINVAL;
     const size_t lds = NS * (BM + BN) * 128 + BM * 8;
     auto kern = dgrad_bf16_kernel<BM, BN, WM, WN, NS, OCC, SPQ>;

@@ -93,3 +93,40 @@ def test_fp32_tensors_beyond_32_bit_offsets(vb):
     t = tokens.long()
     want = (G[t].double() * scale[t].double()[:, None]).t() @ X[t].double()
     assert float((dW.double() - want).norm() / want.norm()) <= 1e-5
+
+
+# 256x256 tiles of dgrad with the last round's tiles cut into quarters: whole tiles and quarters (287 = 256 + 31 tiles,
+# 256 + 24), quarters only (28 and 63 tiles: one to a workgroup; 126: two), none kept, too many for quarters (189), a contraction too short for them; ragged in rows,
+# columns and contraction
+@pytest.mark.parametrize("K_out,kept", [(1544, 40), (1544, 39), (1544, 3), (1544, 8), (1544, 17),
+                                        (1544, 0), (1544, 27), (1536, 40), (1528, 40)])
+def test_dgrad_last_round_in_quarters(vb, K_out, kept):
+    N, T, K_in = 40, 257, 1608
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(K_out + kept)
+    G = torch.randn((R, K_out), generator=gen, device="cuda").bfloat16()
+    W = (torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02).bfloat16()
+    J = torch.rand((R, K_in), generator=gen, device="cuda").bfloat16()
+    p = torch.rand(N, generator=gen, device="cuda") * 0.5 + 0.5
+    chosen = torch.randperm(N, generator=gen, device="cuda")[:kept].sort().values
+    idxA = torch.zeros(N, dtype=torch.int32, device="cuda")
+    idxA[:kept] = chosen.int()
+    cntA = torch.tensor([kept], dtype=torch.int32, device="cuda")
+    dX = torch.full((R, K_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    blocks = torch.zeros(vb.vcas_sq_blocks_bytes(R, K_in) // 4, device="cuda")
+    vb.vcas_sampled_dgrad_norms(shape, G, W, p, idxA, cntA, J, dX, blocks)
+    mask = torch.zeros(N, device="cuda")
+    mask[chosen] = 1.0 / p[chosen]
+    want = (G.double() @ W.double()) * mask.double().repeat_interleave(T)[:, None] * J.double()
+    got = dX.double()
+    assert bool(torch.isfinite(got).all())
+    dropped = mask.repeat_interleave(T) == 0
+    assert float(got[dropped].abs().sum()) == 0.0
+    if kept:
+        # fp32 sums rounded once to bf16: 2^-9 / sqrt(3) = 1.1e-3; a row or a 64-column block alike
+        off = (got - want)[~dropped]
+        assert float((off.norm(dim=1) / want[~dropped].norm(dim=1)).max()) <= 5e-3
+        assert float((off.norm(dim=0) / want[~dropped].norm(dim=0)).max()) <= 5e-3
+        rows = blocks.view(-1, R, 4).permute(1, 0, 2).reshape(R, -1)[:, :(K_in + 63) // 64].double().sum(1)
+        assert float(((rows - (got * got).sum(1)).abs() / (got * got).sum(1).clamp_min(1e-30))[~dropped].max()) <= 1e-5
