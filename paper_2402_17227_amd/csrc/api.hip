@@ -193,9 +193,15 @@ static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const
         q.splits = 1;
         return wgrad_gather(&q, 1, VCAS_BF16, form == kGatherLarge, false, st);
     }
-    const int tile = wgrad_tile_choice(wgrad_tiles_bf16(s.K_out, s.K_in, 256), wgrad_tiles_bf16(s.K_out, s.K_in, 128), fill);
+    // On its own a layer of 192 to 256 tiles of 256x256 has one for nearly every CU, and no second round.  4096x4096, packing
+    // and sampling included, against 1024 tiles of 128x128: 2000 tokens 97 and 105 us, 8200 291 and 323, 16384 522 and
+    // 635.  Fewer such tiles in slices gain nothing below 8192 tokens a slice (1024x4096, four slices: 4100 tokens 80
+    // and 76 us, 16384 175 and 172), more of them fill a second round badly.
+    const int tiles256 = wgrad_tiles_bf16(s.K_out, s.K_in, 256);
+    const bool one_each = fill == kWgradFill && tiles256 >= 192 && tiles256 <= 256;
+    const int tile = one_each ? 256 : wgrad_tile_choice(tiles256, wgrad_tiles_bf16(s.K_out, s.K_in, 128), fill);
     WgradItem it = wgrad_item(s, G, X, scale, idxW, cntW, dW, partials, packed);
-    it.splits = wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), fill);
+    it.splits = one_each ? 1 : wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), fill);
     return wgrad_bf16_batch(&it, 1, tile, st);
 }
 

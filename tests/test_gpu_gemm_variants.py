@@ -45,6 +45,8 @@ BF16_CASES = [
     (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1024, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
     # 128x128 tiles, ragged, either side scaled; beyond them the packed form
     (3, 67, 1096, 1160, 0.7, 0.7), (3, 67, 1160, 1096, 0.7, 0.7), (8, 257, 1096, 1160, 1.0, 0.9),
+    # packed, 256x256 tiles: 15 x 15 of them on a layer's own; below 192 and beyond 256 of them (13 x 14, 17 x 16) as before
+    (1, 300, 3592, 3688, 1.0, 1.0), (2, 200, 3688, 3592, 1.0, 0.8), (2, 300, 3464, 3208, 1.0, 0.9), (2, 300, 3848, 4104, 1.0, 0.9),
 ]
 
 
