@@ -203,24 +203,25 @@ __global__ __launch_bounds__(256) void rows_from_blocks_kernel(const float4 *__r
 // The same for a stack whose dgrad decides SampleA itself: row sums, and of the sample norms what is left when
 // the rows are summed, the 64 lane sums of sample_norm_wave (lane l adds the rows t = l mod 64 of its
 // sample in ascending t); the tree over the lanes and the root are left to the reader.  A sample is
-// cut by lanes, eight to a workgroup, so that N samples are 8 N workgroups and nothing is exchanged
+// cut by lanes, L to a workgroup, so that N samples are 64/L N workgroups and nothing is exchanged
 // between them: with one workgroup per sample (an earlier version) a CU has to pull a whole sample's
 // block sums (128 KiB at T = 512, K = 4096) through its L1, 15-19 us.
+template <int L>
 __global__ __launch_bounds__(256) void lane_sums_from_blocks_kernel(const float4 *__restrict__ blocks4, int64_t R, int nb,
                                                                     int T, const uint8_t *__restrict__ sample_keep,
                                                                     RowsFromBlocks outs, int n_out, float *__restrict__ lanes)
 {
     __shared__ float part_sum[256];
-    const int i = blockIdx.x, lane0 = blockIdx.y * 8, tid = threadIdx.x;
+    const int i = blockIdx.x, lane0 = blockIdx.y * L, tid = threadIdx.x;
     const bool live = !sample_keep || sample_keep[i] != 0;
     const int groups = (nb + 3) >> 2;
     int Gp = 1;
     while (Gp < groups) Gp *= 2;
     const int parts = Gp < 4 ? Gp : 4, chunk = Gp / parts;   // threads per row, groups per thread: a subtree each
-    const int r = tid & 63, part = tid >> 6;                 // 64 rows at a time: lanes lane0 .. lane0 + 7, eight values of t / 64
-    float acc = 0.0f;                                        // of lane lane0 + tid, tid < 8
-    for (int k0 = 0; 64 * k0 < T; k0 += 8) {
-        const int t = lane0 + (r & 7) + 64 * (k0 + (r >> 3));
+    const int r = tid & 63, part = tid >> 6;                 // 64 rows at a time: lanes lane0 .. lane0 + L - 1, 64/L values of t / 64
+    float acc = 0.0f;                                        // of lane lane0 + tid, tid < L
+    for (int k0 = 0; 64 * k0 < T; k0 += 64 / L) {
+        const int t = lane0 + r % L + 64 * (k0 + r / L);
         const int64_t row = (int64_t)i * T + t;
         float sum = 0.0f;
         if (live && t < T && part < parts && part * chunk < groups)
@@ -235,13 +236,13 @@ __global__ __launch_bounds__(256) void lane_sums_from_blocks_kernel(const float4
             part_sum[tid] = total;
         }
         __syncthreads();
-        if (tid < 8)
+        if (tid < L)
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (lane0 + tid + 64 * (k0 + k) < T) acc = acc + part_sum[tid + 8 * k];
+            for (int k = 0; k < 64 / L; ++k)
+                if (lane0 + tid + 64 * (k0 + k) < T) acc = acc + part_sum[tid + L * k];
         __syncthreads();
     }
-    if (tid < 8) lanes[i * 64 + lane0 + tid] = acc;
+    if (tid < L) lanes[i * 64 + lane0 + tid] = acc;
 }
 
 // outs: n_out <= kMaxSiblings arrays of R floats
@@ -263,7 +264,11 @@ vcas_status lane_sums_from_blocks(const float *blocks, int N, int T, int K, cons
     if (n_out < 1 || n_out > kMaxSiblings) return VCAS_EINVAL;
     RowsFromBlocks o = {};
     for (int k = 0; k < n_out; ++k) o.out[k] = outs[k];
-    hipLaunchKernelGGL(lane_sums_from_blocks_kernel, dim3((unsigned)N, 8), dim3(256), 0, st,
+    // Lanes per workgroup so that its rows (L ceil(T/64)) are the 64 of one trip: a second trip waits for memory and three
+    // barriers again.  T = 1024, 16 samples, K = 1024 and 4096, two blocks with eight such passes on the chain: 994 us
+    // with eight lanes and two trips, 956 with four and one.
+    auto kern = T > 512 ? lane_sums_from_blocks_kernel<4> : lane_sums_from_blocks_kernel<8>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)N, T > 512 ? 16 : 8), dim3(256), 0, st,
                        reinterpret_cast<const float4 *>(blocks), (int64_t)N * T, (K + 63) / 64, T, keep, o, n_out, lanes);
     return launch_status();
 }

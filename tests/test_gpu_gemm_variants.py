@@ -45,6 +45,9 @@ BF16_CASES = [
     (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1024, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
     # 128x128 tiles, ragged, either side scaled; beyond them the packed form
     (3, 67, 1096, 1160, 0.7, 0.7), (3, 67, 1160, 1096, 0.7, 0.7), (8, 257, 1096, 1160, 1.0, 0.9),
+    # gathering over whole, partial and single steps of 64 tokens, with both tiles; 17 x 17 tiles
+    (1, 64, 264, 264, 1.0, 1.0), (1, 65, 264, 264, 1.0, 1.0), (1, 200, 264, 264, 1.0, 1.0), (1, 257, 264, 264, 1.0, 1.0),
+    (1, 513, 264, 264, 1.0, 1.0), (1, 129, 1096, 1160, 1.0, 1.0), (1, 321, 1096, 1160, 1.0, 1.0), (3, 67, 2056, 2120, 0.7, 0.7),
     # packed, 256x256 tiles: 15 x 15 of them on a layer's own; below 192 and beyond 256 of them (13 x 14, 17 x 16) as before
     (1, 300, 3592, 3688, 1.0, 1.0), (2, 200, 3688, 3592, 1.0, 0.8), (2, 300, 3464, 3208, 1.0, 0.9), (2, 300, 3848, 4104, 1.0, 0.9),
 ]
@@ -98,8 +101,8 @@ def test_fp32_tensors_beyond_32_bit_offsets(vb):
 
 
 # 256x256 tiles of dgrad with the last round's tiles cut into quarters: whole tiles and quarters (287 = 256 + 31 tiles,
-# 256 + 24), quarters only (28 and 63 tiles: one to a workgroup; 126: two), none kept, too many for quarters (189), a contraction too short for them; ragged in rows,
-# columns and contraction
+# 256 + 24), quarters only (28 and 63 tiles: one to a workgroup; 126: two), none kept, too many for quarters (196), a
+# contraction too short for them; ragged in rows, columns and contraction
 @pytest.mark.parametrize("K_out,kept", [(1544, 40), (1544, 39), (1544, 3), (1544, 8), (1544, 17),
                                         (1544, 0), (1544, 27), (1536, 40), (1528, 40)])
 def test_dgrad_last_round_in_quarters(vb, K_out, kept):
