@@ -510,12 +510,12 @@ static vcas_status data_half_siblings(const vcas_layer_args *layers, int n, hipS
     return dgrad_bf16_group(s, probs, n, layers[0].leave_dropped_rows == 0, (int64_t)((double)R * rho_max + 0.5), st);
 }
 
-// Can layer b share the launches that precede the weight gradients with layer a?  All they need is one number
-// of rows, samples and bytes per element, and the same kind of token sampling.
+// Can layer b share the launches that precede the weight gradients with layer a?  Siblings of one shape and kind of
+// token sampling only: layers of any widths could, but one pass over the X of a whole group takes the CUs from the
+// dgrad chain for longer (144 layers of 1024/4096, 16384 rows: step 11.76 -> 12.5 ms).
 static bool shares_weight_half(const vcas_layer_args &a, const vcas_layer_args &b)
 {
-    return a.shape.N == b.shape.N && a.shape.T == b.shape.T && a.shape.dtype == b.shape.dtype &&
-           (a.token_sampling != 0) == (b.token_sampling != 0);
+    return b.sibling != 0 && same_shape(a.shape, b.shape) && (a.token_sampling != 0) == (b.token_sampling != 0);
 }
 
 // What weight_half does before dW, for n layers (shares_weight_half) whose data halves left the norms of X
@@ -597,31 +597,6 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
         l = next;
     }
     return VCAS_OK;
-}
-
-// Fills in dx_sq_blocks and g_sq_blocks of the entries that feed each other, where the caller has not:
-// the entry that wrote G last has the same rows, leaves its block sums somewhere, and which rows of G
-// exist at all is known from its maskA (the caller says so, or the others are zeros, which count as +0).
-static void link_norms(vcas_layer_args *layers, int L)
-{
-    for (int l = 1; l < L; ++l) {
-        vcas_layer_args &a = layers[l];
-        if (a.g_sq_blocks || a.shape.dtype != VCAS_BF16) continue;
-        int p = l - 1;
-        while (p >= 0 && layers[p].dX != a.G) --p;
-        if (p < 0) continue;
-        vcas_layer_args &b = layers[p];
-        if (b.shape.dtype != VCAS_BF16 || b.shape.N != a.shape.N || b.shape.T != a.shape.T || b.shape.K_in != a.shape.K_out) continue;
-        const uint8_t *keep = a.kept_above ? a.kept_above : b.leave_dropped_rows ? nullptr : b.plan.maskA;
-        if (keep != b.plan.maskA) continue;
-        if (!b.dx_sq_blocks) {
-            const WorkspaceLayout w = workspace_layout(&b.shape);
-            if (vcas_sq_blocks_bytes((int64_t)b.shape.N * b.shape.T, b.shape.K_in) > w.probe_acc - w.probe_exact) continue;
-            b.dx_sq_blocks = reinterpret_cast<float *>(static_cast<unsigned char *>(b.workspace) + w.probe_exact);
-        }
-        a.kept_above = keep;
-        a.g_sq_blocks = b.dx_sq_blocks;
-    }
 }
 
 static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, const void *X, const void *W, double rho,
@@ -1024,16 +999,6 @@ vcas_status vcas_backward_stack(const vcas_layer_args *layers, int32_t L, int32_
         if (!aligned16(a.G) || !aligned16(a.X) || (a.W && !aligned16(a.W)) || (a.dX && !aligned16(a.dX)) ||
             (a.dW && !aligned16(a.dW)) || !aligned16(a.workspace))
             return VCAS_EINVAL;
-    }
-    // Entries whose G is the dX of an entry before them take its norms from the launch that writes it: the
-    // block sums go to the producer's workspace (where only the variance probe keeps anything).  A sweep over
-    // G, 5 to 20 us each, and where R > 4096 the SampleA launch, leave the chain of the data halves for a
-    // 3 us pass over the block sums.
-    std::vector<vcas_layer_args> linked;
-    if (s2 != st) {
-        linked.assign(layers, layers + L);
-        link_norms(linked.data(), L);
-        layers = linked.data();
     }
     // Groups of `group` layers; the last ones shrink (half of what is left), so that the side
     // streams are not a whole group behind when the main stream reaches the end of the stack.
