@@ -265,7 +265,7 @@ vcas_status lane_sums_from_blocks(const float *blocks, int N, int T, int K, cons
     RowsFromBlocks o = {};
     for (int k = 0; k < n_out; ++k) o.out[k] = outs[k];
     // Lanes per workgroup so that its rows (L ceil(T/64)) are the 64 of one trip: a second trip waits for memory and three
-    // barriers again.  T = 1024, 16 samples, K = 1024 and 4096, two blocks with eight such passes on the chain: 994 us
+    // barriers again.  T = 1024, 16 samples, K = 1024 and 4096, two chained blocks with eight such passes: 994 us
     // with eight lanes and two trips, 956 with four and one.
     auto kern = T > 512 ? lane_sums_from_blocks_kernel<4> : lane_sums_from_blocks_kernel<8>;
     hipLaunchKernelGGL(kern, dim3((unsigned)N, T > 512 ? 16 : 8), dim3(256), 0, st,
