@@ -63,7 +63,11 @@ __device__ __forceinline__ void dgrad_bf16_tile(const uint16_t *__restrict__ G, 
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int AI = BM / (8 * NW), BI = BN / (8 * NW);     // LDS-direct loads per wavefront and step
     constexpr int B_ROWS = 512 / BN, B_SLOTS = BN / 8;         // k rows per W load, 16-byte slots per W row
-    constexpr int STAGE = (BM + BN) * 128, B_AT = BM * 128, B_PITCH = BN * 2;
+    // The stages of G lie in front of those of W, so that a stage is a constant within the 64 KiB that an LDS instruction
+    // adds to its address register, and all stages share the registers.  The 256x256 tile then takes 217 VGPRs; with G and W
+    // of a stage side by side, 64 KiB apart, it took 251, two wavefronts filled a SIMD, and the norm passes of a
+    // stack's other streams waited for it to end (four chained layers of 1024x1024, 16 samples of 1024 rows: 315 and 302 us).
+    constexpr int STAGE = (BM + BN) * 128, A_STAGE = BM * 128, B_STAGE = BN * 128, B_AT = NS * A_STAGE, B_PITCH = BN * 2;
     constexpr int LOADS = AI + BI;
     static_assert(AI >= 1 && BI >= 1 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/wave mismatch");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -110,8 +114,8 @@ __device__ __forceinline__ void dgrad_bf16_tile(const uint16_t *__restrict__ G, 
     const int tail_pieces = (K_out - (steps - 1) * BK + 7) / 8;
     // the d-th of the LOADS loads of contraction step `step` into stage `stage`: G and W pieces alternate
     auto issue_nth = [&](int d, int stage, int step) {
-        const uint32_t a_dst = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * AI * 1024);
-        const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + B_AT + wave * BI * 1024);
+        const uint32_t a_dst = __builtin_amdgcn_readfirstlane(lds0 + stage * A_STAGE + wave * AI * 1024);
+        const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds0 + B_AT + stage * B_STAGE + wave * BI * 1024);
         const uint32_t kb = __builtin_amdgcn_readfirstlane(step * BK * 2);
         const uint32_t wb = __builtin_amdgcn_readfirstlane(step * BK * K_in * 2);
         const int pieces = step == steps - 1 ? tail_pieces : 8;
@@ -138,12 +142,12 @@ __device__ __forceinline__ void dgrad_bf16_tile(const uint16_t *__restrict__ G, 
     const uint32_t a_lds = __builtin_amdgcn_readfirstlane(lds0 + wave * AI * 1024);
     const uint32_t b_lds = __builtin_amdgcn_readfirstlane(lds0 + B_AT + wave * BI * 1024);
     auto issue_whole = [&](auto stage_, auto d_, uint32_t kb, uint32_t wb) {
-        constexpr int d = decltype(d_)::value, AT = decltype(stage_)::value * STAGE, LO = AI < BI ? AI : BI;
+        constexpr int d = decltype(d_)::value, stage = decltype(stage_)::value, LO = AI < BI ? AI : BI;
         // G and W alternate while both have loads left, then the rest of the longer one
         constexpr bool of_g = d < 2 * LO ? d % 2 == 0 : AI > BI;
         constexpr int j = d < 2 * LO ? d / 2 : d - LO;
-        if constexpr (of_g) lds_direct_load16_at<AT + j * 1024>(descG, a_lds, a_off[j], kb);
-        else lds_direct_load16_at<AT + j * 1024>(descW, b_lds, b_off[j], wb);
+        if constexpr (of_g) lds_direct_load16_at<stage * A_STAGE + j * 1024>(descG, a_lds, a_off[j], kb);
+        else lds_direct_load16_at<stage * B_STAGE + j * 1024>(descW, b_lds, b_off[j], wb);
     };
     const uint32_t w_step = (uint32_t)BK * K_in * 2;   // bytes from a step of W to the next (of G: 2 BK)
     const int whole = steps - (tail_pieces < 8 ? 1 : 0);   // steps that fetch all of their 16-byte pieces
@@ -151,12 +155,17 @@ __device__ __forceinline__ void dgrad_bf16_tile(const uint16_t *__restrict__ G, 
     const int r32 = lane & 31, h = lane >> 5;
     const int blk = lane >> 4, sl = lane & 15;    // 16-lane block and lane within it
     const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
+    // Byte offsets of a lane's piece of G at each k-slice, rows wm0 + r32: 64 rows on they are the same; 32 rows on the
+    // XOR flips bit 2 of the slot, which is the piece of slice ks ^ 2.
+    uint32_t a_at[BK / 16];
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) a_at[ks] = lds_off(wm0 + r32, ks * 2 + h);
     auto read_slice = [&](int stage, int ks, bf16x8(&fa)[TM], bf16x8(&fb)[TN]) {
-        const unsigned char *tileA = smem + stage * STAGE;
-        const unsigned char *tileB = tileA + B_AT;
+        const unsigned char *tileA = smem + stage * A_STAGE;
+        const unsigned char *tileB = smem + B_AT + stage * B_STAGE;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            fa[i] = *reinterpret_cast<const bf16x8 *>(tileA + lds_off(wm0 + i * 32 + r32, ks * 2 + h));
+            fa[i] = *reinterpret_cast<const bf16x8 *>(tileA + a_at[(i & 1) ? ks ^ 2 : ks] + i * 4096);
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
             bf16x4 half[2];
@@ -509,12 +518,12 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
 {
     constexpr int NW = WM * WN, NT = NW * 64, STAGE = (BM + BN) * 128;
     constexpr bool kTail = BM == 256;   // one workgroup per CU
-    static_assert(STAGE >= kIdxStaged * 4, "index staging area does not fit a stage");
+    static_assert(BM * 128 >= kIdxStaged * 4, "index staging area does not fit a stage of G");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int32_t *row_of = reinterpret_cast<int32_t *>(smem + NS * STAGE);
     // The last stage is not loaded before the first barrier of the main loop; until then it
     // holds the kept-sample list, fetched together with the count instead of after it.
-    int32_t *idx_staged = reinterpret_cast<int32_t *>(smem + (NS - 1) * STAGE);
+    int32_t *idx_staged = reinterpret_cast<int32_t *>(smem + (NS - 1) * BM * 128);
     const int staged = min(N, kIdxStaged);
     __shared__ float sa_norm[64], sa_p[64];
     __shared__ int32_t sa_idx[64];
