@@ -149,17 +149,25 @@ static WgradItem wgrad_item(const vcas_shape &s, const void *G, const void *X, c
 // Where the weight gradient of a bf16 layer on its own is computed, by the tokens it is expected to keep
 // (0: unknown, any of the R).  The gathering kernel is ONE launch that multiplies the token scales into its
 // fragments; the packed form takes two or three (pack, GEMM, reduction of slices), 4 to 6 us each however
-// short the contraction.  64x64 tiles while every CU can have one at once, 128x128 tiles beyond.  Alone on the
-// chip, gathering against packed: 264x136 with 56 tokens 9 and 13 us; 768x768 with 1891 tokens 22 and 26
-// (3782: 39 and 29); 1024x1024 with 1638 tokens 21 and 27; 768x3072 with 1024 tokens 24 and 28 (3072x768 with
-// 1891 tokens: 36 and 30); 3704x3456 with 96 tokens 20 and 24.
+// short the contraction, but cuts a long contraction into slices where the gathering kernel walks it in one
+// workgroup per tile.  So the line rises with the tiles that fill the chip without slices.  64x64 tiles while
+// every CU can have one at once, gathering against packed in us (replayed from a graph):
+//   tiles      512 tokens    768         1024        1280        1536        2048
+//     16       8.9  10.2   11.1  10.5  13.3  10.8  15.7  11.1  18.0  11.3  22.5  12.0
+//     32       8.9  10.8   11.2  11.3  13.4  11.9  15.8  12.1  18.1  12.5  22.6  13.0
+//     64       9.0  13.9   11.3  15.1  13.5  16.7  16.1  16.6  18.2  17.6  22.6  18.5
+//     96       9.1  15.4   11.4  17.4  13.6  18.4  16.2  18.1  18.3  19.1  22.7  20.1
+//    144       9.3  17.6   11.6  20.2  13.8  24.4  16.5  23.6  18.6  25.4  23.1  26.4  (3072: 32.2 and 28.2)
+//    256       9.8  22.5   12.1  27.1  14.5  26.9  17.3  26.7  19.8  27.4  24.1  27.3  (3072: 34.2 and 28.3)
+// 128x128 tiles beyond: 81 tiles 24.6 and 25.5 at 1024 tokens, 29.4 and 27.6 at 1280; 144 tiles 25.3 and 27.6, 30.1
+// and 28.1; 576 tiles 22.1 and 24.3 at 256 tokens, 30.5 and 31.4 at 512, 39.5 and 37.7 at 768.
 enum WgradForm { kPacked, kGatherSmall, kGatherLarge };
 static WgradForm wgrad_form(const vcas_shape &s, int64_t tokens)
 {
     if (tokens <= 0 || !offsets_fit(s)) return kPacked;
     const int64_t small = gather_tiles(VCAS_BF16, s.K_out, s.K_in, false), large = gather_tiles(VCAS_BF16, s.K_out, s.K_in, true);
-    if (small <= 256) return tokens <= (small < 32 ? 1024 : 2048) ? kGatherSmall : kPacked;
-    return large * (tokens < 64 ? 64 : tokens) <= 160 * 1024 ? kGatherLarge : kPacked;
+    if (small <= 256) return tokens <= 2048 && tokens <= 400 + 12 * small ? kGatherSmall : kPacked;
+    return tokens <= 1024 && large * (tokens < 64 ? 64 : tokens) <= 160 * 1024 ? kGatherLarge : kPacked;
 }
 static int64_t expected_tokens(const vcas_shape &s, double rho, double nu, int token_sampling)
 {

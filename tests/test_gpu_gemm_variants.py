@@ -135,3 +135,27 @@ def test_dgrad_last_round_in_quarters(vb, K_out, kept):
         assert float((off.norm(dim=0) / want[~dropped].norm(dim=0)).max()) <= 5e-3
         rows = blocks.view(-1, R, 4).permute(1, 0, 2).reshape(R, -1)[:, :(K_in + 63) // 64].double().sum(1)
         assert float(((rows - (got * got).sum(1)).abs() / (got * got).sum(1).clamp_min(1e-30))[~dropped].max()) <= 1e-5
+
+
+# On both sides of the lines between the two forms of a small weight gradient: 64x64 tiles by their number (16, 32, 64,
+# 144 of them), 128x128 tiles (81).  vcas_sampled_wgrad, which knows no expected count, always takes the packed form: its
+# bits are those of the same form, and the gathering kernel adds in another order.
+@pytest.mark.parametrize("K_in,K_out,tokens,packed", [
+    (256, 256, 512, False), (256, 256, 1024, True), (512, 256, 768, False), (512, 256, 1280, True),
+    (512, 512, 1024, False), (512, 512, 1536, True), (768, 768, 2048, False), (768, 768, 2056, True),
+    (1096, 1032, 1024, False), (1096, 1032, 1280, True)])
+def test_form_of_a_small_weight_gradient(vb, K_in, K_out, tokens, packed):
+    N, T = 8, tokens // 8
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(tokens)
+    G = torch.randn((tokens, K_out), generator=gen, device="cuda").bfloat16()
+    X = torch.randn((tokens, K_in), generator=gen, device="cuda").bfloat16()
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    dW = torch.full((K_out, K_in), float("nan"), device="cuda")
+    vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(3, 1, 0), True, plan, None, dW, ws)
+    other = torch.full((K_out, K_in), float("nan"), device="cuda")
+    vb.vcas_sampled_wgrad(shape, G, X, plan.scaleW, plan.idxW, plan.cntW, other, ws)
+    want = G.double().t() @ X.double()
+    # fp32 sums of exact products, in any order: sqrt(2048) 2^-24 = 3e-6
+    assert float((dW.double() - want).norm() / want.norm()) <= 1e-5 and float((other.double() - want).norm() / want.norm()) <= 1e-5
+    assert torch.equal(dW, other) == packed
