@@ -175,6 +175,25 @@ static int64_t expected_tokens(const vcas_shape &s, double rho, double nu, int t
     return t < 1 ? 1 : t;
 }
 
+// One layer of a gathering launch, unsliced.
+static GatherTask gather_task(const vcas_shape &s, const void *G, const void *X, const float *scale, const int32_t *idxW,
+                              const int32_t *cntW, float *dW)
+{
+    GatherTask q = {};
+    q.G = G;
+    q.X = X;
+    q.row_scale = scale;
+    q.idx = idxW;
+    q.cnt = cntW;
+    q.dst = dW;
+    q.R = (int32_t)((int64_t)s.N * s.T);
+    q.K_in = s.K_in;
+    q.K_out = s.K_out;
+    q.scale_g = s.K_out < s.K_in;   // the narrower operand, as in the packed form
+    q.splits = 1;
+    return q;
+}
+
 // One layer on its own.  partials: room for wgrad_split(s) partial tiles; packed (bf16): room for
 // R rows of the narrower operand.
 static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const void *X, const float *scale,
@@ -187,18 +206,7 @@ static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const
                          fill, st);
     const WgradForm form = wgrad_form(s, tokens);
     if (form != kPacked) {
-        GatherTask q = {};
-        q.G = G;
-        q.X = X;
-        q.row_scale = scale;
-        q.idx = idxW;
-        q.cnt = cntW;
-        q.dst = dW;
-        q.R = (int32_t)((int64_t)s.N * s.T);
-        q.K_in = s.K_in;
-        q.K_out = s.K_out;
-        q.scale_g = s.K_out < s.K_in;   // the narrower operand, as in the packed form
-        q.splits = 1;
+        GatherTask q = gather_task(s, G, X, scale, idxW, cntW, dW);
         return wgrad_gather(&q, 1, VCAS_BF16, form == kGatherLarge, false, st);
     }
     // On its own a layer of 192 to 256 tiles of 256x256 has one for nearly every CU, and no second round.  4096x4096, packing
@@ -543,11 +551,12 @@ static vcas_status weight_half_group(const vcas_layer_args *layers, int n, hipSt
     return sampler_w_group(samplers, n, 0, s.N, s.T, layers[0].token_sampling, 2, st);
 }
 
-// Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched launches unless a
-// call on its own would gather, fp32 layers one by one).  A layer with wgrad_fill == 0 gets the tile and the slices a
-// call on its own would pick, hence that call's bits; the others are planned per launch: the
-// tiles of every layer of the batch count towards `fill`, so a block's weight gradients fill the
-// chip together and are rarely sliced at all.
+// Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched launches, fp32 layers
+// one by one).  A layer with wgrad_fill == 0 gets the form, the tile and the slices a call on its own would
+// pick, hence that call's bits; the others are planned per launch: the tiles of every layer of the batch
+// count towards `fill`, so a block's weight gradients fill the chip together and are rarely sliced at all.
+// Layers that gather with one tile size share a launch too: one by one, each left most CUs empty (four layers of
+// 768x768 and 2048 tokens are 144 workgroups each).
 static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1, hipStream_t st)
 {
     for (int l = l0; l < l1;) {
@@ -556,16 +565,27 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
             ++l;
             continue;
         }
-        // fp32, or as a call on its own would gather
-        auto own = [](const vcas_layer_args &b) { return b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill; };
-        auto by_itself = [&](const vcas_layer_args &b) {
-            return b.shape.dtype != VCAS_BF16 ||
-                   (own(b) && wgrad_form(b.shape, expected_tokens(b.shape, b.rho, b.nu, b.token_sampling)) != kPacked);
-        };
-        if (by_itself(a)) {
-            VCAS_TRY(dispatch_wgrad(a.shape, a.G, a.X, a.plan.scaleW, a.plan.idxW, a.plan.cntW, a.dW, a.workspace, st,
-                                    a.wgrad_fill, expected_tokens(a.shape, a.rho, a.nu, a.token_sampling)));
+        if (a.shape.dtype != VCAS_BF16) {
+            VCAS_TRY(dispatch_wgrad(a.shape, a.G, a.X, a.plan.scaleW, a.plan.idxW, a.plan.cntW, a.dW, a.workspace, st, a.wgrad_fill));
             ++l;
+            continue;
+        }
+        // fp32 has no forms: kPacked stands for "not in this run" there
+        auto own = [](const vcas_layer_args &b) { return b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill; };
+        auto form_of = [&](const vcas_layer_args &b) {
+            return b.shape.dtype == VCAS_BF16 && own(b) ? wgrad_form(b.shape, expected_tokens(b.shape, b.rho, b.nu, b.token_sampling)) : kPacked;
+        };
+        const WgradForm form = form_of(a);
+        if (form != kPacked) {
+            GatherTask tasks[kGatherBatch];
+            int n = 0;
+            for (; l < l1 && n < kGatherBatch; ++l) {
+                const vcas_layer_args &b = layers[l];
+                if (!b.dW) continue;
+                if (form_of(b) != form) break;
+                tasks[n++] = gather_task(b.shape, b.G, b.X, b.plan.scaleW, b.plan.idxW, b.plan.cntW, b.dW);
+            }
+            VCAS_TRY(wgrad_gather(tasks, n, VCAS_BF16, form == kGatherLarge, false, st));
             continue;
         }
         // a run of bf16 layers that plan their launch the same way
@@ -575,7 +595,7 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
         for (; next < l1 && n < kWgradBatch; ++next) {
             const vcas_layer_args &b = layers[next];
             if (!b.dW) continue;
-            if (by_itself(b) || own(b) != alone) break;
+            if (b.shape.dtype != VCAS_BF16 || own(b) != alone || form_of(b) != kPacked) break;
             const int t256 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 256), t128 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 128);
             if (alone && n > 0 &&
                 wgrad_tile_choice(t256, t128, kWgradFill) !=
