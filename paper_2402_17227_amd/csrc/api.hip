@@ -127,6 +127,19 @@ static int wgrad_slices_bf16(const vcas_shape &s, int launch_tiles, int fill)
     return want < 1 ? 1 : (int)want;
 }
 
+// Tile edge and slices of a bf16 layer whose launch is planned for it alone.  192 to 256 tiles of 256x256 are one for nearly
+// every CU, and no second round.  4096x4096, packing and sampling included, against 1024 tiles of 128x128: 2000 tokens 97
+// and 105 us, 8200 291 and 323, 16384 522 and 635.  Fewer such tiles in slices gain nothing below 8192 tokens a slice
+// (1024x4096, four slices: 4100 tokens 80 and 76 us, 16384 175 and 172), more of them fill a second round badly.
+static int own_tile(const vcas_shape &s, int &splits)
+{
+    const int tiles256 = wgrad_tiles_bf16(s.K_out, s.K_in, 256);
+    const bool one_each = tiles256 >= 192 && tiles256 <= 256;
+    const int tile = one_each ? 256 : wgrad_tile_choice(tiles256, wgrad_tiles_bf16(s.K_out, s.K_in, 128), kWgradFill);
+    splits = one_each ? 1 : wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), kWgradFill);
+    return tile;
+}
+
 static int fill_or_default(int fill) { return fill <= 0 || fill > kWgradFill ? kWgradFill : fill; }
 
 static WgradItem wgrad_item(const vcas_shape &s, const void *G, const void *X, const float *scale, const int32_t *idxW,
@@ -200,24 +213,20 @@ static vcas_status dispatch_wgrad_into(const vcas_shape &s, const void *G, const
                                        const int32_t *idxW, const int32_t *cntW, float *dW, float *partials,
                                        uint16_t *packed, hipStream_t st, int fill, int64_t tokens)
 {
-    fill = fill_or_default(fill);
-    if (s.dtype != VCAS_BF16)
+    if (s.dtype != VCAS_BF16) {
+        fill = fill_or_default(fill);
         return wgrad_f32(s, G, X, scale, idxW, cntW, dW, partials, wgrad_split_for(&s, wgrad_tiles_f32(s.K_out, s.K_in), fill),
                          fill, st);
+    }
     const WgradForm form = wgrad_form(s, tokens);
     if (form != kPacked) {
         GatherTask q = gather_task(s, G, X, scale, idxW, cntW, dW);
         return wgrad_gather(&q, 1, VCAS_BF16, form == kGatherLarge, false, st);
     }
-    // On its own a layer of 192 to 256 tiles of 256x256 has one for nearly every CU, and no second round.  4096x4096, packing
-    // and sampling included, against 1024 tiles of 128x128: 2000 tokens 97 and 105 us, 8200 291 and 323, 16384 522 and
-    // 635.  Fewer such tiles in slices gain nothing below 8192 tokens a slice (1024x4096, four slices: 4100 tokens 80
-    // and 76 us, 16384 175 and 172), more of them fill a second round badly.
-    const int tiles256 = wgrad_tiles_bf16(s.K_out, s.K_in, 256);
-    const bool one_each = fill == kWgradFill && tiles256 >= 192 && tiles256 <= 256;
-    const int tile = one_each ? 256 : wgrad_tile_choice(tiles256, wgrad_tiles_bf16(s.K_out, s.K_in, 128), fill);
+    int splits;
+    const int tile = own_tile(s, splits);
     WgradItem it = wgrad_item(s, G, X, scale, idxW, cntW, dW, partials, packed);
-    it.splits = one_each ? 1 : wgrad_slices_bf16(s, wgrad_tiles_bf16(s.K_out, s.K_in, tile), fill);
+    it.splits = splits;
     return wgrad_bf16_batch(&it, 1, tile, st);
 }
 
@@ -590,26 +599,21 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
         }
         // a run of bf16 layers that plan their launch the same way
         const bool alone = own(a);
-        int picked[kWgradBatch], n = 0, next = l;
-        int tiles256 = 0, tiles128 = 0;
+        int picked[kWgradBatch], splits[kWgradBatch], n = 0, next = l;
+        int tile = 0, tiles256 = 0, tiles128 = 0;
         for (; next < l1 && n < kWgradBatch; ++next) {
             const vcas_layer_args &b = layers[next];
             if (!b.dW) continue;
             if (b.shape.dtype != VCAS_BF16 || own(b) != alone || form_of(b) != kPacked) break;
-            const int t256 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 256), t128 = wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 128);
-            if (alone && n > 0 &&
-                wgrad_tile_choice(t256, t128, kWgradFill) !=
-                    wgrad_tile_choice(wgrad_tiles_bf16(layers[picked[0]].shape.K_out, layers[picked[0]].shape.K_in, 256),
-                                      wgrad_tiles_bf16(layers[picked[0]].shape.K_out, layers[picked[0]].shape.K_in, 128), kWgradFill))
-                break;
+            const int its_tile = own_tile(b.shape, splits[n]);
+            if (alone && n > 0 && its_tile != tile) break;
+            if (alone) tile = its_tile;
             picked[n++] = next;
-            tiles256 += t256;
-            tiles128 += t128;
+            tiles256 += wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 256);
+            tiles128 += wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, 128);
         }
         const int fill = fill_or_default(a.wgrad_fill);
-        const vcas_shape &s0 = layers[picked[0]].shape;
-        const int tile = alone ? wgrad_tile_choice(wgrad_tiles_bf16(s0.K_out, s0.K_in, 256), wgrad_tiles_bf16(s0.K_out, s0.K_in, 128), fill)
-                               : wgrad_tile_choice(tiles256, tiles128, fill);
+        if (!alone) tile = wgrad_tile_choice(tiles256, tiles128, fill);
         int launch_tiles = 0;
         for (int i = 0; i < n; ++i) launch_tiles += wgrad_tiles_bf16(layers[picked[i]].shape.K_out, layers[picked[i]].shape.K_in, tile);
         WgradItem items[kWgradBatch];
@@ -619,7 +623,7 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
             unsigned char *base = static_cast<unsigned char *>(b.workspace);
             items[i] = wgrad_item(b.shape, b.G, b.X, b.plan.scaleW, b.plan.idxW, b.plan.cntW, b.dW,
                                   reinterpret_cast<float *>(base + w.partials), reinterpret_cast<uint16_t *>(base + w.packed));
-            items[i].splits = wgrad_slices_bf16(b.shape, alone ? wgrad_tiles_bf16(b.shape.K_out, b.shape.K_in, tile) : launch_tiles, fill);
+            items[i].splits = alone ? splits[i] : wgrad_slices_bf16(b.shape, launch_tiles, fill);
         }
         VCAS_TRY(wgrad_bf16_batch(items, n, tile, st));
         l = next;

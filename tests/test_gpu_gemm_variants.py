@@ -189,3 +189,25 @@ def test_gathering_layers_of_a_stack_share_launches(vb):
         want = torch.full((K, K), float("nan"), device="cuda")
         vb.vcas_linear_backward(shape, G, X, W, 0.7, 0.5, vb.Rng(2, l, 0), True, plan, dX, want, ws)
         assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
+
+
+def test_layers_of_one_big_tile_per_cu_in_a_stack(vb):
+    """Two layers of 14 x 14 tiles of 256x256 and one of 13 x 14 in a stack with wgrad_fill 0: the bits of calls of their
+    own, whichever tile either side takes."""
+    N, T = 2, 100
+    entries, keep = [], []
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    one = lambda *size: torch.randn(size, generator=gen, device="cuda").bfloat16()
+    for l, (K_in, K_out) in enumerate([(3400, 3456), (3400, 3456), (3400, 3208)]):
+        shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+        G, X = one(N * T, K_out), one(N * T, K_in)
+        plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+        dW = torch.full((K_out, K_in), float("nan"), device="cuda")
+        entries.append(vb.layer_args(shape, G, X, None, 1.0, 1.0, vb.Rng(2, l, 0), True, plan, None, dW, ws))
+        keep.append((shape, G, X, plan, ws, dW))
+    vb.vcas_backward_stack(vb.make_stack(entries), 3, *[torch.cuda.Stream() for _ in range(2)])
+    torch.cuda.synchronize()
+    for l, (shape, G, X, plan, ws, dW) in enumerate(keep):
+        want = torch.full_like(dW, float("nan"))
+        vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(2, l, 0), True, plan, None, want, ws)
+        assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
