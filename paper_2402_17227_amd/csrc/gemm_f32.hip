@@ -1,8 +1,8 @@
 // fp32 gather-GEMMs of the VCAS backward pass (the fp32 configuration) on v_mfma_f32_32x32x2_f32:
 // dgrad (Eq. 2, upper line) here, wgrad (Sec. 4.2) in wgrad_gather.hpp.
-// The *_far kernels at the end serve tensors that 32-bit buffer offsets do not reach: 64x64 output
-// tiles, four wavefronts, operands staged through registers into k-major LDS tiles ([k][row], pitch 68
-// floats, so that fragment reads are 32 consecutive floats), contraction in steps of 16.
+// dgrad_f32_staged_kernel and wgrad_f32_far_kernel serve tensors that 32-bit buffer offsets do not reach, the former also
+// short contractions: 64x64 output tiles, four wavefronts, operands staged through registers into k-major LDS tiles
+// ([k][row], pitch 68 floats, so that fragment reads are 32 consecutive floats), contraction in steps of 16.
 #include "wgrad_gather.hpp"
 
 namespace vcas {
@@ -223,11 +223,11 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(const float 
     }
 }
 
-// dgrad for tensors of 2 GiB and more.
+// dgrad for tensors of 2 GiB and more, and for many tiles of a short contraction (see dgrad_f32).
 // grid: tiles_n * (ceil(R/64) + 1) + 8 workgroups.  The first ceil8(compute
 // tiles) ids compute (spread over the XCDs), the next ones zero the rows of
 // dropped samples, the rest exit.
-__global__ __launch_bounds__(256) void dgrad_f32_far_kernel(const float *__restrict__ G, const float *__restrict__ W,
+__global__ __launch_bounds__(256) void dgrad_f32_staged_kernel(const float *__restrict__ G, const float *__restrict__ W,
                                                         const float *__restrict__ p,
                                                         const int32_t *__restrict__ idxA,
                                                         const int32_t *__restrict__ cntA, float *__restrict__ dX,
@@ -274,8 +274,10 @@ __global__ __launch_bounds__(256) void dgrad_f32_far_kernel(const float *__restr
         float sc = 0.0f;
         if (m < M) {
             const int s = idxA[m / T];
-            dst = s * T + (int)(m % T);
-            sc = 1.0f / (p[s]);
+            if (s >= 0 && s < N) {
+                dst = s * T + (int)(m % T);
+                sc = 1.0f / (p[s]);
+            }
         }
         row_of[tid] = dst;
         scale_of[tid] = sc;
@@ -476,11 +478,18 @@ vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const f
                       const int32_t *cntA, void *dX, const void *J, bool fill, int64_t expected_rows, hipStream_t st)
 {
     const int64_t R = (int64_t)s.N * s.T;
-    if (!offsets_fit(s)) {   // larger tensors than 32-bit buffer offsets reach, which the fp32 calls have always taken
+    const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
+    // Many tiles of a short contraction are prologues and epilogues: four wavefronts with a fifth of the LDS, six workgroups
+    // to a CU, hide them better than eight wavefronts, two to a CU.  This kernel and the 64x64 one below: 8192 rows,
+    // 1024 columns (2048 tiles), contraction 64 23.3 and 28.7 us, 128 32.3 and 36.1, 192 41.0 and 44.2, 256 50.5 and 51.9,
+    // 384 68.6 and 68.4; 768 tiles, contraction 64 13.0 and 15.0, 256 23.8 and 23.3; 384 tiles, contraction 64 11.3 and 10.9
+    // (32x64 tiles).
+    const bool short_tiles = s.K_out <= 256 && ((rows + 63) / 64) * ((s.K_in + 63) / 64) > 512;
+    if (short_tiles || !offsets_fit(s)) {   // offsets: larger tensors, which the fp32 calls have always taken
         const int tiles_n = (s.K_in + 63) / 64;
         const int64_t grid = tiles_n * ((R + 63) / 64 + 1) + 8;
         if (grid > (int64_t)1 << 30) return VCAS_EINVAL;
-        launch_timed(0, dgrad_f32_far_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const float *>(G),
+        launch_timed(0, dgrad_f32_staged_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const float *>(G),
                      static_cast<const float *>(W), p, idxA, cntA, static_cast<float *>(dX), s.N, s.T, s.K_in, s.K_out,
                      tiles_n, static_cast<const float *>(J), fill ? 1 : 0);
         return launch_status();
@@ -491,7 +500,6 @@ vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const f
     // 174 us; 1024->1024, 2048 rows: 42 and 46 us).  When even 32x32 tiles leave CUs empty, eight
     // wavefronts share each tile's contraction (344->2888, 36 kept rows: 23 us against 34 with 32x64
     // tiles; the kernel with register-staged loads took 85, and 143 us in the first case above).
-    const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
     auto per_cu = [&](int bm, int bn) { return (((rows + bm - 1) / bm) * ((s.K_in + bn - 1) / bn) + 255) / 256; };
     if (per_cu(32, 32) <= 1) return launch_dgrad_f32<32, 32, 1, 1, 8, 2, 3>(s, G, W, p, idxA, cntA, dX, J, fill, st);
     if (55 * per_cu(32, 64) < 100 * per_cu(64, 64))

@@ -211,3 +211,40 @@ def test_layers_of_one_big_tile_per_cu_in_a_stack(vb):
         want = torch.full_like(dW, float("nan"))
         vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(2, l, 0), True, plan, None, want, ws)
         assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
+
+
+# fp32 dgrad where few 64x64 tiles cover more than 256 CUs' worth of smaller ones (8 x 31 tiles of 64x64), with contractions
+# of less than, exactly and just beyond a step of 64, and the register-staged kernel (more than 512 tiles, contraction up to
+# 256) on both sides of its lines; samples dropped, Jacobians, rows and columns ragged
+@pytest.mark.parametrize("N,T,K_in,K_out,kept,jacobian", [
+    (9, 215, 456, 40, 9, False), (9, 215, 456, 64, 9, True), (9, 215, 456, 72, 9, False), (9, 215, 456, 200, 9, True),
+    (12, 215, 456, 72, 9, True), (5, 413, 1000, 8, 5, False), (5, 413, 1000, 136, 4, True), (5, 413, 1000, 256, 5, False),
+    (5, 413, 1000, 264, 5, True), (4, 512, 1024, 136, 4, False), (40, 13, 4040, 24, 37, True), (33, 64, 1040, 72, 1, False)])
+def test_fp32_dgrad_tiles(vb, N, T, K_in, K_out, kept, jacobian):
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_F32)
+    gen = torch.Generator(device="cuda").manual_seed(K_out + kept)
+    G = torch.randn((R, K_out), generator=gen, device="cuda")
+    W = torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02
+    J = torch.rand((R, K_in), generator=gen, device="cuda")
+    p = torch.rand(N, generator=gen, device="cuda") * 0.5 + 0.5
+    chosen = torch.randperm(N, generator=gen, device="cuda")[:kept].sort().values
+    idxA = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    idxA[:kept] = chosen.int()
+    cntA = torch.tensor([kept], dtype=torch.int32, device="cuda")
+    rows = torch.zeros(N, device="cuda")
+    rows[chosen] = 1.0 / p[chosen]
+    rows = rows.repeat_interleave(T)[:, None]
+    G[rows[:, 0] == 0] = float("nan")    # rows of dropped samples are not read
+    dX = torch.full((R, K_in), float("nan"), device="cuda")
+    if jacobian:
+        vb.vcas_sampled_dgrad_jac(shape, G, W, p, idxA, cntA, J, dX)
+    else:
+        vb.vcas_sampled_dgrad(shape, G, W, p, idxA, cntA, dX)
+    want = (G.nan_to_num().double() @ W.double()) * rows.double() * (J.double() if jacobian else 1.0)
+    on = rows[:, 0] > 0
+    assert float(dX[~on].abs().sum()) == 0.0
+    off = (dX.double() - want)[on]
+    # sums of up to 264 fp32 products: sqrt(264) 2^-24 = 1e-6, a row or a column alike
+    assert float((off.norm(dim=1) / want[on].norm(dim=1)).max()) <= 1e-5
+    assert float((off.norm(dim=0) / want[on].norm(dim=0)).max()) <= 1e-5
