@@ -732,18 +732,22 @@ enum DgradTile { kTile256, kTile128, kTile64, kTile128Whole, kTile64Whole };
 //  - 256x256 (one workgroup of eight wavefronts per CU) from 128 tiles up, half the CUs: inside a stack
 //    other kernels take the rest (192 made a step 1-3 % longer).  Where the kept count is known on the
 //    device only, the tiles of ALL rows are counted and half of them may be empty: 192.
-//  - one tile per CU and nothing else to hide its latencies: the kernels that read whole steps ahead
+//  - a contraction of less than 512 (eight steps): two stages.  The kernels that read whole steps ahead are twice the code
+//    for a loop that is over before it pays.  64x128 tiles, contraction 128, 256, 320, 512, 1024: 8 tiles 6.2, 7.7, 8.0,
+//    9.7, 10.5 us and reading ahead 7.1, 7.9, 8.7, 9.7, 10.2; 192 tiles 7.6, 9.0, 9.3, 10.0, 11.5 and 8.2, 9.0, 9.4, 10.1,
+//    11.0.
+//  - else one tile per CU and nothing else to hide its latencies: the kernels that read whole steps ahead
 //    (kWholeStep), 64x128 up to 200 tiles, 128x128 up to 224.  768->3072 transposed, i.e. K_out 3072 and
 //    K_in 768: 2048 rows, 192 or 96 tiles, 18 and 21 us (64x128 without reading ahead 23); 4096 rows,
 //    384 or 192 tiles, 35 and 24 us (30 with two 64x128 workgroups per CU).
 //  - two workgroups per CU: 64x128 up to 256 tiles of 128x128, 128x128 beyond (1024->1024: 4096 rows,
 //    512 or 256 tiles, 18 us both, 22 reading ahead; 8192 rows, 30 and 24 us).
-static DgradTile dgrad_tile(int64_t rows, int K_in, int n, bool rows_known)
+static DgradTile dgrad_tile(int64_t rows, int K_in, int K_out, int n, bool rows_known)
 {
     auto tiles = [&](int bm, int bn) { return n * ((rows + bm - 1) / bm) * ((K_in + bn - 1) / bn); };
     if (tiles(256, 256) >= (rows_known ? 128 : 192)) return kTile256;
-    if (tiles(64, 128) <= 200) return kTile64Whole;
-    if (tiles(128, 128) <= 224) return kTile128Whole;
+    if (K_out >= 512 && tiles(64, 128) <= 200) return kTile64Whole;
+    if (K_out >= 512 && tiles(128, 128) <= 224) return kTile128Whole;
     return tiles(128, 128) > 256 ? kTile128 : kTile64;
 }
 
@@ -760,7 +764,7 @@ vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int
     }
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    switch (dgrad_tile(rows, s.K_in, n, true)) {
+    switch (dgrad_tile(rows, s.K_in, s.K_out, n, true)) {
     case kTile256: return launch_dgrad_group<256, 256, 2, 4, 2, 1, -1>(s, grp, n, fill, st);
     case kTile64Whole: return launch_dgrad_group<64, 128, 2, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
     case kTile128Whole: return launch_dgrad_group<128, 128, 4, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
@@ -787,7 +791,7 @@ vcas_status dgrad_bf16(const vcas_shape &s, const void *G, const void *W, const 
     }
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    switch (dgrad_tile(rows, s.K_in, 1, expected_rows > 0)) {
+    switch (dgrad_tile(rows, s.K_in, s.K_out, 1, expected_rows > 0)) {
     case kTile256: return launch_dgrad<256, 256, 2, 4, 2, 1, -1>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
     case kTile64Whole: return launch_dgrad<64, 128, 2, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
     case kTile128Whole: return launch_dgrad<128, 128, 4, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);

@@ -248,3 +248,28 @@ def test_fp32_dgrad_tiles(vb, N, T, K_in, K_out, kept, jacobian):
     # sums of up to 264 fp32 products: sqrt(264) 2^-24 = 1e-6, a row or a column alike
     assert float((off.norm(dim=1) / want[on].norm(dim=1)).max()) <= 1e-5
     assert float((off.norm(dim=0) / want[on].norm(dim=0)).max()) <= 1e-5
+
+
+# bf16 dgrad on both sides of the contraction length from which it reads whole steps ahead (512: eight steps), full and
+# ragged last steps, 64x128 and 128x128 tiles of either kind
+@pytest.mark.parametrize("K_out", [8, 64, 72, 128, 136, 504, 512, 520, 568, 576, 640, 1032])
+@pytest.mark.parametrize("N,T,K_in", [(5, 41, 200), (9, 233, 776), (11, 233, 1544)])
+def test_bf16_dgrad_contractions(vb, N, T, K_in, K_out):
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(K_out + N)
+    G = torch.randn((R, K_out), generator=gen, device="cuda").bfloat16()
+    W = (torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02).bfloat16()
+    J = torch.rand((R, K_in), generator=gen, device="cuda").bfloat16()
+    p = torch.rand(N, generator=gen, device="cuda") * 0.5 + 0.5
+    idxA = torch.arange(1, N + 1, dtype=torch.int32, device="cuda")      # all samples but the first
+    cntA = torch.tensor([N - 1], dtype=torch.int32, device="cuda")
+    G[:T] = float("nan")    # rows of dropped samples are not read
+    dX = torch.full((R, K_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    vb.vcas_sampled_dgrad_jac(shape, G, W, p, idxA, cntA, J, dX)
+    want = (G[T:].double() @ W.double()) / p[1:].double().repeat_interleave(T)[:, None] * J[T:].double()
+    assert float(dX[:T].abs().sum()) == 0.0
+    off = dX[T:].double() - want
+    # fp32 sums rounded once to bf16: 2^-9 / sqrt(3) = 1.1e-3; a row or a column alike
+    assert float((off.norm(dim=1) / want.norm(dim=1)).max()) <= 5e-3
+    assert float((off.norm(dim=0) / want.norm(dim=0)).max()) <= 5e-3

@@ -61,7 +61,7 @@ def test_rows_from_blocks_bit_exact(vb, N, T, K):
                                                     (33, 125, 3080, 200, 1.0, True),     # 256x256 tiles, ragged rows and columns
                                                     (33, 125, 3080, 200, 0.5, False),
                                                     (17, 128, 1024, 72, 1.0, True),      # 64x128 tiles, two stages
-                                                    (6, 50, 264, 136, 0.7, False),       # 64x128 tiles, four stages
+                                                    (6, 50, 264, 136, 0.7, False),       # 64x128 tiles, few of them
                                                     (9, 64, 40, 72, 0.8, True)])         # less than one block of 64 columns
 def test_dgrad_block_sums(vb, N, T, kin, kout, frac, jac):
     from tests.gpu_util import from_device, rel_l2_rows, blocks_from_device_layout
