@@ -412,8 +412,10 @@ vcas_status vcas_backward_weight_cached(const vcas_shape *shape, const void *G, 
  *   out[1] = mean_j of Eq. 3, sum_t (1-q_t)/q_t score_t^2, under draw j's data mask
  *   out[2] = mean_j ||dW(SampleA only, draw j) - dW exact||_F^2
  *   out[3] = mean_j ||dW(SampleA and SampleW, draw j) - dW exact||_F^2
- * dW exact is this library's dW at keep ratio one.  `plan` is scratch for the
- * draws (left holding the last one).
+ * dW exact is this library's dW at keep ratio one (fp32 sums, as those of the
+ * draws, but not in their order).  out[2] is exactly zero where every p_i is 0 or
+ * 1, and a draw adds exactly zero to out[3] where every q_t is as well.  `plan`
+ * is scratch for the draws (left holding the last one).
  */
 vcas_status vcas_variance_probe(const vcas_shape *shape, const void *G, const void *X, double rho,
                                 double nu, const vcas_rng *base, int32_t M, const vcas_plan *plan,

@@ -728,6 +728,7 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
             ProbeDraw &d = draws.draw[k];
             d.index = base.draw + (uint32_t)(j0 + k);
             d.p = p;
+            d.gnorm = gnorm;
             d.maskA = maskA;
             d.idxA = idxA;
             d.cntA = cntA;
@@ -736,7 +737,7 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
             d.q = q;
             d.list_a = list_a;
             d.rows_a = reinterpret_cast<int32_t *>(words + 24);
-            d.eq3 = reinterpret_cast<double *>(words);
+            d.closed = reinterpret_cast<double *>(words);
             InlineSampleA &a = group_a.prob[k];
             a.gsq = pl.gsq;
             a.budget = (double)s.N * rho;
@@ -791,7 +792,7 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
         }
         VCAS_TRY(probe_draws(draws, n, pl.gsq, pl.xsq, scale_a, R, s.T, base, st));
         VCAS_TRY(sampler_w_group(group_w, n, 0, s.N, s.T, 1, 2, st));
-        VCAS_TRY(probe_eq3(draws, n, R, s.T, pl.xsq, last, st));
+        VCAS_TRY(probe_closed(draws, n, R, s.N, s.T, pl.xsq, last, st));
         const double weight = 1.0 / (double)M;
         bool large = true;
         if (fits) {
@@ -806,11 +807,12 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
             float *draw = reinterpret_cast<float *>(ws + w.probe_draw);
             for (int i = 0; i < 2 * n; ++i) {
                 VCAS_TRY(dispatch_wgrad(s, G, X, tasks[i].row_scale, tasks[i].idx, tasks[i].cnt, draw, ws, st));
-                VCAS_TRY(sq_diff_add(draw, exact, elems, weight, reinterpret_cast<double *>(ws + w.probe_acc), out + 2 + i / n, st));
+                VCAS_TRY(sq_diff_add(draw, exact, elems, weight, reinterpret_cast<double *>(ws + w.probe_acc),
+                                     draws.draw[i % n].closed, 1 + i / n, out + 2 + i / n, st));
             }
         }
         VCAS_TRY(probe_finish(draws, n, fits ? tile_sums : nullptr, gather_tiles(s.dtype, s.K_out, s.K_in, large), weight,
-                              draws.draw[0].p, group_a.prob[0].gnorm, s.N, j0 == 0, out, st));
+                              j0 == 0, out, st));
     }
     return VCAS_OK;
 }

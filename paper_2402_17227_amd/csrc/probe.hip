@@ -50,11 +50,12 @@ __global__ __launch_bounds__(256) void probe_draws_kernel(ProbeDraws d, const fl
     if (t == 0) *w.rows_a = rows;
 }
 
-// Eq. 3 under one draw's data mask: sum of (1 - q)/q score^2 over q > 0 (fp64, fixed order); one workgroup per
-// draw.  Where the draw is the last one, also zeroes the norms of X of its dropped samples, as the plan wants.
-__global__ __launch_bounds__(1024) void probe_eq3_kernel(ProbeDraws d, int R, int T, float *__restrict__ xsq, int last)
+// The closed forms of one draw (fp64, fixed order), one workgroup each: sum of (1 - p)/p gnorm^2 over p > 0, and Eq. 3
+// under the draw's data mask, the sum of (1 - q)/q score^2 over q > 0.  Where the draw is the last one, also zeroes
+// the norms of X of its dropped samples, as the plan wants.
+__global__ __launch_bounds__(1024) void probe_closed_kernel(ProbeDraws d, int R, int N, int T, float *__restrict__ xsq, int last)
 {
-    __shared__ double sh[16];
+    __shared__ double sh[16], sh_a[16];
     const ProbeDraw &w = d.draw[blockIdx.x];
     double acc = 0.0;
     for (int t0 = threadIdx.x; t0 < R; t0 += 4 * 1024) {
@@ -74,10 +75,29 @@ __global__ __launch_bounds__(1024) void probe_eq3_kernel(ProbeDraws d, int R, in
             if ((int)blockIdx.x == last && !w.maskA[t / T]) xsq[t] = 0.0f;
         }
     }
+    double acc_a = 0.0;
+    for (int i = threadIdx.x; i < N; i += 1024) {
+        const double pr = w.p[i], g = w.gnorm[i];
+        if (pr > 0.0) acc_a += (1.0 - pr) / pr * (g * g);
+    }
     acc = wave_exchange_sum(acc);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+    acc_a = wave_exchange_sum(acc_a);
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = acc;
+        sh_a[threadIdx.x >> 6] = acc_a;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) *w.eq3 = tree16(sh);
+    if (threadIdx.x == 0) {
+        w.closed[0] = tree16(sh_a);
+        w.closed[1] = tree16(sh);
+    }
+}
+
+// Every probability that these closed forms sum over is 0 or 1: the draw can only be the exact gradient, and its distance is
+// zero.  The kernels that form the two add in different orders, so that what they differ by is rounding.
+__device__ __forceinline__ bool no_choice(const double *closed, int n)
+{
+    return closed[0] == 0.0 && (n < 2 || closed[1] == 0.0);
 }
 
 __device__ __forceinline__ double block_sum_256(double v, double *sh)
@@ -91,33 +111,29 @@ __device__ __forceinline__ double block_sum_256(double v, double *sh)
 
 // Adds a chunk of n draws to the four results: tile sums of the products (draw k: SampleA only in
 // sq[k * tiles ..], both samplers in sq[(n + k) * tiles ..]; null: added elsewhere), Eq. 3 of each draw,
-// and with the first chunk the closed form over the samples.
+// and with the first chunk the closed form over the samples (the same in every draw).
 __global__ __launch_bounds__(256) void probe_finish_kernel(ProbeDraws d, int n, const double *__restrict__ sq, int tiles,
-                                                           double weight, const float *__restrict__ p,
-                                                           const float *__restrict__ gnorm, int N, int first,
-                                                           double *__restrict__ out)
+                                                           double weight, int first, double *__restrict__ out)
 {
     __shared__ double sh[4];
+    __shared__ int skip[2 * kProbeDraws];
     if (sq) {
+        if ((int)threadIdx.x < 2 * n) skip[threadIdx.x] = no_choice(d.draw[threadIdx.x % n].closed, 1 + threadIdx.x / n);
+        __syncthreads();
         for (int w = 0; w < 2; ++w) {
             double acc = 0.0;
-            for (int i = threadIdx.x; i < n * tiles; i += 256) acc += sq[(int64_t)w * n * tiles + i];
+            for (int i = threadIdx.x; i < n * tiles; i += 256) {
+                const double one = sq[(int64_t)w * n * tiles + i];
+                acc += skip[w * n + i / tiles] ? 0.0 : one;
+            }
             acc = block_sum_256(acc, sh);
             if (threadIdx.x == 0) out[2 + w] += weight * acc;
         }
     }
-    if (first) {
-        double acc = 0.0;
-        for (int i = threadIdx.x; i < N; i += 256) {
-            const double pr = p[i], g = gnorm[i];
-            if (pr > 0.0) acc += (1.0 - pr) / pr * (g * g);
-        }
-        acc = block_sum_256(acc, sh);
-        if (threadIdx.x == 0) out[0] = acc;
-    }
     if (threadIdx.x == 0) {
+        if (first) out[0] = d.draw[0].closed[0];
         double s = 0.0;
-        for (int k = 0; k < n; ++k) s += *d.draw[k].eq3;
+        for (int k = 0; k < n; ++k) s += d.draw[k].closed[1];
         out[1] += weight * s;
     }
 }
@@ -138,9 +154,10 @@ __global__ __launch_bounds__(256) void sq_diff_partial_kernel(const float *__res
 }
 
 __global__ __launch_bounds__(64) void sq_diff_final_kernel(const double *__restrict__ partial, int blocks,
-                                                           double weight, double *__restrict__ out)
+                                                           double weight, const double *__restrict__ closed, int n_closed,
+                                                           double *__restrict__ out)
 {
-    if (threadIdx.x != 0) return;
+    if (threadIdx.x != 0 || no_choice(closed, n_closed)) return;
     double s = 0.0;
     for (int i = 0; i < blocks; ++i) s += partial[i];
     *out += weight * s;
@@ -169,24 +186,25 @@ vcas_status probe_draws(const ProbeDraws &d, int n, const float *gsq, const floa
     return launch_status();
 }
 
-vcas_status probe_eq3(const ProbeDraws &d, int n, int64_t R, int T, float *xsq, int last, hipStream_t st)
+vcas_status probe_closed(const ProbeDraws &d, int n, int64_t R, int N, int T, float *xsq, int last, hipStream_t st)
 {
-    hipLaunchKernelGGL(probe_eq3_kernel, dim3(n), dim3(1024), 0, st, d, (int)R, T, xsq, last);
+    hipLaunchKernelGGL(probe_closed_kernel, dim3(n), dim3(1024), 0, st, d, (int)R, N, T, xsq, last);
     return launch_status();
 }
 
-vcas_status probe_finish(const ProbeDraws &d, int n, const double *sq, int tiles, double weight, const float *p,
-                         const float *gnorm, int N, bool first, double *out, hipStream_t st)
+vcas_status probe_finish(const ProbeDraws &d, int n, const double *sq, int tiles, double weight, bool first, double *out,
+                         hipStream_t st)
 {
-    hipLaunchKernelGGL(probe_finish_kernel, dim3(1), dim3(256), 0, st, d, n, sq, tiles, weight, p, gnorm, N, first ? 1 : 0, out);
+    hipLaunchKernelGGL(probe_finish_kernel, dim3(1), dim3(256), 0, st, d, n, sq, tiles, weight, first ? 1 : 0, out);
     return launch_status();
 }
 
-vcas_status sq_diff_add(const float *a, const float *b, int64_t n, double weight, double *partial, double *out, hipStream_t st)
+vcas_status sq_diff_add(const float *a, const float *b, int64_t n, double weight, double *partial, const double *closed,
+                        int n_closed, double *out, hipStream_t st)
 {
     const int blocks = 32;   // what `partial` has room for
     hipLaunchKernelGGL(sq_diff_partial_kernel, dim3(blocks), dim3(256), 0, st, a, b, n, partial);
-    hipLaunchKernelGGL(sq_diff_final_kernel, dim3(1), dim3(64), 0, st, partial, blocks, weight, out);
+    hipLaunchKernelGGL(sq_diff_final_kernel, dim3(1), dim3(64), 0, st, partial, blocks, weight, closed, n_closed, out);
     return launch_status();
 }
 

@@ -10,13 +10,13 @@ constexpr int kProbeDraws = 8;   // mask draws that go through the launches toge
 // One mask draw: what SampleA has decided, and where SampleW's inputs and the lists go.
 struct ProbeDraw {
     uint32_t index;            // rng.draw of this draw
-    const float *p;
+    const float *p, *gnorm;
     const uint8_t *maskA;
     const int32_t *idxA, *cntA;
     float *u, *score;          // [R]
     const float *q;            // [R], SampleW's outcome
     int32_t *list_a, *rows_a;  // [R] rows of kept samples, and how many
-    double *eq3;
+    double *closed;            // [2] Sec. 4.1's variance under p, and Eq. 3 under this draw's data mask
 };
 struct ProbeDraws {
     ProbeDraw draw[kProbeDraws];
@@ -32,10 +32,11 @@ vcas_status probe_begin(float *ones, int32_t *iota, int32_t *cnt, double *out, i
 vcas_status probe_draws(const ProbeDraws &d, int n, const float *gsq, const float *xsq, float *scale_a, int64_t R, int T,
                         const vcas_rng &rng, hipStream_t st);
 // last: which of the n draws is the probe's last one (-1: none)
-vcas_status probe_eq3(const ProbeDraws &d, int n, int64_t R, int T, float *xsq, int last, hipStream_t st);
-vcas_status probe_finish(const ProbeDraws &d, int n, const double *sq, int tiles, double weight, const float *p,
-                         const float *gnorm, int N, bool first, double *out, hipStream_t st);
-// out += weight * ||a - b||^2; partial: 32 doubles
-vcas_status sq_diff_add(const float *a, const float *b, int64_t n, double weight, double *partial, double *out, hipStream_t st);
+vcas_status probe_closed(const ProbeDraws &d, int n, int64_t R, int N, int T, float *xsq, int last, hipStream_t st);
+vcas_status probe_finish(const ProbeDraws &d, int n, const double *sq, int tiles, double weight, bool first, double *out,
+                         hipStream_t st);
+// out += weight * ||a - b||^2 unless the first n_closed closed forms are all zero; partial: 32 doubles
+vcas_status sq_diff_add(const float *a, const float *b, int64_t n, double weight, double *partial, const double *closed,
+                        int n_closed, double *out, hipStream_t st);
 
 }  // namespace vcas

@@ -34,3 +34,35 @@ def test_probe_over_chunks_of_draws(case):
     np.testing.assert_allclose(got[:2], want[:2], rtol=1e-9)
     np.testing.assert_allclose(got[2:], want[2:], rtol=1e-4 if dtype == F32 else 3e-2)
     compare_plan(plan_to_numpy(plan), oracle.sampling_plan(G, X, dtype, N, T, 0.5, 0.5, 5, 4, 10 + M - 1))
+
+
+# Where nothing is left to chance a draw is the exact gradient and its distance is zero, whichever kernels form the two: bf16
+# exact gradients of many rows (packed, in slices) and of few, fp32 in slices, products beyond the comparing kernel (K_in
+# K_out of 2^28 and more; one draw after the other), more than one chunk of draws
+@pytest.mark.parametrize("case", [
+    (BF16, 8, 300, 264, 136, 9), (BF16, 3, 40, 776, 1032, 2), (F32, 8, 300, 264, 136, 3), (F32, 5, 37, 72, 64, 9),
+    (F32, 2, 6, 16392, 16392, 2),
+], ids=lambda c: "x".join(map(str, c)))
+def test_probe_without_a_choice(case):
+    from paper_2402_17227_amd import binding as vb
+    dtype, N, T, K_in, K_out, M = case
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    real = torch.bfloat16 if dtype == BF16 else torch.float32
+    G = torch.randn((N * T, K_out), generator=gen, device="cuda").to(real)
+    X = torch.randn((N * T, K_in), generator=gen, device="cuda").to(real)
+    shape = vb.shape_of(N, T, K_in, K_out, dtype)
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+
+    def probe(rho, nu):
+        out = torch.full((4,), float("nan"), dtype=torch.float64, device="cuda")
+        vb.vcas_variance_probe(shape, G, X, rho, nu, vb.Rng(5, 4, 10), M, plan, out, ws)
+        return out.tolist()
+
+    assert probe(1.0, 1.0) == [0.0] * 4
+    only_tokens = probe(1.0, 0.5)
+    assert only_tokens[0] == only_tokens[2] == 0.0 and only_tokens[1] > 0.0 and only_tokens[3] > 0.0
+    # half of the budget is enough for every sample that is not zero, and a zero row is not one more choice
+    G[(N // 2) * T:] = 0
+    X[1] = 0
+    assert probe(0.5, 1.0) == [0.0] * 4
+    assert probe(0.25, 1.0)[2] > 0.0
