@@ -663,9 +663,9 @@ static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, cons
     return weight_half(s, G, X, rho, nu, rng, token_sampling, pl, dW, workspace, side);
 }
 
-// The probe in chunks of up to kProbeDraws mask draws (see probe.hip).  The row norms and the exact gradient
-// come first, once; the vectors of a chunk's draws lie in the workspace, those of the very last draw
-// in the plan.
+// The probe in chunks of up to probe_chunk mask draws (see probe.hip).  The row norms and the exact gradient
+// come first, once; the vectors of a chunk's draws lie in the workspace, those of the very last draw and of
+// draws that go alone in the plan.
 static vcas_status variance_probe(const vcas_shape &s, const void *G, const void *X, double rho, double nu,
                                   const vcas_rng &base, int M, const vcas_plan &pl, double *out, unsigned char *ws,
                                   hipStream_t st)
@@ -693,21 +693,22 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
     // 32x32 floats
     double *tile_sums = reinterpret_cast<double *>(ws + w.probe_draw);
     unsigned char *const chunk_at = at;
-    for (int j0 = 0; j0 < M; j0 += kProbeDraws) {
-        const int n = M - j0 < kProbeDraws ? M - j0 : kProbeDraws;
+    const int chunk = probe_chunk(s);
+    for (int j0 = 0; j0 < M; j0 += chunk) {
+        const int n = M - j0 < chunk ? M - j0 : chunk;
         at = chunk_at;
         ProbeDraws draws = {};
         SampleAGroup group_a = {};
         SampleWGroup group_w = {};
         GatherTask tasks[2 * kProbeDraws] = {};
         for (int k = 0; k < n; ++k) {
-            const bool last = j0 + k == M - 1;
+            const bool in_plan = j0 + k == M - 1 || chunk == 1;
             float *gnorm = pl.gnorm, *p = pl.p, *score = pl.score, *q = pl.q, *scale = pl.scaleW, *u;
             uint8_t *maskA = pl.maskA, *maskW = pl.maskW;
             int32_t *idxA = pl.idxA, *cntA = pl.cntA, *idxW = pl.idxW, *cntW = pl.cntW;
             unsigned char *words = take(256);   // small results of this draw
             int32_t *list_a = reinterpret_cast<int32_t *>(take(4 * R));
-            if (last) {
+            if (in_plan) {
                 u = reinterpret_cast<float *>(ws + w.uniforms);
             } else {
                 unsigned char *const first = at;

@@ -59,7 +59,7 @@ inline int elem_bytes(int dtype) { return dtype == VCAS_BF16 ? 2 : 4; }
 // probe lays its own vectors
 
 constexpr size_t kLaneSumBytes = 64 * 64 * sizeof(float);   // lane sums of the row norms of up to 64 samples
-size_t probe_scratch_bytes(int64_t N, int64_t R);   // host: probe.hip
+size_t probe_scratch_bytes(const vcas_shape &s);   // host: probe.hip
 
 struct WorkspaceLayout {
     size_t control, partials, probe_exact, probe_draw, probe_acc, rule, lanes, uniforms, packed, packed_bytes, total;
@@ -85,7 +85,7 @@ inline WorkspaceLayout workspace_layout(const vcas_shape *s)
     const size_t packed_bytes = s->dtype == VCAS_BF16 ? (size_t)s->N * s->T * (s->K_in < s->K_out ? s->K_in : s->K_out) * 2 : 0;
     w.packed_bytes = (packed_bytes + 255) & ~(size_t)255;
     // the variance probe's vectors lie over the packed operand, which it is done with when it needs them
-    const size_t probe = probe_scratch_bytes(s->N, (int64_t)s->N * s->T);
+    const size_t probe = probe_scratch_bytes(*s);
     w.total = w.packed + (w.packed_bytes > probe ? w.packed_bytes : probe);
     return w;
 }

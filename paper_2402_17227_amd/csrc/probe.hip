@@ -163,12 +163,7 @@ __global__ __launch_bounds__(64) void sq_diff_final_kernel(const double *__restr
     *out += weight * s;
 }
 
-// The vectors of a chunk's draws (those of the probe's last draw lie in the plan), a row list and a few words for
-// each, and 1/p of every row.
-size_t probe_scratch_bytes(int64_t N, int64_t R)
-{
-    return kProbeDraws * probe_draw_bytes(N, R) + (kProbeDraws + 1) * probe_pad(4 * R) + kProbeDraws * 256;
-}
+size_t probe_scratch_bytes(const vcas_shape &s) { return probe_chunk_bytes(s.N, (int64_t)s.N * s.T, probe_chunk(s)); }
 
 // ---- host launchers ---------------------------------------------------------------------------
 

@@ -5,7 +5,7 @@
 
 namespace vcas {
 
-constexpr int kProbeDraws = 8;   // mask draws that go through the launches together
+constexpr int kProbeDraws = 8;   // mask draws that go through the launches together, at the most
 
 // One mask draw: what SampleA has decided, and where SampleW's inputs and the lists go.
 struct ProbeDraw {
@@ -27,6 +27,22 @@ inline size_t probe_pad(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 inline size_t probe_draw_bytes(int64_t N, int64_t R)
 {
     return 5 * probe_pad(4 * R) + probe_pad(R) + 3 * probe_pad(4 * N) + probe_pad(N) + 256;
+}
+// n draws together: their vectors (those of the probe's last draw, or of a draw that goes alone, lie in the plan), a
+// row list and a few words for each, and 1/p of every row.
+inline size_t probe_chunk_bytes(int64_t N, int64_t R, int n)
+{
+    return (n > 1 ? n * probe_draw_bytes(N, R) : 0) + (n + 1) * probe_pad(4 * R) + n * 256;
+}
+// How many draws go together.  Their scratch is part of every layer's workspace: 64 MiB of it (eight draws of 328000 rows),
+// or half of what the layer's G and X take.
+inline int probe_chunk(const vcas_shape &s)
+{
+    const int64_t R = (int64_t)s.N * s.T;
+    const size_t rows = (size_t)R * (s.K_in + s.K_out) * elem_bytes(s.dtype) / 2, room = rows > (64u << 20) ? rows : 64u << 20;
+    int n = kProbeDraws;
+    while (n > 1 && probe_chunk_bytes(s.N, R, n) > room) --n;
+    return n;
 }
 vcas_status probe_begin(float *ones, int32_t *iota, int32_t *cnt, double *out, int64_t R, hipStream_t st);
 vcas_status probe_draws(const ProbeDraws &d, int n, const float *gsq, const float *xsq, float *scale_a, int64_t R, int T,

@@ -1,6 +1,6 @@
 """The variance probe over one draw, a chunk of eight, and more than one chunk, with both output tiles of the comparing
-kernel, more samples than a workgroup has threads and rows beyond the one-workgroup samplers, against the oracle; and the
-plan it leaves: that of the last draw."""
+kernel, more samples than a workgroup has threads, rows beyond the one-workgroup samplers and rows so many that fewer draws go
+together, against the oracle; and the plan it leaves: that of the last draw."""
 import numpy as np
 import pytest
 import torch
@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (F32, 8, 24, 72, 64, 1), (BF16, 8, 24, 72, 64, 8), (F32, 5, 37, 264, 136, 9), (BF16, 5, 37, 264, 136, 17),
     (BF16, 3, 40, 776, 1032, 2), (F32, 3, 40, 776, 392, 2), (BF16, 1100, 2, 16, 24, 3), (F32, 7, 2400, 8, 8, 9),
+    # rows whose vectors fill a chunk's scratch: seven draws together, then two, one after the other
+    (F32, 70, 4700, 8, 8, 9), (BF16, 100, 10500, 8, 8, 3), (BF16, 1100, 2100, 8, 8, 3),
 ], ids=lambda c: "x".join(map(str, c)))
 def test_probe_over_chunks_of_draws(case):
     from paper_2402_17227_amd import binding as vb

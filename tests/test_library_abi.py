@@ -38,6 +38,16 @@ def test_workspace_bytes_and_status_strings(vb):
     assert b"null" in vb.lib().vcas_status_string(2)
 
 
+@pytest.mark.parametrize("N,T", [(64, 1024), (512, 512), (512, 1040), (16384, 1024), (16384, 65536)])
+@pytest.mark.parametrize("K", [8, 40, 64, 200])
+def test_workspace_of_many_rows(vb, N, T, K):
+    """What a workspace holds by the row (uniforms, the variance probe's vectors, in bf16 the packed operand) stays below the
+    layer's own G and X where those are large, and below 128 MiB where they are not."""
+    for dtype, size in ((vb.VCAS_F32, 4), (vb.VCAS_BF16, 2)):
+        small = vb.vcas_workspace_bytes(vb.shape_of(1, 1, K, K, dtype))
+        assert vb.vcas_workspace_bytes(vb.shape_of(N, T, K, K, dtype)) - small <= max(128 << 20, N * T * 2 * K * size) + 8 * 4 * K * K
+
+
 def test_block_sum_buffer_size(vb):
     """Four neighbouring 64-column blocks of a row share 16 bytes: ceil(ceil(K/64)/4) groups of R x 16 bytes."""
     assert vb.vcas_sq_blocks_bytes(16384, 1024) == 16384 * 16 * 4
