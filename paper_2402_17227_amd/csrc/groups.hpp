@@ -52,7 +52,7 @@ struct SampleWProblem {
     float *xsq;
     const float *p;
     const uint8_t *maskA;
-    const float *u;
+    float *u;       // uniforms by row; a long vector's counts lie over them once they have been compared
     double budget;
     float *score, *q;
     uint8_t *maskW;

@@ -297,31 +297,41 @@ __global__ __launch_bounds__(1024) void sampler_w_rule_kernel(SampleWGroup grp, 
     }
 }
 
-// q, mask and scale of every row.
+// q, mask and scale of every row.  COUNTED: also how many of the workgroup's 256 rows are kept, over the first of their
+// uniforms.
+template <bool COUNTED>
 __global__ __launch_bounds__(256) void sampler_w_apply_kernel(SampleWGroup grp, int R, int T, int token_sampling)
 {
     const SampleWProblem &w = grp.prob[blockIdx.y];
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= R) return;
-    const int i = t / T;
-    float qv;
-    bool m;
-    if (token_sampling) {
-        const KeepRule rule = {w.rule[0], w.rule[1]};
-        qv = keep_prob(w.score[t], rule);
-        m = w.u[t] < qv;
-    } else {
-        m = w.maskA[i] != 0;
-        qv = m ? 1.0f : 0.0f;
+    bool m = false;
+    if (t < R) {
+        const int i = t / T;
+        float qv;
+        if (token_sampling) {
+            const KeepRule rule = {w.rule[0], w.rule[1]};
+            qv = keep_prob(w.score[t], rule);
+            m = w.u[t] < qv;
+        } else {
+            m = w.maskA[i] != 0;
+            qv = m ? 1.0f : 0.0f;
+        }
+        w.q[t] = qv;
+        w.maskW[t] = m ? 1 : 0;
+        w.scaleW[t] = m ? 1.0f / (w.p[i] * qv) : 0.0f;
     }
-    w.q[t] = qv;
-    w.maskW[t] = m ? 1 : 0;
-    w.scaleW[t] = m ? 1.0f / (w.p[i] * qv) : 0.0f;
+    if constexpr (COUNTED) {
+        __shared__ int wave_count[4];
+        const int n = ballot_count(m);
+        if ((threadIdx.x & 63) == 0) wave_count[threadIdx.x >> 6] = n;
+        __syncthreads();   // ... and everybody has read its uniform
+        if (threadIdx.x == 0) w.u[t] = __int_as_float((wave_count[0] + wave_count[1]) + (wave_count[2] + wave_count[3]));
+    }
 }
 
 // Kept list of 1024 rows per workgroup.  The place of a row in the ascending list is the number of kept
-// rows in front of it: every workgroup adds up the mask bytes before its own rows again (a few 16-byte
-// loads per thread), which is cheaper than an exchange between workgroups.
+// rows in front of it: every workgroup adds up the mask bytes before its own rows again, a few 16-byte
+// loads per thread up to kListRows, which is cheaper than an exchange between workgroups.
 __global__ __launch_bounds__(1024) void sampler_w_list_kernel(SampleWGroup grp, int R)
 {
     __shared__ int wave_count[16], wave_before[16];
@@ -356,6 +366,52 @@ __global__ __launch_bounds__(1024) void sampler_w_list_kernel(SampleWGroup grp, 
     }
     if (m) w.idxW[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = t;
     if (tid == 0 && first + 1024 >= R) *w.cntW = total;
+}
+
+// The same for longer vectors, where adding up everything in front would be R^2 / 2048 bytes of reads: the counts that
+// sampler_w_apply_kernel left for every 256 rows become places (one workgroup per layer), and every 256 rows go there.
+__global__ __launch_bounds__(1024) void sampler_w_places_kernel(SampleWGroup grp, int R)
+{
+    __shared__ int wave_total[16];
+    const SampleWProblem &w = grp.prob[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, blocks = (R + 255) / 256;
+    int run = 0, next = tid < blocks ? __float_as_int(w.u[256 * tid]) : 0;
+    for (int b0 = 0; b0 < blocks; b0 += 1024) {
+        const int b = b0 + tid, mine = next;
+        next = b + 1024 < blocks ? __float_as_int(w.u[256 * (b + 1024)]) : 0;
+        int incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d, kWave);
+            if (lane >= d) incl += up;
+        }
+        if (lane == 63) wave_total[wave] = incl;
+        __syncthreads();
+        int before = run;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            before += v < wave ? wave_total[v] : 0;
+            run += wave_total[v];
+        }
+        if (b < blocks) w.u[256 * b] = __int_as_float(before + incl - mine);
+        __syncthreads();   // the totals have been read
+    }
+    if (tid == 0) *w.cntW = run;
+}
+
+__global__ __launch_bounds__(256) void sampler_w_place_kernel(SampleWGroup grp, int R)
+{
+    __shared__ int wave_count[4];
+    const SampleWProblem &w = grp.prob[blockIdx.y];
+    const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool m = t < R && w.maskW[t] != 0;
+    const uint64_t b = __ballot(m);
+    if (lane == 0) wave_count[wave] = __builtin_popcountll(b);
+    int at = __float_as_int(w.u[blockIdx.x * 256]);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 3; ++v) at += v < wave ? wave_count[v] : 0;
+    if (m) w.idxW[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = t;
 }
 
 // ---- host launchers ---------------------------------------------------------
@@ -434,6 +490,10 @@ vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *
     return launch_status();
 }
 
+// Norm pass, apply and list of one layer with cached norms, mask bytes against counts: 65536 rows 8.0 and 9.1 us, 131072 9.4
+// and 9.5, 262144 12.6 and 11.0, 2^20 37 and 23, 2^24 5351 and 347.
+constexpr int kListRows = 131072;
+
 // SampleW of n <= kMaxSamplers layers with one N and T in one set of launches.  Up to 16384 rows one
 // workgroup per layer does everything; beyond, see sampler_w_rule_kernel and what
 // follows it.
@@ -461,8 +521,15 @@ vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq
         else if (R <= 65536) hipLaunchKernelGGL(sampler_w_rule_kernel<64>, dim3(n), dim3(1024), 0, st, grp, R);
         else hipLaunchKernelGGL(sampler_w_rule_kernel<0>, dim3(n), dim3(1024), 0, st, grp, R);
     }
-    hipLaunchKernelGGL(sampler_w_apply_kernel, dim3((R + 255) / 256, n), dim3(256), 0, st, grp, R, T, token_sampling);
-    hipLaunchKernelGGL(sampler_w_list_kernel, dim3((R + 1023) / 1024, n), dim3(1024), 0, st, grp, R);
+    const dim3 by256((R + 255) / 256, n);
+    if (R <= kListRows) {
+        hipLaunchKernelGGL(sampler_w_apply_kernel<false>, by256, dim3(256), 0, st, grp, R, T, token_sampling);
+        hipLaunchKernelGGL(sampler_w_list_kernel, dim3((R + 1023) / 1024, n), dim3(1024), 0, st, grp, R);
+    } else {
+        hipLaunchKernelGGL(sampler_w_apply_kernel<true>, by256, dim3(256), 0, st, grp, R, T, token_sampling);
+        hipLaunchKernelGGL(sampler_w_places_kernel, dim3(n), dim3(1024), 0, st, grp, R);
+        hipLaunchKernelGGL(sampler_w_place_kernel, by256, dim3(256), 0, st, grp, R);
+    }
     return launch_status();
 }
 

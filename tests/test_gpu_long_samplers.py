@@ -1,6 +1,6 @@
 """SampleW on both sides of the lines between its forms: one element per thread up to sixteen in one workgroup, the three
-launches for more rows than that (scores in 32 or 64 registers per thread, or read again every round), more samples than
-a workgroup has threads.  Plans bit for bit against the oracle."""
+launches for more rows than that (scores in 32 or 64 registers per thread, or read again every round), the list from the
+mask bytes or from counts, more samples than a workgroup has threads.  Plans bit for bit against the oracle."""
 import pytest
 import torch
 
@@ -27,6 +27,8 @@ CASES = [  # dtype, N, T, K_in, K_out, rho, nu
     (BF16, 64, 1024, 8, 8, 0.5, 0.5), (F32, 2048, 31, 8, 8, 0.5, 0.05),
     (BF16, 3, 21846, 8, 8, 0.7, 0.6),            # 65538 rows
     (BF16, 40, 13, 520, 8, 0.5, 0.02),           # sums in which almost nothing is kept
+    (F32, 64, 2048, 8, 8, 0.6, 0.5), (BF16, 11, 11916, 8, 8, 0.7, 0.4),    # 131072 rows, 131076
+    (F32, 1111, 500, 8, 8, 0.5, 0.3),            # more counts than a workgroup has threads
 ]
 
 
@@ -75,3 +77,26 @@ def test_siblings_with_long_vectors(vb, R):
         assert n == int(b[3].cntW.item()) and torch.equal(a[3].idxW[:n], b[3].idxW[:n])
         assert torch.equal(a[3].q.view(torch.int32), b[3].q.view(torch.int32)) and torch.equal(a[3].scaleW, b[3].scaleW)
         assert torch.equal(a[5], b[5]) and torch.equal(a[6], b[6])
+
+
+def test_plans_of_many_rows_take_linear_time(vb):
+    """Four times the rows, in the launches behind the keep rule (norms given, no token sampling, no dW): about four times
+    the time, where work that grows with the square of the rows would take sixteen times."""
+    took = []
+    for R in (1 << 23, 1 << 25):
+        shape = vb.shape_of(64, R // 64, 8, 8, F32)
+        G, xsq = torch.randn((R, 8), device="cuda"), torch.rand(R, device="cuda")
+        plan, ws = vb.Plan.allocate(64, R // 64), vb.make_workspace(shape)
+        vb.vcas_backward_data(shape, G, G, None, 0.7, vb.Rng(1, 2, 0), False, plan, None, ws)
+        best = float("inf")
+        for _ in range(4):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            vb.vcas_backward_weight_cached(shape, G, G, xsq, 0.7, 0.5, vb.Rng(1, 2, 0), False, plan, None, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        took.append(best)
+        kept = plan.maskA.bool().repeat_interleave(R // 64).nonzero()[:, 0]
+        assert torch.equal(plan.idxW[:kept.numel()].long(), kept) and int(plan.cntW.item()) == kept.numel()
+    assert took[1] <= 8 * took[0], took
