@@ -507,8 +507,9 @@ __device__ __forceinline__ int tail_tiles(int compute, int K_out)
 
 // grid: 1-D per layer, sized by dgrad_grid.  The first ceil8(compute
 // tiles) ids compute (spread over the XCDs in contiguous runs; the quarters of the last round, if any, behind the whole
-// tiles), the following ones write the zero rows of dropped samples, the rest exit.
-template <int BM, int BN, int WM, int WN, int NS, int SPQ>
+// tiles), the following ones write the zero rows of dropped samples, the rest exit.  QUARTERS: the last round may go out
+// in quarters; the caller has sized the grid for them.
+template <int BM, int BN, int WM, int WN, int NS, int SPQ, bool QUARTERS>
 __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, const uint16_t *__restrict__ W,
                                                 const float *__restrict__ p, const int32_t *__restrict__ idxA,
                                                 const int32_t *__restrict__ cntA, uint16_t *__restrict__ dX, int N,
@@ -517,7 +518,7 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
                                                 const InlineSampleA &sa, float *__restrict__ sq_blocks)
 {
     constexpr int NW = WM * WN, NT = NW * 64, STAGE = (BM + BN) * 128;
-    constexpr bool kTail = BM == 256;   // one workgroup per CU
+    constexpr bool kTail = QUARTERS && BM == 256;   // one workgroup per CU
     static_assert(BM * 128 >= kIdxStaged * 4, "index staging area does not fit a stage of G");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int32_t *row_of = reinterpret_cast<int32_t *>(smem + NS * STAGE);
@@ -580,8 +581,7 @@ __device__ __forceinline__ void dgrad_bf16_body(const uint16_t *__restrict__ G, 
     const int64_t M = (int64_t)cnt * T;
     const int64_t R = (int64_t)N * T;
     const int compute = (int)((M + BM - 1) / BM) * tiles_n;
-    // Tiles of the last round that go out as quarters (not in a launch of siblings: each knows its own count only)
-    const int tail = kTail && gridDim.y == 1 ? tail_tiles(compute, K_out) : 0;
+    const int tail = kTail ? tail_tiles(compute, K_out) : 0;   // tiles of the last round that go out as quarters
     // 8 ids per XCD for each quarter that an XCD gets, 32 at most (a CU each); the ones beyond 32 are second quarters
     const int per_xcd = (4 * tail + 7) / 8;
     const int whole8 = (compute - tail + 7) / 8 * 8, compute8 = whole8 + 8 * min(per_xcd, kTailCUs / 8);
@@ -653,19 +653,19 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void dgrad_bf16_kernel(const uint
                                                                   const uint16_t *__restrict__ J, int fill_dropped,
                                                                   InlineSampleA sa, float *__restrict__ sq_blocks)
 {
-    dgrad_bf16_body<BM, BN, WM, WN, NS, SPQ>(G, W, p, idxA, cntA, dX, N, T, K_in, K_out, tiles_n, J, fill_dropped, sa,
+    dgrad_bf16_body<BM, BN, WM, WN, NS, SPQ, true>(G, W, p, idxA, cntA, dX, N, T, K_in, K_out, tiles_n, J, fill_dropped, sa,
                                              sq_blocks);
 }
 
 // Several layers of one shape whose upstream gradients do not depend on each other (the Q, K and V
-// projections of an attention block) in one launch: blockIdx.y picks the layer, everything else
-// is the kernel above.
+// projections of an attention block) in one launch: blockIdx.y picks the layer, everything else is the kernel above
+// but the quarters (each layer knows its own count only, and what the others leave of the last round is not known).
 template <int BM, int BN, int WM, int WN, int NS, int OCC, int SPQ>
 __global__ __launch_bounds__(WM *WN * 64, OCC) void dgrad_bf16_group_kernel(DgradGroup grp, int N, int T, int K_in,
                                                                         int K_out, int tiles_n, int fill_dropped)
 {
     const DgradProblem &q = grp.prob[blockIdx.y];
-    dgrad_bf16_body<BM, BN, WM, WN, NS, SPQ>(q.G, q.W, q.p, q.idxA, q.cntA, q.dX, N, T, K_in, K_out, tiles_n, q.J,
+    dgrad_bf16_body<BM, BN, WM, WN, NS, SPQ, false>(q.G, q.W, q.p, q.idxA, q.cntA, q.dX, N, T, K_in, K_out, tiles_n, q.J,
                                              fill_dropped, q.sa, q.sq_blocks);
 }
 

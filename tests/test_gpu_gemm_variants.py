@@ -273,3 +273,53 @@ def test_bf16_dgrad_contractions(vb, N, T, K_in, K_out):
     # fp32 sums rounded once to bf16: 2^-9 / sqrt(3) = 1.1e-3; a row or a column alike
     assert float((off.norm(dim=1) / want.norm(dim=1)).max()) <= 5e-3
     assert float((off.norm(dim=0) / want.norm(dim=0)).max()) <= 5e-3
+
+
+# The quartered last round as an entry of a stack reaches it: dropped rows left unwritten (a grid without zero-fill duty) or
+# zeroed, SampleA ahead of dgrad, inside it from the row sums (up to 4096 rows) and from the lane sums of block sums, where a
+# workgroup's second quarter goes on with the kept list in LDS; a list of more than the 1024 samples that are staged.
+# Whole 256x256 tiles in front of the quarters, one quarter to a workgroup (up to 64 tiles), two (up to 128).
+@pytest.mark.parametrize("N,T,K_in,K_out,rho,live,draw,whole,tail,route", [
+    (40, 257, 1608, 1544, 1.0, 40, 0, 256, 31, "swept"), (40, 257, 1608, 1544, 1.0, 40, 0, 256, 31, "blocks"),
+    (40, 257, 1352, 1544, 0.5, 40, 0, 0, 126, "swept"), (40, 257, 1352, 1544, 0.5, 40, 0, 0, 126, "blocks"),
+    (40, 257, 1352, 1536, 0.5, 9, 0, 0, 60, "swept"), (40, 257, 1352, 1536, 0.5, 9, 0, 0, 60, "blocks"),
+    (64, 64, 4040, 1544, 0.6, 64, 9, 0, 128, "swept"), (64, 64, 4040, 1544, 0.6, 15, 0, 0, 64, "swept"),
+    (64, 64, 4040, 1544, 0.6, 64, 9, 0, 128, "blocks"), (1100, 9, 1608, 1544, 1.0, 1100, 0, 256, 17, "swept")])
+@pytest.mark.parametrize("fill", [False, True])
+def test_quarters_of_a_stack_entry(vb, N, T, K_in, K_out, rho, live, draw, whole, tail, route, fill):
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(N + live)
+    G = torch.randn((R, K_out), generator=gen, device="cuda").bfloat16()
+    G.mul_(torch.linspace(1.0, 1.5, N, device="cuda").bfloat16().repeat_interleave(T)[:, None])
+    X = torch.randn((R, K_in), generator=gen, device="cuda").bfloat16()
+    W = (torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02).bfloat16()
+    above = torch.zeros(N, dtype=torch.uint8, device="cuda")
+    above[torch.randperm(N, generator=gen, device="cuda")[:live]] = 1
+    gone = above.repeat_interleave(T) == 0
+    G[gone] = float("nan")    # never read
+    groups = (K_out + 255) // 256
+    squares = torch.zeros((R, groups * 256), device="cuda")
+    squares[:, :K_out] = G.nan_to_num().float().square()
+    blocks = squares.view(R, groups, 4, 64).sum(3).permute(1, 0, 2).contiguous()
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    dX = torch.full((R, K_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    entry = vb.layer_args(shape, G, X, W, rho, 0.5, vb.Rng(7, 1, draw), True, plan, dX, None, ws, kept_above=above,
+                          leave_dropped_rows=not fill, g_sq_blocks=blocks if route == "blocks" else None)
+    vb.vcas_backward_stack(vb.make_stack([entry]), 1, torch.cuda.Stream(), torch.cuda.Stream())
+    torch.cuda.synchronize()
+    norms = torch.where(gone, 0.0, G.nan_to_num().double().square().sum(1)).view(N, T).sum(1).sqrt()
+    assert float((plan.gnorm.double() - norms).abs().max() / norms.max()) <= 1e-5
+    mask, p = plan.maskA.bool(), plan.p
+    kept = int(mask.sum())
+    tiles = (kept * T + 255) // 256 * ((K_in + 255) // 256)
+    assert tiles == whole + tail, (kept, tiles)     # the case is what it says
+    assert bool((mask <= above.bool()).all()) and kept == int(plan.cntA.item())
+    on = mask.repeat_interleave(T)
+    want = (G[on].double() @ W.double()) / p[mask].double().repeat_interleave(T)[:, None]
+    off = dX[on].double() - want
+    # fp32 sums rounded once to bf16: 2^-9 / sqrt(3) = 1.1e-3; a row or a column alike
+    assert float((off.norm(dim=1) / want.norm(dim=1)).max()) <= 5e-3
+    assert float((off.norm(dim=0) / want.norm(dim=0)).max()) <= 5e-3
+    rest = dX[~on]
+    assert bool((rest == 0).all()) if fill else bool(torch.isnan(rest).all())
