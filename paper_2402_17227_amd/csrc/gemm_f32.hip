@@ -167,7 +167,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(const float 
     int stage = 0;
     for (int s = 0; s < steps; ++s) {
         wait_loads_outstanding<(NS - 2) * LOADS>();   // step s has landed, the younger ones may stay in flight
-        asm volatile("" ::: "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage of step s - 1 has been read: its next loads go out now
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         issue(stage == 0 ? NS - 1 : stage - 1, s + NS - 1);
@@ -192,6 +192,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(const float 
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].z, b[q][2], acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].w, b[q][3], acc, 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
         stage = stage + 1 == NS ? 0 : stage + 1;
     }
     wait_loads_outstanding<0>();

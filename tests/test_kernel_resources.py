@@ -1,4 +1,5 @@
-"""What the built kernels take of a CU, from the metadata of the library's own gfx950 code objects (no GPU needed)."""
+"""What the built kernels take of a CU and where they wait, from the metadata and the assembly of the library's own gfx950
+code objects (no GPU needed)."""
 import os
 import re
 import shutil
@@ -11,8 +12,8 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{demangled name: (VGPRs, bytes of scratch per lane)} of every kernel in libvcas.so."""
+def objects(tmp_path_factory):
+    """The gfx950 code objects of libvcas.so, as files."""
     from paper_2402_17227_amd import binding, build
     if not os.path.exists(os.path.join(LLVM, "llvm-readelf")) or not shutil.which("c++filt"):
         pytest.skip("needs the LLVM tools the library is built with")
@@ -22,7 +23,7 @@ def kernels(tmp_path_factory):
     fat = tmp / "fat.bin"
     subprocess.run([f"{LLVM}/llvm-objcopy", "--dump-section", f".hip_fatbin={fat}", binding.LIB_PATH, str(tmp / "copy.so")],
                    check=True)
-    data, found, at = fat.read_bytes(), {}, 0
+    data, found, at = fat.read_bytes(), [], 0
     while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
         entries, pos = struct.unpack_from("<Q", data, at + 24)[0], at + 32
         for _ in range(entries):
@@ -31,14 +32,26 @@ def kernels(tmp_path_factory):
             pos += 24 + length
             if b"gfx950" not in target or not size:
                 continue
-            obj = tmp / "one.co"
-            obj.write_bytes(data[at + offset:at + offset + size])
-            notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(obj)], check=True, capture_output=True, text=True).stdout
-            for block in notes.split("  - .agpr_count:")[1:]:
-                field = lambda key: re.search(rf"\.{key}:\s+(\S+)", block).group(1)
-                name = subprocess.run(["c++filt", field("name")], check=True, capture_output=True, text=True).stdout.strip()
-                found[name] = (int(field("vgpr_count")), int(field("private_segment_fixed_size")))
+            found.append(tmp / f"{len(found)}.co")
+            found[-1].write_bytes(data[at + offset:at + offset + size])
         at += 24
+    assert found
+    return found
+
+
+def _demangled(name):
+    return subprocess.run(["c++filt", name], check=True, capture_output=True, text=True).stdout.strip()
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """{demangled name: (VGPRs, bytes of scratch per lane)} of every kernel."""
+    found = {}
+    for obj in objects:
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(obj)], check=True, capture_output=True, text=True).stdout
+        for block in notes.split("  - .agpr_count:")[1:]:
+            field = lambda key: re.search(rf"\.{key}:\s+(\S+)", block).group(1)
+            found[_demangled(field("name"))] = (int(field("vgpr_count")), int(field("private_segment_fixed_size")))
     assert found
     return found
 
@@ -51,3 +64,27 @@ def test_256x256_dgrad_leaves_registers_for_side_streams(kernels):
     assert len(big) == 2
     for name, (vgprs, scratch) in big.items():
         assert vgprs <= 224 and scratch == 0, (name, vgprs, scratch)
+
+
+def test_fp32_dgrad_gives_a_stage_back_when_it_has_been_read(objects):
+    """Behind a barrier of the main loop the next loads go into the stage of the step before: at every barrier of the
+    LDS-direct fp32 dgrad kernels the wavefront's own LDS reads have been waited for in so many words, not only because the
+    matrix instructions that use them happen to come first."""
+    seen = 0
+    for obj in objects:
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True,
+                              text=True).stdout
+        for body in re.split(r"\n(?=[0-9a-f]+ <)", text):
+            if "dgrad_f32_kernel" not in body.split("\n", 1)[0]:
+                continue
+            code = [line.split("//")[0].strip() for line in body.split("\n")[1:]]
+            code = [c for c in code if c]
+            barriers = [i for i, c in enumerate(code) if c.startswith("s_barrier")]
+            assert barriers
+            for i in barriers:
+                j = i - 1
+                while code[j].startswith("s_waitcnt") and "lgkmcnt(0)" not in code[j]:
+                    j -= 1
+                assert "lgkmcnt(0)" in code[j], code[max(0, i - 6):i + 1]
+            seen += 1
+    assert seen == 3
