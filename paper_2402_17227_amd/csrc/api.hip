@@ -20,19 +20,15 @@ vcas_status row_sumsq_group(const RowNormGroup &grp, int n, int dtype, int64_t R
 vcas_status keep_probs(const float *score, int n, double budget, float *prob, hipStream_t st);
 vcas_status sample_compact(const float *prob, int n, const vcas_rng &rng, uint32_t stream_id, uint8_t *mask,
                            int32_t *idx, int32_t *count, hipStream_t st);
-vcas_status compact_only(const uint8_t *mask, int n, int32_t *idx, int32_t *count, hipStream_t st);
 vcas_status leverage_scores(const float *gsq, const float *xsq, const float *p, const uint8_t *maskA, int64_t R,
                             int T, float *score, hipStream_t st);
 vcas_status row_scale(const float *p, const float *q, const uint8_t *maskW, int64_t R, int T, float *scale,
                       hipStream_t st);
-vcas_status broadcast_data_mask(const uint8_t *maskA, int64_t R, int T, float *q, uint8_t *maskW, hipStream_t st);
 vcas_status sampler_a(const float *gsq, int N, int T, double budget, const vcas_rng &rng, float *gnorm, float *p,
                       uint8_t *maskA, int32_t *idxA, int32_t *cntA, hipStream_t st);
 vcas_status sampler_a_group(const SampleAGroup &grp, int n, int N, int T, hipStream_t st);
-vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq, int N, int T, int token_sampling,
-                            int prepared, hipStream_t st);
-vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int T, hipStream_t st);
-vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *u, hipStream_t st);
+vcas_status sampler_w_group(const SampleWGroup &grp, int n, int N, int T, int token_sampling, int roots_given, hipStream_t st);
+vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int K, int T, hipStream_t st);
 vcas_status row_sumsq_pair(const void *G, int K_out, float *gsq, const void *X, int K_in, float *xsq, int dtype,
                            int64_t R, const vcas_rng &rng, uint32_t stream_id, float *uniforms, float *root_g,
                            float *root_x, int T, const uint8_t *keep_g, hipStream_t st);
@@ -311,7 +307,6 @@ static SampleWProblem sample_w_problem(const vcas_shape &s, double rho, double n
     const WorkspaceLayout l = workspace_layout(&s);
     unsigned char *base = static_cast<unsigned char *>(workspace);
     SampleWProblem w;
-    w.gsq = pl.gsq;
     w.xsq = pl.xsq;
     w.p = pl.p;
     w.maskA = pl.maskA;
@@ -338,7 +333,6 @@ static void put_row_job(RowJobGroup &grp, int i, const vcas_shape &s, const void
     grp.out[i] = pl.xsq;
     grp.job[i] = {token_sampling ? u : nullptr, rng.seed, rng.layer, 1u, rng.draw, rng.draw_offset};
     grp.sj[i] = {pl.gsq, pl.p, pl.score};
-    grp.groups[i] = s.K_in / (16 / elem_bytes(s.dtype));
 }
 
 static float *uniforms_of(const vcas_shape &s, void *workspace)
@@ -439,12 +433,12 @@ static vcas_status weight_half(const vcas_shape &s, const void *G, const void *X
     if (!together) {
         RowJobGroup norms = {};
         put_row_job(norms, 0, s, X, xsq_forward, rng, token_sampling, pl, workspace);
-        VCAS_TRY(row_sumsq_scores_uniforms_group(norms, 1, s.dtype, R, s.T, st));
+        VCAS_TRY(row_sumsq_scores_uniforms_group(norms, 1, s.dtype, R, s.K_in, s.T, st));
     }
     // what the norm passes have left in score and q: roots (together) or the scores themselves
     SampleWGroup sampler = {};
     sampler.prob[0] = sample_w_problem(s, rho, nu, pl, workspace);
-    VCAS_TRY(sampler_w_group(sampler, 1, together ? 1 : 0, s.N, s.T, token_sampling, together ? 1 : 2, st));
+    VCAS_TRY(sampler_w_group(sampler, 1, s.N, s.T, token_sampling, together ? 1 : 0, st));
     if (dW)
         VCAS_TRY(dispatch_wgrad(s, G, X, pl.scaleW, pl.idxW, pl.cntW, dW, workspace, st, kWgradFill,
                                 expected_tokens(s, rho, nu, token_sampling)));
@@ -556,8 +550,8 @@ static vcas_status weight_half_group(const vcas_layer_args *layers, int n, hipSt
         put_row_job(norms, i, a.shape, a.X, a.xsq_forward, a.rng, a.token_sampling, a.plan, a.workspace);
         samplers.prob[i] = sample_w_problem(a.shape, a.rho, a.nu, a.plan, a.workspace);
     }
-    VCAS_TRY(row_sumsq_scores_uniforms_group(norms, n, s.dtype, (int64_t)s.N * s.T, s.T, st));
-    return sampler_w_group(samplers, n, 0, s.N, s.T, layers[0].token_sampling, 2, st);
+    VCAS_TRY(row_sumsq_scores_uniforms_group(norms, n, s.dtype, (int64_t)s.N * s.T, s.K_in, s.T, st));
+    return sampler_w_group(samplers, n, s.N, s.T, layers[0].token_sampling, 0, st);
 }
 
 // Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched launches, fp32 layers
@@ -752,7 +746,6 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
             a.idxA = idxA;
             a.cntA = cntA;
             SampleWProblem &sw = group_w.prob[k];
-            sw.gsq = pl.gsq;
             sw.xsq = pl.xsq;
             sw.p = p;
             sw.maskA = maskA;
@@ -792,7 +785,7 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
             }
         }
         VCAS_TRY(probe_draws(draws, n, pl.gsq, pl.xsq, scale_a, R, s.T, base, st));
-        VCAS_TRY(sampler_w_group(group_w, n, 0, s.N, s.T, 1, 2, st));
+        VCAS_TRY(sampler_w_group(group_w, n, s.N, s.T, 1, 0, st));
         VCAS_TRY(probe_closed(draws, n, R, s.N, s.T, pl.xsq, last, st));
         const double weight = 1.0 / (double)M;
         bool large = true;

@@ -737,11 +737,15 @@ enum DgradTile { kTile256, kTile128, kTile64, kTile128Whole, kTile64Whole };
 //    9.7, 10.5 us and reading ahead 7.1, 7.9, 8.7, 9.7, 10.2; 192 tiles 7.6, 9.0, 9.3, 10.0, 11.5 and 8.2, 9.0, 9.4, 10.1,
 //    11.0.
 //  - else one tile per CU and nothing else to hide its latencies: the kernels that read whole steps ahead
-//    (kWholeStep), 64x128 up to 200 tiles, 128x128 up to 224.  768->3072 transposed, i.e. K_out 3072 and
-//    K_in 768: 2048 rows, 192 or 96 tiles, 18 and 21 us (64x128 without reading ahead 23); 4096 rows,
-//    384 or 192 tiles, 35 and 24 us (30 with two 64x128 workgroups per CU).
-//  - two workgroups per CU: 64x128 up to 256 tiles of 128x128, 128x128 beyond (1024->1024: 4096 rows,
-//    512 or 256 tiles, 18 us both, 22 reading ahead; 8192 rows, 30 and 24 us).
+//    (kWholeStep), 64x128 up to 200 tiles, 128x128 up to 224.  A second round costs more than the better tile gains, and
+//    more samples may be kept than expected, so the lines lie that much below 256.  K_in 1024, contraction 1024 and 3072:
+//      64x128 tiles     192          240          256          288             128x128 tiles  192          240          256          288
+//      64x128 ahead   9.4  18.6    9.7  19.3   10.1  20.2   16.1  35.3
+//      64x128        12.0  27.4   12.3  27.9   12.4  28.1   12.6  28.4                      12.9  28.7   13.4  30.8   13.7  31.4   17.3  45.6
+//      128x128 ahead 10.4  21.2   10.6  21.5   10.6  21.5   10.7  21.9                      11.0  23.4   12.2  26.4   13.1  28.2   20.4  46.0
+//      128x128                                                                              15.3  35.5   16.1  36.6   16.1  36.6   16.6  38.4
+//  - two workgroups per CU: 64x128 up to 256 tiles of 128x128, 128x128 beyond (the last columns; 8192 rows, 512 tiles, 30
+//    and 24 us).
 static DgradTile dgrad_tile(int64_t rows, int K_in, int K_out, int n, bool rows_known)
 {
     auto tiles = [&](int bm, int bn) { return n * ((rows + bm - 1) / bm) * ((K_in + bn - 1) / bn); };

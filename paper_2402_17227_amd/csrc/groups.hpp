@@ -48,7 +48,6 @@ struct WgradItem {
 
 // One layer of a grouped SampleW launch: the pointer arguments of the one-workgroup sampler.
 struct SampleWProblem {
-    const float *gsq;
     float *xsq;
     const float *p;
     const uint8_t *maskA;
@@ -72,9 +71,8 @@ struct RowNormGroup {
     const uint8_t *keep[kMaxSiblings];
 };
 
-// Row norms with their side jobs (SampleW's scores and uniforms) for up to kMaxSamplers matrices with one number
-// of rows in one launch; groups: 16-byte groups per row of each.  Where norms is set, the sums of squares of
-// every row are read there and the matrix is not.
+// Row norms with their side jobs (SampleW's scores and uniforms) for up to kMaxSamplers matrices of one shape
+// in one launch.  Where norms is set, the sums of squares of every row are read there and the matrix is not.
 struct RowJobGroup {
     const uint4 *A[kMaxSamplers];
     const float *norms[kMaxSamplers];
@@ -82,7 +80,6 @@ struct RowJobGroup {
     float *out[kMaxSamplers];
     UniformJob job[kMaxSamplers];
     ScoreJob sj[kMaxSamplers];
-    int32_t groups[kMaxSamplers];
 };
 
 }  // namespace vcas

@@ -74,14 +74,13 @@ __device__ __forceinline__ void cached_xsq_scores_body(const float *__restrict__
     }
 }
 
-// The same, side jobs included, for several matrices with R rows each: blockIdx.y picks the matrix.  CH covers
-// the longest rows.
+// The same, side jobs included, for several matrices of one shape: blockIdx.y picks the matrix.
 template <bool BF16, int CH>
-__global__ __launch_bounds__(256) void row_sumsq_jobs_group_kernel(RowJobGroup grp, int64_t R, int T)
+__global__ __launch_bounds__(256) void row_sumsq_jobs_group_kernel(RowJobGroup grp, int64_t R, int groups_per_row, int T)
 {
     const int z = blockIdx.y;
     if (grp.norms[z]) cached_xsq_scores_body(grp.norms[z], R, T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
-    else row_sumsq_body<BF16, CH>(grp.A[z], R, grp.groups[z], T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
+    else row_sumsq_body<BF16, CH>(grp.A[z], R, groups_per_row, T, grp.keep[z], grp.out[z], grp.job[z], grp.sj[z]);
 }
 
 // Row sums of squares alone, for several matrices of one shape in one launch: blockIdx.y picks the matrix.
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(256) void rows_from_blocks_kernel(const float4 *__r
 }
 
 // The same for a stack whose dgrad decides SampleA itself: row sums, and of the sample norms what is left when
-// the rows are summed, the 64 lane sums of sample_norm_wave (lane l adds the rows t = l mod 64 of its
+// the rows are summed, the 64 lane sums of sample_norms_batched (lane l adds the rows t = l mod 64 of its
 // sample in ascending t); the tree over the lanes and the root are left to the reader.  A sample is
 // cut by lanes, L to a workgroup, so that N samples are 64/L N workgroups and nothing is exchanged
 // between them: with one workgroup per sample (an earlier version) a CU has to pull a whole sample's
@@ -307,19 +306,19 @@ static vcas_status launch_row_sumsq_group(const RowNormGroup &grp, int n, int64_
     return launch_status();
 }
 
-// Row norms of X on kept samples, the SampleW scores and the uniforms of n <= kMaxSamplers layers with R rows
-// each and one dtype in one launch
-vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int T, hipStream_t st)
+// Row norms of X [R, K] on kept samples, the SampleW scores and the uniforms of n <= kMaxSamplers layers in one launch
+vcas_status row_sumsq_scores_uniforms_group(const RowJobGroup &grp, int n, int dtype, int64_t R, int K, int T, hipStream_t st)
 {
     if (n < 1 || n > kMaxSamplers) return VCAS_EINVAL;
     const bool bf = dtype == VCAS_BF16;
-    int need = 0;
+    const int groups = K / (bf ? 8 : 4);
+    int need = 0;   // chunks of a row; 0: no matrix is read
     for (int i = 0; i < n; ++i)
-        if (!grp.norms[i] && (grp.groups[i] + 63) / 64 > need) need = (grp.groups[i] + 63) / 64;
+        if (!grp.norms[i]) need = (groups + 63) / 64;
     const int64_t blocks64 = need ? (R + 3) / 4 : (R + 255) / 256;
     const int blocks = (int)(blocks64 < 4096 ? blocks64 : 4096);
 #define VCAS_LAUNCH_CH(B, C) \
-    hipLaunchKernelGGL((row_sumsq_jobs_group_kernel<B, C>), dim3(blocks, n), dim3(256), 0, st, grp, R, T)
+    hipLaunchKernelGGL((row_sumsq_jobs_group_kernel<B, C>), dim3(blocks, n), dim3(256), 0, st, grp, R, groups, T)
 #define VCAS_LAUNCH_DT(C)          \
     do {                           \
         if (bf) VCAS_LAUNCH_CH(true, C); \

@@ -9,27 +9,10 @@
 
 namespace vcas {
 
-// ||G_i||_F from the T squared row norms of sample i, by one wavefront (every lane returns it):
-// value t belongs to lane t mod 64, plain fp32 adds in ascending t, exchange tree, correctly
-// rounded sqrt.  Eight loads are in flight at a time (a lane's values past the end re-read the
-// last one and count as +0, which leaves the sum as it is).
-__device__ __forceinline__ float sample_norm_wave(const float *__restrict__ row, int T)
-{
-    const int lane = threadIdx.x & 63;
-    float acc = 0.0f;
-    for (int t0 = lane; t0 < T; t0 += 512) {
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = row[min(t0 + 64 * k, T - 1)];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc = acc + (t0 + 64 * k < T ? v[k] : 0.0f);
-    }
-    return __builtin_sqrtf(wave_exchange_sum(acc));
-}
-
-// The same norms for several samples of one wavefront at a time, so that their loads overlap:
-// samples first, first + stride, ... (< N), B at a time with K loads per lane and sample in flight;
-// out[i] = ||G_i||_F.  Same additions in the same order as sample_norm_wave.
+// ||G_i||_F from the T squared row norms of sample i, several samples of one wavefront at a time so that their loads
+// overlap: samples first, first + stride, ... (< N), B at a time with K loads per lane and sample in flight;
+// out[i] = ||G_i||_F.  Value t of a sample belongs to lane t mod 64, plain fp32 adds in ascending t, exchange tree, correctly
+// rounded sqrt (a lane's values past the end re-read the last one and count as +0, which leaves the sum as it is).
 template <int B, int K>
 __device__ __forceinline__ void sample_norms_batched(const float *__restrict__ gsq, int first, int stride, int N,
                                                      int T, float *__restrict__ out)
@@ -117,7 +100,7 @@ __device__ __forceinline__ SampleADecision sample_a_wave(float a, int N, double 
 // random stream, and where the plan's SampleA fields go (written by one workgroup).
 struct InlineSampleA {
     const float *gsq;     // row sums of squares of G: the sample norms are taken here too,
-    const float *lanes;   // or [N][64] lane sums of the row sums (the sums of sample_norm_wave before its tree); both null: off
+    const float *lanes;   // or [N][64] lane sums of the row sums (the sums of sample_norms_batched before their tree); both null: off
     double budget;
     uint64_t seed;
     uint32_t layer, draw;

@@ -285,12 +285,9 @@ __device__ __forceinline__ void sampler_a_fast_body(const float *__restrict__ gs
 
 // ---- SampleW --------------------------------------------------------------------------------
 
-// What the caller has already left in the score and q arrays when SampleW starts.
-enum : int {
-    kFromSquares = 0,   // nothing: scores come from gsq, xsq and p
-    kRootsGiven = 1,    // score[t] = sqrt(gsq[t]), q[t] = sqrt(xsq[t]) for every row
-    kScoresGiven = 2,   // score[t] is final (0 on dropped samples, whose xsq is 0 already)
-};
+// What the norm passes have left in the score and q arrays when SampleW starts (`roots_given`): the square roots of
+// gsq and xsq for every row, taken before SampleA, and xsq itself is still there on dropped samples; or the scores,
+// final (0 on dropped samples, whose xsq is 0 already).
 
 // t / T for t * T < 2^32 with a multiplier the wavefront computes once (T > 1):
 // t * (floor(2^32 / T) + 1) / 2^32 = t / T + t * e / 2^32 with 0 < e <= 1, and
@@ -340,12 +337,11 @@ __device__ __forceinline__ void sample_w_finish(const float (&a)[E], const float
 // SampleW for R <= 1024*E (one workgroup of 1024).  The whole vector is this one
 // workgroup's arithmetic, so everything per sample (1/p_i, the keep byte) is
 // computed once into LDS when N <= 1024, and the square roots come from the
-// many-workgroup norm pass when the caller says so (`prepared`).
+// many-workgroup norm pass.
 template <int E>
-__device__ __forceinline__ void sampler_w_fast_body(const float *__restrict__ gsq, float *__restrict__ xsq,
-                                                    int zero_dropped_xsq, const float *__restrict__ p,
+__device__ __forceinline__ void sampler_w_fast_body(float *__restrict__ xsq, const float *__restrict__ p,
                                                     const uint8_t *__restrict__ maskA, const float *__restrict__ u,
-                                                    int N, int T, double budget, int token_sampling, int prepared,
+                                                    int N, int T, double budget, int token_sampling, int roots_given,
                                                     float *__restrict__ score, float *__restrict__ q,
                                                     uint8_t *__restrict__ maskW, float *__restrict__ scaleW,
                                                     int32_t *__restrict__ idxW, int32_t *__restrict__ cntW)
@@ -362,13 +358,8 @@ __device__ __forceinline__ void sampler_w_fast_body(const float *__restrict__ gs
     for (int j = 0; j < E; ++j) {
         const int t = min(tid + 1024 * j, R - 1);
         uu[j] = token_sampling ? u[t] : 0.0f;
-        if (prepared == kFromSquares) {
-            a[j] = gsq[t];
-            rx[j] = xsq[t];
-        } else {
-            a[j] = score[t];
-            rx[j] = prepared == kRootsGiven ? q[t] : 0.0f;
-        }
+        a[j] = score[t];
+        rx[j] = roots_given ? q[t] : 0.0f;
     }
     if (tabled) {
         if (tid < N) {
@@ -385,17 +376,16 @@ __device__ __forceinline__ void sampler_w_fast_body(const float *__restrict__ gs
         const int t = tid + 1024 * j;
         if (t >= R) {
             a[j] = 0.0f;
-        } else if (prepared != kScoresGiven) {
+        } else if (roots_given) {
             const int i = sample_of(t, T, magic);
             const bool keep = tabled ? table.keep[i] != 0 : maskA[i] != 0;
-            const float rg = prepared == kRootsGiven ? a[j] : __builtin_sqrtf(a[j]);
-            const float rxx = prepared == kRootsGiven ? rx[j] : __builtin_sqrtf(rx[j]);
+            const float rg = a[j];
             a[j] = 0.0f;
             if (keep) {
                 const float inv = tabled ? table.pinv[i] : 1.0f / p[i];
                 const float s1 = inv * rg;
-                a[j] = s1 * rxx;
-            } else if (zero_dropped_xsq) {
+                a[j] = s1 * rx[j];
+            } else {
                 xsq[t] = 0.0f;
             }
             score[t] = a[j];

@@ -169,17 +169,6 @@ __global__ __launch_bounds__(256) void row_scale_kernel(const float *__restrict_
     scale[t] = maskW[t] ? 1.0f / (p[i] * q[t]) : 0.0f;
 }
 
-// "SampleA only" token plan: every token of a kept sample is kept with q = 1.
-__global__ __launch_bounds__(256) void broadcast_data_mask_kernel(const uint8_t *__restrict__ maskA, int64_t R, int T,
-                                                                  float *__restrict__ q, uint8_t *__restrict__ maskW)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= R) return;
-    const uint8_t m = maskA[t / T] ? 1 : 0;
-    q[t] = m ? 1.0f : 0.0f;
-    maskW[t] = m;
-}
-
 // ---- fused single-workgroup samplers (used by vcas_linear_backward) -----------
 // The vectors are at most R floats, so one workgroup of 1024 threads does the
 // whole decision chain of a sampler in one launch instead of five.
@@ -205,12 +194,12 @@ __global__ __launch_bounds__(1024) void sampler_a_group_kernel(SampleAGroup grp,
 
 // SampleW of up to kMaxSamplers layers of one shape, one workgroup per layer.
 template <int E>
-__global__ __launch_bounds__(1024) void sampler_w_group_kernel(SampleWGroup grp, int zero_dropped_xsq, int N, int T,
-                                                               int token_sampling, int prepared)
+__global__ __launch_bounds__(1024) void sampler_w_group_kernel(SampleWGroup grp, int N, int T, int token_sampling,
+                                                               int roots_given)
 {
     const SampleWProblem &w = grp.prob[blockIdx.x];
-    sampler_w_fast_body<E>(w.gsq, w.xsq, zero_dropped_xsq, w.p, w.maskA, w.u, N, T, w.budget, token_sampling, prepared,
-                           w.score, w.q, w.maskW, w.scaleW, w.idxW, w.cntW);
+    sampler_w_fast_body<E>(w.xsq, w.p, w.maskA, w.u, N, T, w.budget, token_sampling, roots_given, w.score, w.q, w.maskW,
+                           w.scaleW, w.idxW, w.cntW);
 }
 
 // SampleA: ||G_i||_F from gsq, p, Bernoulli mask over samples, kept list.
@@ -238,17 +227,6 @@ __global__ __launch_bounds__(1024) void sampler_a_kernel(const float *__restrict
     compact_block(maskA, N, idxA, cntA);
 }
 
-// Uniforms of SampleW for every row (independent of the data, so they are
-// drawn by many workgroups while the row norms stream).
-__global__ __launch_bounds__(256) void uniforms_kernel(int64_t R, uint64_t seed, uint32_t layer, uint32_t stream_id,
-                                                       uint32_t draw, const uint32_t *__restrict__ draw_offset,
-                                                       float *__restrict__ u)
-{
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (draw_offset) draw += *draw_offset;
-    if (r < R) u[r] = philox_uniform(seed, layer, stream_id, draw, (uint32_t)r);
-}
-
 // ---- SampleW of more rows than one workgroup's registers hold comfortably ----------------------
 // Only the rounds of the keep probabilities need the whole vector in one place.  Launches: scores
 // (many workgroups, where the norm pass has not written them), the rounds (one workgroup: reads R
@@ -256,8 +234,8 @@ __global__ __launch_bounds__(256) void uniforms_kernel(int64_t R, uint64_t seed,
 // workgroups), the kept list (many workgroups).  One workgroup for all of it took 227 us at R = 65536 from memory and 132 us with
 // the scores in (spilling) registers; see sampler_w_group for the line.
 
-__global__ __launch_bounds__(256) void sampler_w_scores_kernel(SampleWGroup grp, int R, int T, int prepared,
-                                                               int zero_dropped_xsq)
+// From the square roots that the norm pass has left.
+__global__ __launch_bounds__(256) void sampler_w_scores_kernel(SampleWGroup grp, int R, int T)
 {
     const SampleWProblem &w = grp.prob[blockIdx.y];
     const int t = blockIdx.x * 256 + threadIdx.x;
@@ -266,9 +244,9 @@ __global__ __launch_bounds__(256) void sampler_w_scores_kernel(SampleWGroup grp,
     float s = 0.0f;
     if (w.maskA[i]) {
         const float inv = 1.0f / w.p[i];
-        const float a = inv * (prepared == kRootsGiven ? w.score[t] : __builtin_sqrtf(w.gsq[t]));
-        s = a * (prepared == kRootsGiven ? w.q[t] : __builtin_sqrtf(w.xsq[t]));
-    } else if (zero_dropped_xsq) {
+        const float a = inv * w.score[t];
+        s = a * w.q[t];
+    } else {
         w.xsq[t] = 0.0f;
     }
     w.score[t] = s;
@@ -434,12 +412,6 @@ vcas_status sample_compact(const float *prob, int n, const vcas_rng &rng, uint32
     return launch_status();
 }
 
-vcas_status compact_only(const uint8_t *mask, int n, int32_t *idx, int32_t *count, hipStream_t st)
-{
-    hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(1024), 0, st, mask, n, idx, count);
-    return launch_status();
-}
-
 vcas_status leverage_scores(const float *gsq, const float *xsq, const float *p, const uint8_t *maskA, int64_t R,
                             int T, float *score, hipStream_t st)
 {
@@ -453,13 +425,6 @@ vcas_status row_scale(const float *p, const float *q, const uint8_t *maskW, int6
 {
     hipLaunchKernelGGL(row_scale_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, st, p, q, maskW, R, T,
                        scale);
-    return launch_status();
-}
-
-vcas_status broadcast_data_mask(const uint8_t *maskA, int64_t R, int T, float *q, uint8_t *maskW, hipStream_t st)
-{
-    hipLaunchKernelGGL(broadcast_data_mask_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, st, maskA, R, T,
-                       q, maskW);
     return launch_status();
 }
 
@@ -483,13 +448,6 @@ vcas_status sampler_a_group(const SampleAGroup &grp, int n, int N, int T, hipStr
     return launch_status();
 }
 
-vcas_status uniforms(int64_t R, const vcas_rng &rng, uint32_t stream_id, float *u, hipStream_t st)
-{
-    hipLaunchKernelGGL(uniforms_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, st, R, rng.seed, rng.layer,
-                       stream_id, rng.draw, rng.draw_offset, u);
-    return launch_status();
-}
-
 // Norm pass, apply and list of one layer with cached norms, mask bytes against counts: 65536 rows 8.0 and 9.1 us, 131072 9.4
 // and 9.5, 262144 12.6 and 11.0, 2^20 37 and 23, 2^24 5351 and 347.
 constexpr int kListRows = 131072;
@@ -497,16 +455,15 @@ constexpr int kListRows = 131072;
 // SampleW of n <= kMaxSamplers layers with one N and T in one set of launches.  Up to 16384 rows one
 // workgroup per layer does everything; beyond, see sampler_w_rule_kernel and what
 // follows it.
-vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq, int N, int T, int token_sampling,
-                            int prepared, hipStream_t st)
+vcas_status sampler_w_group(const SampleWGroup &grp, int n, int N, int T, int token_sampling, int roots_given, hipStream_t st)
 {
     const int64_t R64 = (int64_t)N * T;
     if (n < 1 || n > kMaxSamplers || R64 > (int64_t)1 << 30) return VCAS_EINVAL;
     const int R = (int)R64;
 #define VCAS_SAMPLER_W(E) \
     if (R <= 1024 * (E)) { \
-        hipLaunchKernelGGL(sampler_w_group_kernel<E>, dim3(n), dim3(1024), 0, st, grp, zero_dropped_xsq, N, T, \
-                           token_sampling, prepared); \
+        hipLaunchKernelGGL(sampler_w_group_kernel<E>, dim3(n), dim3(1024), 0, st, grp, N, T, token_sampling, \
+                           roots_given); \
         return launch_status(); \
     }
     VCAS_SAMPLER_W(1)
@@ -514,8 +471,7 @@ vcas_status sampler_w_group(const SampleWGroup &grp, int n, int zero_dropped_xsq
     VCAS_SAMPLER_W(8)
     VCAS_SAMPLER_W(16)
 #undef VCAS_SAMPLER_W
-    if (prepared != kScoresGiven)
-        hipLaunchKernelGGL(sampler_w_scores_kernel, dim3((R + 255) / 256, n), dim3(256), 0, st, grp, R, T, prepared, zero_dropped_xsq);
+    if (roots_given) hipLaunchKernelGGL(sampler_w_scores_kernel, dim3((R + 255) / 256, n), dim3(256), 0, st, grp, R, T);
     if (token_sampling) {
         if (R <= 32768) hipLaunchKernelGGL(sampler_w_rule_kernel<32>, dim3(n), dim3(1024), 0, st, grp, R);
         else if (R <= 65536) hipLaunchKernelGGL(sampler_w_rule_kernel<64>, dim3(n), dim3(1024), 0, st, grp, R);

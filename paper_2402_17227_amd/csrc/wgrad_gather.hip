@@ -11,8 +11,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void wgrad_gather_kernel(GatherBat
     for (int i = 1; i < batch.n; ++i)
         if ((int)blockIdx.x >= batch.task[i].first_wg) p = i;
     const GatherTask &q = batch.task[p];
-    if (q.row_scale) wgrad_gather_body<BF16, PA, PB, SK, WM, WN, WK, DIFF, true>(q, (int)blockIdx.x - q.first_wg);
-    else wgrad_gather_body<BF16, PA, PB, SK, WM, WN, WK, DIFF, false>(q, (int)blockIdx.x - q.first_wg);
+    wgrad_gather_body<BF16, PA, PB, SK, WM, WN, WK, DIFF>(q, (int)blockIdx.x - q.first_wg);
 }
 
 int gather_tiles(int dtype, int K_out, int K_in, bool large)

@@ -45,8 +45,8 @@ __device__ __forceinline__ int tile_swz(int k)
 // One product of a launch (device view).
 struct GatherTask {
     const void *G, *X;           // [R,K_out], [R,K_in]
-    const float *row_scale;      // by token; null: 1
-    const int32_t *idx, *cnt;    // kept list and its length; idx null: every token in order, *cnt of them
+    const float *row_scale;      // by token
+    const int32_t *idx, *cnt;    // kept list and its length
     float *dst, *partials;       // dW, and [split][K_out][K_in] where more than one slice is active
     const float *exact;          // DIFF: the matrix the product is compared with,
     double *sq_out;              //       and one sum of squared differences per tile
@@ -65,7 +65,7 @@ __device__ __forceinline__ void lds_direct_load4(i32x4 desc, uint32_t lds_base, 
 
 // WM x WN wavefronts share the tile, WK of them each block: they take different parts of every step
 // and their sums meet in LDS at the end, in wavefront order.
-template <bool BF16, int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF, bool SCALED>
+template <bool BF16, int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF>
 __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local_id)
 {
     constexpr int NW = WM * WN * WK, E = BF16 ? 2 : 4;
@@ -125,8 +125,7 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
     auto load_tokens = [&](int st) {   // wavefront 0: the tokens of step st into their table
         if (wave == 0 && st < steps) {
             const int k = (s_begin + st) * SK + lane;   // lanes past SK fetch ahead, and nobody reads what they fetched
-            if (q.idx) lds_direct_load4(descI, __builtin_amdgcn_readfirstlane(lds0 + TOK_AT + (st & 3) * 256), (uint32_t)k * 4u);
-            else tok[(st & 3) * 64 + lane] = k;
+            lds_direct_load4(descI, __builtin_amdgcn_readfirstlane(lds0 + TOK_AT + (st & 3) * 256), (uint32_t)k * 4u);
         }
     };
     // byte offsets of step st's loads, from its tokens (which have landed)
@@ -146,10 +145,8 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
             const bool in = k0 + b_k[j] < cnt && t < (uint32_t)R && b_col[j] != kOutside;
             b_off[j] = in ? t * (uint32_t)(K_in * E) + b_col[j] : kOutside;
         }
-        if (SCALED) {
-            const uint32_t t = (uint32_t)t_of[lane];
-            s_off = k0 + lane < cnt && t < (uint32_t)R ? t * 4u : kOutside;
-        }
+        const uint32_t t = (uint32_t)t_of[lane];
+        s_off = k0 + lane < cnt && t < (uint32_t)R ? t * 4u : kOutside;
     };
     auto issue = [&](int st) {   // tiles and scales of step st at the offsets aimed at
         if (st >= steps) return;
@@ -159,7 +156,7 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
 #pragma unroll
         for (int j = 0; j < BI; ++j)
             lds_direct_load16(descX, __builtin_amdgcn_readfirstlane(lds0 + (st & 1) * STAGE + B_AT + (wave * BI + j) * 1024), b_off[j], 0u);
-        if (SCALED && wave == NW - 1)
+        if (wave == NW - 1)
             lds_direct_load4(descS, __builtin_amdgcn_readfirstlane(lds0 + SCL_AT + (st & 3) * 256), s_off);
     };
     auto landed = [&]() {
@@ -209,10 +206,8 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
             for (int i = 0; i < TM; ++i) a[z & 1][0][i] = frag(tileA, std::integral_constant<int, PA>(), wm0 + i * 32);
 #pragma unroll
             for (int i = 0; i < TN; ++i) b[z & 1][0][i] = frag(tileB, std::integral_constant<int, PB>(), wn0 + i * 32);
-            if constexpr (SCALED) {
-                s4[z & 1][0] = *reinterpret_cast<const float4 *>(sc + part * 16 + (blk >> 1) * 8);
-                s4[z & 1][1] = *reinterpret_cast<const float4 *>(sc + part * 16 + (blk >> 1) * 8 + 4);
-            }
+            s4[z & 1][0] = *reinterpret_cast<const float4 *>(sc + part * 16 + (blk >> 1) * 8);
+            s4[z & 1][1] = *reinterpret_cast<const float4 *>(sc + part * 16 + (blk >> 1) * 8 + 4);
         } else {
             // half h of the wavefront takes tokens 4h + e of the part, e < 4: the order of the contraction
             // is free, and the four scales of a half are then one 16-byte read
@@ -228,12 +223,12 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
 #pragma unroll
                 for (int i = 0; i < TN; ++i) b[z & 1][e][i] = cell(tileB, PB, wn0 + i * 32 + r32, k);
             }
-            if constexpr (SCALED) s4[z & 1][0] = *reinterpret_cast<const float4 *>(sc + 8 * part + 4 * h);
+            s4[z & 1][0] = *reinterpret_cast<const float4 *>(sc + 8 * part + 4 * h);
         }
     };
     auto mma = [&](int z) {
         const float4 *sv = s4[z & 1];
-        if constexpr (BF16 && SCALED) {
+        if constexpr (BF16) {
             auto scaled = [&](bf16x8 v) {
                 u32x4 w = __builtin_bit_cast(u32x4, v);
                 w[0] = pack_bf16(bf16_lo(w[0]) * sv[0].x, bf16_hi(w[0]) * sv[0].y);
@@ -250,7 +245,7 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
                 for (int i = 0; i < TN; ++i) b[z & 1][0][i] = scaled(b[z & 1][0][i]);
             }
         }
-        if constexpr (!BF16 && SCALED) {
+        if constexpr (!BF16) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 a[z & 1][0][i] = a[z & 1][0][i] * sv[0].x;
