@@ -726,7 +726,7 @@ static vcas_status launch_dgrad_group(const vcas_shape &s, const DgradGroup &grp
 
 enum DgradTile { kTile256, kTile128, kTile64, kTile128Whole, kTile64Whole };
 
-// Which kernel for n layers of `rows` kept rows each.  The larger tile moves fewer operand bytes per
+// Which kernel for n layers of `rows` kept rows each, of R.  The larger tile moves fewer operand bytes per
 // flop (loads into LDS and fragment reads out of it, not MFMAs, bound the smaller ones), so the largest
 // that still fills the chip wins:
 //  - 256x256 (one workgroup of eight wavefronts per CU) from 128 tiles up, half the CUs: inside a stack
@@ -738,19 +738,24 @@ enum DgradTile { kTile256, kTile128, kTile64, kTile128Whole, kTile64Whole };
 //    11.0.
 //  - else one tile per CU and nothing else to hide its latencies: the kernels that read whole steps ahead
 //    (kWholeStep), 64x128 up to 200 tiles, 128x128 up to 224.  A second round costs more than the better tile gains, and
-//    more samples may be kept than expected, so the lines lie that much below 256.  K_in 1024, contraction 1024 and 3072:
+//    more samples may be kept than expected, so the lines lie that much below 256; 64x128 tiles of ALL rows up to 256
+//    are no risk.  K_in 1024, contraction 1024 and 3072, every row kept, us:
 //      64x128 tiles     192          240          256          288             128x128 tiles  192          240          256          288
 //      64x128 ahead   9.4  18.6    9.7  19.3   10.1  20.2   16.1  35.3
 //      64x128        12.0  27.4   12.3  27.9   12.4  28.1   12.6  28.4                      12.9  28.7   13.4  30.8   13.7  31.4   17.3  45.6
 //      128x128 ahead 10.4  21.2   10.6  21.5   10.6  21.5   10.7  21.9                      11.0  23.4   12.2  26.4   13.1  28.2   20.4  46.0
 //      128x128                                                                              15.3  35.5   16.1  36.6   16.1  36.6   16.6  38.4
+//    Forty draws of a sampled layer, 64x128 and 128x128 ahead: 32 samples, keep ratio 0.5, contraction 3072: 200 tiles expected
+//    20.2 and 22.6, 216 23.0 and 22.7, 232 24.8 and 22.9; 13 samples of 130 rows, 1128 columns, contraction 3376, 207
+//    expected and 243 of all rows 25.5 and 30.6.
 //  - two workgroups per CU: 64x128 up to 256 tiles of 128x128, 128x128 beyond (the last columns; 8192 rows, 512 tiles, 30
 //    and 24 us).
-static DgradTile dgrad_tile(int64_t rows, int K_in, int K_out, int n, bool rows_known)
+static DgradTile dgrad_tile(int64_t rows, int64_t R, int K_in, int K_out, int n, bool rows_known)
 {
-    auto tiles = [&](int bm, int bn) { return n * ((rows + bm - 1) / bm) * ((K_in + bn - 1) / bn); };
+    auto tiles_of = [&](int64_t m, int bm, int bn) { return n * ((m + bm - 1) / bm) * ((K_in + bn - 1) / bn); };
+    auto tiles = [&](int bm, int bn) { return tiles_of(rows, bm, bn); };
     if (tiles(256, 256) >= (rows_known ? 128 : 192)) return kTile256;
-    if (K_out >= 512 && tiles(64, 128) <= 200) return kTile64Whole;
+    if (K_out >= 512 && (tiles(64, 128) <= 200 || tiles_of(R, 64, 128) <= 256)) return kTile64Whole;
     if (K_out >= 512 && tiles(128, 128) <= 224) return kTile128Whole;
     return tiles(128, 128) > 256 ? kTile128 : kTile64;
 }
@@ -768,7 +773,7 @@ vcas_status dgrad_bf16_group(const vcas_shape &s, const DgradProblem *probs, int
     }
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    switch (dgrad_tile(rows, s.K_in, s.K_out, n, true)) {
+    switch (dgrad_tile(rows, R, s.K_in, s.K_out, n, true)) {
     case kTile256: return launch_dgrad_group<256, 256, 2, 4, 2, 1, -1>(s, grp, n, fill, st);
     case kTile64Whole: return launch_dgrad_group<64, 128, 2, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
     case kTile128Whole: return launch_dgrad_group<128, 128, 4, 2, 4, 1, kWholeStep>(s, grp, n, fill, st);
@@ -795,7 +800,7 @@ vcas_status dgrad_bf16(const vcas_shape &s, const void *G, const void *W, const 
     }
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    switch (dgrad_tile(rows, s.K_in, s.K_out, 1, expected_rows > 0)) {
+    switch (dgrad_tile(rows, R, s.K_in, s.K_out, 1, expected_rows > 0)) {
     case kTile256: return launch_dgrad<256, 256, 2, 4, 2, 1, -1>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
     case kTile64Whole: return launch_dgrad<64, 128, 2, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);
     case kTile128Whole: return launch_dgrad<128, 128, 4, 2, 4, 1, kWholeStep>(s, G, W, p, idxA, cntA, dX, J, fill, sa, sq_blocks, st);

@@ -251,9 +251,9 @@ def test_fp32_dgrad_tiles(vb, N, T, K_in, K_out, kept, jacobian):
 
 
 # bf16 dgrad on both sides of the contraction length from which it reads whole steps ahead (512: eight steps), full and
-# ragged last steps, 64x128 and 128x128 tiles of either kind
+# ragged last steps, 64x128 and 128x128 tiles of either kind; 243 and 261 tiles of 64x128, about one to a CU
 @pytest.mark.parametrize("K_out", [8, 64, 72, 128, 136, 504, 512, 520, 568, 576, 640, 1032])
-@pytest.mark.parametrize("N,T,K_in", [(5, 41, 200), (9, 233, 776), (11, 233, 1544)])
+@pytest.mark.parametrize("N,T,K_in", [(5, 41, 200), (9, 233, 776), (11, 233, 1544), (13, 130, 1128), (13, 140, 1128)])
 def test_bf16_dgrad_contractions(vb, N, T, K_in, K_out):
     R = N * T
     shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
@@ -323,3 +323,27 @@ def test_quarters_of_a_stack_entry(vb, N, T, K_in, K_out, rho, live, draw, whole
     assert float((off.norm(dim=0) / want.norm(dim=0)).max()) <= 5e-3
     rest = dX[~on]
     assert bool((rest == 0).all()) if fill else bool(torch.isnan(rest).all())
+
+
+def test_dgrad_tile_where_few_tiles_cannot_become_a_second_round(vb):
+    """207 tiles of 64x128 are expected, 243 are all there can be: one to a CU, half the rows of the 128x128 tile.  The larger
+    tile (99 of them at work) took 1.2 times as long."""
+    N, T, K_in, K_out = 13, 130, 1128, 3376
+    R = N * T
+    shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
+    G = torch.randn((R, K_out), device="cuda").bfloat16()
+    X = torch.randn((R, K_in), device="cuda").bfloat16()
+    W = torch.randn((K_out, K_in), device="cuda").bfloat16()
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    dX = torch.empty((R, K_in), dtype=torch.bfloat16, device="cuda")
+
+    def per_launch(rho):
+        vb.vcas_backward_data(shape, G, X, W, rho, vb.Rng(1, 1, 0), True, plan, dX, ws)
+        torch.cuda.synchronize()
+        vb.vcas_profile_begin()
+        for draw in range(40):
+            vb.vcas_backward_data(shape, G, X, W, rho, vb.Rng(1, 1, draw), True, plan, dX, ws)
+        return vb.vcas_profile_end()[0][0] / 40
+
+    expected_200_at_most = min(per_launch(0.8) for _ in range(3))    # 198 tiles
+    assert min(per_launch(0.834) for _ in range(3)) <= 1.1 * expected_200_at_most
