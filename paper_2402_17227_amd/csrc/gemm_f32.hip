@@ -224,7 +224,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(const float 
     }
 }
 
-// dgrad for tensors of 2 GiB and more, and for many tiles of a short contraction (see dgrad_f32).
+// dgrad for tensors of 2 GiB and more, and for many tiles of a short or ragged contraction (see dgrad_f32).
 // grid: tiles_n * (ceil(R/64) + 1) + 8 workgroups.  The first ceil8(compute
 // tiles) ids compute (spread over the XCDs), the next ones zero the rows of
 // dropped samples, the rest exit.
@@ -480,12 +480,20 @@ vcas_status dgrad_f32(const vcas_shape &s, const void *G, const void *W, const f
 {
     const int64_t R = (int64_t)s.N * s.T;
     const int64_t rows = expected_rows > 0 && expected_rows < R ? expected_rows : R;
-    // Many tiles of a short contraction are prologues and epilogues: four wavefronts with a fifth of the LDS, six workgroups
-    // to a CU, hide them better than eight wavefronts, two to a CU.  This kernel and the 64x64 one below: 8192 rows,
-    // 1024 columns (2048 tiles), contraction 64 23.3 and 28.7 us, 128 32.3 and 36.1, 192 41.0 and 44.2, 256 50.5 and 51.9,
-    // 384 68.6 and 68.4; 768 tiles, contraction 64 13.0 and 15.0, 256 23.8 and 23.3; 384 tiles, contraction 64 11.3 and 10.9
-    // (32x64 tiles).
-    const bool short_tiles = s.K_out <= 256 && ((rows + 63) / 64) * ((s.K_in + 63) / 64) > 512;
+    // More than two 64x64 tiles to a CU: the kernel below runs its tiles two to a CU and in steps of 64 elements, the staged
+    // one four to a CU (of half as many wavefronts) and in steps of 16.  It hides prologues and epilogues better, computes less
+    // for a ragged contraction, and takes 1.15 times as long for an element; between one and two rounds of its four to a CU
+    // the second one leaves most of the chip idle.  1024 columns, staged and LDS-direct, us:
+    //   contraction    64          128          192          256          264          328          384          520
+    //    768 tiles  10.6 13.2   14.2 16.0   18.1 19.3   21.7 22.1   23.1 25.1   26.6 27.9   29.3 27.9   38.3 37.1
+    //   1024        12.1 15.1   17.4 19.2   22.3 23.0   26.7 27.1   28.3 31.2   33.3 35.2   36.8 35.3   47.2 47.3
+    //   1280        16.8 18.5   24.1 23.9   30.7 28.3   37.3 33.2   39.6 38.3   46.2 42.9   50.9 42.7   65.7 57.6
+    //   2048        21.3 26.7   30.3 34.3   39.3 41.7   48.3 49.6   51.2 57.4   59.8 65.4   67.1 65.4   87.9 89.4
+    //   4096        37.2 48.1   54.3 63.0   73.3 79.6   89.8 94.3   96.6 110.6  115 128
+    // Up to 512 tiles the one below wins throughout (contraction 256: 10.9 and 13.3 at 256 tiles, 15.4 and 17.0 at 512).
+    const int64_t tiles = ((rows + 63) / 64) * ((s.K_in + 63) / 64);
+    const int staged_cost = (tiles > 1024 && tiles < 2048 ? 127 : 115) * ((s.K_out + 15) / 16 * 16);
+    const bool short_tiles = tiles > 512 && staged_cost < 100 * ((s.K_out + 63) / 64 * 64) + 4000;
     if (short_tiles || !offsets_fit(s)) {   // offsets: larger tensors, which the fp32 calls have always taken
         const int tiles_n = (s.K_in + 63) / 64;
         const int64_t grid = tiles_n * ((R + 63) / 64 + 1) + 8;
