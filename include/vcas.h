@@ -307,8 +307,8 @@ typedef struct {
                                   squares of its dX here (rows of kept samples only); needs dX */
     const float *g_sq_blocks;  /* vcas_sq_blocks_bytes(R, K_out) bytes, device: block sums of squares of this entry's G, as
                                   the entry that wrote G left them; the pass over G is replaced by a pass over
-                                  them (the same bits), which for N <= 64 and T <= 1024 also leaves the sample
-                                  norms, so that dgrad decides SampleA itself and no launch of its own does.
+                                  them (the same bits), which for N <= 64 also leaves what the sample norms are
+                                  added up from, so that dgrad decides SampleA itself and no launch of its own does.
                                   Needs kept_above: rows of samples dropped above have no block sums */
 } vcas_layer_args;
 
@@ -325,8 +325,9 @@ typedef struct {
  *                   group's last SampleA: row norms of X where still due, SampleW;
  *   gemm_stream     after the group's SampleW: dW (and its split-K reduction).
  * Consecutive entries marked `sibling` that have one shape may share the launches
- * of their data halves and of their weight gradients (up to four layers per
- * launch); a group is extended rather than cut inside such a run.
+ * of their data halves (up to four layers per launch) and of their norms of X and
+ * SampleW (up to eight); a group is extended rather than cut inside such a run.
+ * The weight gradients of a group share launches whether siblings or not.
  * Towards the end of the stack the groups shrink (each takes half of the layers
  * that are left), so that the side streams finish shortly after `stream`.
  * sampler_stream and gemm_stream may be the same stream, or null (= `stream`).

@@ -120,9 +120,9 @@ def test_stack_takes_norms_from_the_layer_above(vb, N, T):
     """A chain down -> up -> o -> (v, k, q): every entry's dX buffer is the next entry's G, the entries know
     which samples the one above kept and leave dropped rows unwritten.  With the block sums handed down the
     sweeps over G disappear for every entry but the first; plans, dX and dW must be the bits of the same stack
-    with the sweeps.  Up to 64 samples of up to 1024 rows the pass over the block sums also leaves the sample
-    norms and dgrad decides SampleA (one workgroup per sample, 1 to 16 threads per row); beyond (the last two
-    cases) the row sums go through the SampleA launch as before."""
+    with the sweeps.  Up to 64 samples the pass over the block sums also leaves 64 lane sums a sample, from which
+    dgrad decides SampleA (eight lanes to a workgroup up to 512 rows a sample, four beyond); with 70 samples the row
+    sums go through the SampleA launch."""
     from tests.gpu_util import to_device, plan_to_numpy
     # G of an entry is [R, K_out]; its dX is [R, K_in] and is the next entry's G: K_in(above) == K_out(below)
     chain = [("down", 264, 136), ("up", 136, 264), ("o", 136, 136), ("v", 200, 136), ("k", 200, 136), ("q", 200, 136)]
