@@ -159,23 +159,27 @@ static WgradItem wgrad_item(const vcas_shape &s, const void *G, const void *X, c
 // (0: unknown, any of the R).  The gathering kernel is ONE launch that multiplies the token scales into its
 // fragments; the packed form takes two or three (pack, GEMM, reduction of slices), 4 to 6 us each however
 // short the contraction, but cuts a long contraction into slices where the gathering kernel walks it in one
-// workgroup per tile.  So the line rises with the tiles that fill the chip without slices.  64x64 tiles while
-// every CU can have one at once, gathering against packed in us (replayed from a graph):
-//   tiles      512 tokens    768         1024        1280        1536        2048
-//     16       8.9  10.2   11.1  10.5  13.3  10.8  15.7  11.1  18.0  11.3  22.5  12.0
-//     32       8.9  10.8   11.2  11.3  13.4  11.9  15.8  12.1  18.1  12.5  22.6  13.0
-//     64       9.0  13.9   11.3  15.1  13.5  16.7  16.1  16.6  18.2  17.6  22.6  18.5
-//     96       9.1  15.4   11.4  17.4  13.6  18.4  16.2  18.1  18.3  19.1  22.7  20.1
-//    144       9.3  17.6   11.6  20.2  13.8  24.4  16.5  23.6  18.6  25.4  23.1  26.4  (3072: 32.2 and 28.2)
-//    256       9.8  22.5   12.1  27.1  14.5  26.9  17.3  26.7  19.8  27.4  24.1  27.3  (3072: 34.2 and 28.3)
-// 128x128 tiles beyond: 81 tiles 24.6 and 25.5 at 1024 tokens, 29.4 and 27.6 at 1280; 144 tiles 25.3 and 27.6, 30.1
-// and 28.1; 576 tiles 22.1 and 24.3 at 256 tokens, 30.5 and 31.4 at 512, 39.5 and 37.7 at 768.
+// workgroup per tile.  So the line rises with the tiles that fill the chip without slices.  64x64 tiles while a CU has
+// two of them at the most, 128x128 tiles beyond.  Both halves of a layer one after the other, 80 mask draws over four
+// sets of buffers, packed and gathering in us:
+//   64x64 tiles     400 tokens    512          768          1024         1536         2048
+//      16                      37.0 32.7   36.6 35.4   36.6 38.0
+//      32                      37.1 32.1   36.1 35.3   36.4 38.5
+//      64          36.8 32.8               38.4 36.5   39.1 38.5   41.1 44.3   43.8 50.5
+//      96          37.4 31.9               39.7 37.0   41.0 39.3   43.5 45.1   45.7 51.2
+//     144          39.6 33.1               44.1 37.4   45.5 40.7   48.2 46.6   50.6 53.1
+//     192          41.8 33.3               45.4 38.4   47.2 42.0   50.2 48.0   53.9 54.8
+//     256          44.1 34.7               47.4 39.9   49.7 43.6   52.8 50.1   58.7 57.8
+//     322                      45.5 38.4   49.6 44.5   51.4 49.0   (128x128, 84 of them: 40.4, 48.2, 54.2)
+//     512                      49.0 40.8   52.5 47.4   56.5 52.8   (128 of them: 43.0, 50.4, 57.8)
+//     576                      50.5 45.2   57.2 53.2   59.8 59.7   (144 of them: 42.0, 50.6, 56.7)
+// 576 tiles of 128x128, alone on the chip: 22.1 and 24.3 at 256 tokens, 30.5 and 31.4 at 512, 39.5 and 37.7 at 768.
 enum WgradForm { kPacked, kGatherSmall, kGatherLarge };
 static WgradForm wgrad_form(const vcas_shape &s, int64_t tokens)
 {
     if (tokens <= 0 || !offsets_fit(s)) return kPacked;
     const int64_t small = gather_tiles(VCAS_BF16, s.K_out, s.K_in, false), large = gather_tiles(VCAS_BF16, s.K_out, s.K_in, true);
-    if (small <= 256) return tokens <= 2048 && tokens <= 400 + 12 * small ? kGatherSmall : kPacked;
+    if (small <= 512) return tokens <= (small > 256 ? 1024 : small > 181 ? 2048 : 600 + 8 * small) ? kGatherSmall : kPacked;
     return tokens <= 1024 && large * (tokens < 64 ? 64 : tokens) <= 160 * 1024 ? kGatherLarge : kPacked;
 }
 static int64_t expected_tokens(const vcas_shape &s, double rho, double nu, int token_sampling)

@@ -39,13 +39,14 @@ def test_fp32_kernels_at_their_edges(vb, case):
 
 
 BF16_CASES = [
-    # wgrad gathering with 64x64 tiles: fewer than 32 of them, up to 256, ragged; G scaled, X scaled
+    # wgrad gathering with 64x64 tiles: fewer than 32 of them, 256, ragged; G scaled, X scaled
     (3, 11, 8, 8, 0.5, 0.5), (9, 233, 264, 136, 0.6, 0.7), (9, 233, 136, 264, 0.7, 0.7), (8, 256, 1024, 1024, 1.0, 0.99),
     # nothing kept, one token; 1024 and 1025 tokens of fewer than 32 tiles (gathering, packed)
     (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1024, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
-    # 128x128 tiles, ragged, either side scaled; beyond them the packed form
+    # 18 x 19 tiles, ragged, either side scaled; beyond 1024 tokens the packed form; 128x128 tiles, ragged, either side scaled
     (3, 67, 1096, 1160, 0.7, 0.7), (3, 67, 1160, 1096, 0.7, 0.7), (8, 257, 1096, 1160, 1.0, 0.9),
-    # gathering over whole, partial and single steps of 64 tokens, with both tiles; 17 x 17 tiles
+    (3, 67, 1480, 1544, 0.7, 0.7), (3, 67, 1544, 1480, 0.7, 0.7), (1, 129, 1480, 1544, 1.0, 1.0), (1, 321, 1480, 1544, 1.0, 1.0),
+    # gathering over whole, partial and single steps of 64 tokens, with 64x64 tiles; 17 x 17 tiles of 128x128
     (1, 64, 264, 264, 1.0, 1.0), (1, 65, 264, 264, 1.0, 1.0), (1, 200, 264, 264, 1.0, 1.0), (1, 257, 264, 264, 1.0, 1.0),
     (1, 513, 264, 264, 1.0, 1.0), (1, 129, 1096, 1160, 1.0, 1.0), (1, 321, 1096, 1160, 1.0, 1.0), (3, 67, 2056, 2120, 0.7, 0.7),
     # packed, 256x256 tiles: 15 x 15 of them on a layer's own; below 192 and beyond 256 of them (13 x 14, 17 x 16) as before
@@ -137,13 +138,14 @@ def test_dgrad_last_round_in_quarters(vb, K_out, kept):
         assert float(((rows - (got * got).sum(1)).abs() / (got * got).sum(1).clamp_min(1e-30))[~dropped].max()) <= 1e-5
 
 
-# On both sides of the lines between the two forms of a small weight gradient: 64x64 tiles by their number (16, 32, 64,
-# 144 of them), 128x128 tiles (81).  vcas_sampled_wgrad, which knows no expected count, always takes the packed form: its
+# On both sides of the lines between the two forms of a small weight gradient: 64x64 tiles by their number (16, 32, 64, 144, 192,
+# 306 and 504 of them), 128x128 tiles (135).  vcas_sampled_wgrad, which knows no expected count, always takes the packed form: its
 # bits are those of the same form, and the gathering kernel adds in another order.
 @pytest.mark.parametrize("K_in,K_out,tokens,packed", [
     (256, 256, 512, False), (256, 256, 1024, True), (512, 256, 768, False), (512, 256, 1280, True),
-    (512, 512, 1024, False), (512, 512, 1536, True), (768, 768, 2048, False), (768, 768, 2056, True),
-    (1096, 1032, 1024, False), (1096, 1032, 1280, True)])
+    (512, 512, 1024, False), (512, 512, 1536, True), (768, 768, 1752, False), (768, 768, 1760, True), (1024, 768, 2048, False),
+    (1024, 768, 2056, True), (1096, 1032, 1024, False), (1096, 1032, 1280, True), (1304, 1496, 1024, False), (1304, 1496, 1032, True),
+    (1112, 1864, 1024, False), (1112, 1864, 1032, True)])
 def test_form_of_a_small_weight_gradient(vb, K_in, K_out, tokens, packed):
     N, T = 8, tokens // 8
     shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
