@@ -26,7 +26,7 @@ F32_CASES = [
     (3, 11, 8, 8, 0.5, 0.5), (3, 33, 264, 72, 0.7, 0.6), (7, 40, 96, 520, 0.6, 0.5), (40, 64, 64, 136, 1.0, 1.0),
     # dgrad with 32x64 tiles
     (5, 131, 552, 200, 1.0, 0.3),
-    # dgrad with 64x64 tiles
+    # the same where 64x64 tiles would be 264, a second one for eight CUs (those tiles: test_fp32_dgrad_tiles)
     (9, 233, 456, 72, 1.0, 0.5),
     # wgrad with 64x64 tiles (768 of them and more): full, remainder and single steps of 32 tokens, nothing kept
     (4, 47, 1608, 1928, 0.5, 0.5), (2, 16, 1608, 1928, 1.0, 1.0), (2, 5, 1608, 1928, 0.02, 0.02),
