@@ -1,5 +1,6 @@
 """fp32 products from bf16 parts: the lines between the tiles of the weight gradient and the edges of its slices, the accuracy
-that three parts and separate small sums give, and operands whose parts are not finite, against 64 bits."""
+that three parts and separate small sums give, operands down to fp32's smallest numbers, and operands whose parts are not finite, against
+64 bits."""
 import math
 
 import pytest
@@ -77,6 +78,36 @@ def _dgrad(vb, G, W):
     dX = torch.full((R, W.shape[1]), float("nan"), device="cuda")
     vb.vcas_sampled_dgrad(vb.shape_of(1, R, W.shape[1], W.shape[0], vb.VCAS_F32), G, W, ones, zero, one, dX)
     return dX
+
+
+# Operands of about 2^a and 2^b: values whose small parts are below bf16's smallest number, subnormal ones, products whose small
+# parts are; values and sums that are beyond what the parts can hold
+RANGES = [(-112, 30), (-118, 30), (-126, 60), (-140, 60), (30, -126), (-60, -60), (106, -100), (45, 45)]
+
+
+@pytest.mark.parametrize("a,b", RANGES)
+@pytest.mark.parametrize("R,K_in,K_out", [(1935, 456, 200), (1100, 1000, 776), (2065, 2056, 328)])
+def test_dgrad_keeps_small_values(vb, R, K_in, K_out, a, b):
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    G = (torch.randn((R, K_out), generator=gen, device="cuda").double() * 2.0 ** a).float()
+    W = (torch.randn((K_out, K_in), generator=gen, device="cuda").double() * 2.0 ** b).float()
+    off, want = _dgrad(vb, G, W).double(), G.double() @ W.double()
+    off -= want
+    for dim in (0, 1):
+        assert float((off.norm(dim=dim) / want.norm(dim=dim)).max()) <= 4 * _bound(K_out)
+
+
+@pytest.mark.parametrize("a,b", RANGES)
+@pytest.mark.parametrize("R,K_in,K_out", [(1200, 520, 520), (4001, 520, 520), (300, 1288, 1160)])
+def test_wgrad_keeps_small_values(vb, R, K_in, K_out, a, b):
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    G = (torch.randn((R, K_out), generator=gen, device="cuda").double() * 2.0 ** a).float()
+    X = (torch.randn((R, K_in), generator=gen, device="cuda").double() * 2.0 ** b).float()
+    scale = torch.full((R,), 4.0, device="cuda")
+    off, want = _wgrad(vb, G, X, scale, torch.arange(R, device="cuda")).double(), 4 * (G.double().t() @ X.double())
+    off -= want
+    for dim in (0, 1):
+        assert float((off.norm(dim=dim) / want.norm(dim=dim)).max()) <= 4 * _bound(R)
 
 
 def _same(got, A, B):
