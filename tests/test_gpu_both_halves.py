@@ -50,3 +50,43 @@ def test_one_launch_is_the_two(dtype, N, T, K_in, K_out, rho, nu):
         bits = torch.int16 if dtype == BF16 else torch.int32
         assert torch.equal(dX_a.view(bits), dX_b.view(bits)) and torch.equal(dW_a.view(torch.int32), dW_b.view(torch.int32))
         assert bool(dX_a.isfinite().all()) and bool(dW_a.isfinite().all())
+
+
+# fp32 sums that bf16 parts cannot hold (2^90) in single 32x32 blocks of dX and dW, which are formed again in plain fp32: beside
+# them the blocks keep their bits whatever tile either way takes (dX 128x128 in one launch; apart 64x64, 64x128, 128x128)
+@pytest.mark.parametrize("N,T,K_in,K_out", [(10, 100, 520, 520), (20, 200, 776, 520), (20, 200, 776, 2200), (30, 64, 520, 2568)])
+def test_one_launch_is_the_two_beside_sums_formed_again(N, T, K_in, K_out):
+    from paper_2402_17227_amd import binding as vb
+    vb.lib()
+    gen = torch.Generator(device="cuda").manual_seed(K_out)
+    G = torch.randn((N * T, K_out), generator=gen, device="cuda")
+    X = torch.randn((N * T, K_in), generator=gen, device="cuda")
+    W = torch.randn((K_out, K_in), generator=gen, device="cuda") * 0.02
+    rows = torch.arange(3, N, 5, device="cuda") * T + 37      # one token of one sample in five
+    G[rows, 70] = 2.0 ** 50
+    X[rows, 100] = 2.0 ** 40
+    W[70, 65] = 2.0 ** 40
+    shape = vb.shape_of(N, T, K_in, K_out, F32)
+    ws = vb.make_workspace(shape)
+    got = []
+    for whole in (True, False):
+        plan = vb.Plan.allocate(N, T)
+        dX = torch.full((N * T, K_in), float("nan"), device="cuda")
+        dW = torch.full((K_out, K_in), float("nan"), device="cuda")
+        if whole:
+            vb.vcas_linear_backward(shape, G, X, W, 0.5, 0.5, vb.Rng(7, 2, 0), True, plan, dX, dW, ws)
+        else:
+            vb.vcas_backward_data(shape, G, X, W, 0.5, vb.Rng(7, 2, 0), True, plan, dX, ws)
+            vb.vcas_backward_weight(shape, G, X, 0.5, 0.5, vb.Rng(7, 2, 0), True, plan, dW, ws)
+        got.append((dX, dW))
+    (dX, dW), (dX_apart, dW_apart) = got
+    assert torch.equal(dX, dX_apart) and torch.equal(dW, dW_apart)
+    scale = (plan.maskA / plan.p.double()).nan_to_num(0.0).repeat_interleave(T)[:, None]
+    kept = plan.idxW[:int(plan.cntW)].long()
+    assert bool((kept[:, None] == rows[None]).any())
+    G, X, W, Gw = G.double(), X.double(), W.double(), G[kept].double() * plan.scaleW[kept].double()[:, None]
+    for out, want, terms in ((dX, G @ W * scale, G.abs() @ W.abs() * scale),
+                             (dW, Gw.t() @ X[kept], Gw.abs().t() @ X[kept].abs())):
+        assert float(out.abs().max()) > 2.0 ** 88
+        # every element within fp32 sums of its own terms; 1e-12: dropped samples' rows are zero on both sides
+        assert float(((out.double() - want).abs() / terms.clamp_min(1e-12)).max()) <= 2e-6

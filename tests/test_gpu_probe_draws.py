@@ -68,3 +68,25 @@ def test_probe_without_a_choice(case):
     X[1] = 0
     assert probe(0.5, 1.0) == [0.0] * 4
     assert probe(0.25, 1.0)[2] > 0.0
+
+
+# Products of which some sums (2^90) are beyond what the bf16 parts of fp32 values hold and are formed again, in the comparing
+# kernel's 64x64 and 128x128 tiles
+@pytest.mark.parametrize("K_in,K_out,M", [(264, 136, 2), (776, 392, 2), (776, 776, 2)])
+def test_probe_of_sums_beyond_the_parts(K_in, K_out, M):
+    from paper_2402_17227_amd import binding as vb
+    from tests.gpu_util import to_device
+    N, T = 6, 40
+    sp = workloads.LayerSpec("probe", F32, N, T, K_in, K_out, 0.5, 0.5, layer=4, seed=5, gen_seed=M, token_sigma=0.5)
+    G, X, _ = workloads.make_layer(sp)
+    G[::3, 70] *= np.float32(2.0 ** 50)      # tokens of every sample, so that either mask has a choice
+    X[::3, 100] *= np.float32(2.0 ** 40)
+    shape = vb.shape_of(N, T, K_in, K_out, F32)
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    out = torch.full((4,), float("nan"), dtype=torch.float64, device="cuda")
+    vb.vcas_variance_probe(shape, to_device(G, F32), to_device(X, F32), 0.5, 0.2, vb.Rng(5, 4, 10), M, plan, out, ws)
+    want = oracle.variance_probe(G, X, F32, N, T, 0.5, 0.2, 5, 4, 10, M)
+    got = out.cpu().numpy()
+    assert want[2:].min() > 2.0 ** 150
+    np.testing.assert_allclose(got[:2], want[:2], rtol=1e-9)
+    np.testing.assert_allclose(got[2:], want[2:], rtol=1e-4)
