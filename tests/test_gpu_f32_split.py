@@ -60,6 +60,24 @@ def test_wgrad_tiles_and_slices(vb, R, K_in, K_out, kept):
     assert float((dW - want).norm() / want.norm()) <= _bound(kept)
 
 
+# One kept token: a product rounded once, as on the fp32 instruction, and not the 9e-8 that the parts leave; few tokens no
+# more than fp32 sums of that many terms
+@pytest.mark.parametrize("kept", [1, 2, 3, 7])
+@pytest.mark.parametrize("R,K_in,K_out", [(700, 584, 776), (4001, 520, 520), (300, 1288, 1160), (40, 1288, 2056)])
+def test_wgrad_of_few_tokens(vb, R, K_in, K_out, kept):
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    G = torch.randn((R, K_out), generator=gen, device="cuda")
+    X = torch.randn((R, K_in), generator=gen, device="cuda")
+    scale = torch.ones(R, device="cuda")
+    rows = torch.arange(kept, device="cuda") * 5 + 2
+    dW = _wgrad(vb, G, X, scale, rows).double()
+    g, x = G[rows].double(), X[rows].double()
+    off = (dW - g.t() @ x).abs()
+    terms = g.abs().t() @ x.abs()
+    # a rounding of the sum so far with every term
+    assert float((off / terms).max()) <= kept * 2.0 ** -24
+
+
 # every tile of the data half: 64x64, 64x128, 128x128
 @pytest.mark.parametrize("R,K_in,K_out", [(1935, 456, 200), (1100, 1000, 776), (2065, 2056, 328)])
 def test_dgrad_accuracy(vb, R, K_in, K_out):
