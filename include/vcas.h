@@ -298,7 +298,10 @@ typedef struct {
                            cutting the contraction into split-K slices (1..384; larger values count as 384).
                            0 = 384, what every other entry point uses: right for a launch that has the chip
                            to itself.  Beside the data chain of a stack fewer, longer slices (64) make the
-                           step shorter.  The number of slices fixes the order of a weight gradient's sums:
+                           step shorter.  A bf16 entry that is expected to keep few tokens (N T rho nu up to
+                           1300, in a group of layers no wider than 640 tiles of 128x128) is not cut at all
+                           for any value from 1 to 383: there, adding up slices costs more than it saves.
+                           The number of slices fixes the order of a weight gradient's sums:
                            dW is the same bits for the same value of this field, and within rounding
                            (fp32 sums in another order) across values. */
     /* The norms of G from the launch that wrote G (see vcas_sampled_dgrad_norms), for entries that feed

@@ -612,34 +612,43 @@ static vcas_status weight_half_group(const vcas_layer_args *layers, int n, hipSt
     return sampler_w_group(samplers, n, s.N, s.T, layers[0].token_sampling, 0, st);
 }
 
-// The form of a bf16 weight gradient that runs beside the dgrads of the layers below it (a stack's side stream, a
-// wgrad_fill below kWgradFill).  A workgroup that gathers holds its CU for all of the layer's tokens, and there is one
+// Do the bf16 weight gradients of a group that run beside the dgrads of the layers below them (a stack's side stream, a
+// wgrad_fill below kWgradFill) gather, unsliced?  A workgroup that gathers holds its CU for all of the layer's tokens, and there is one
 // for every tile of 128x128, so the dgrad waits for CUs that long; the packed form keeps to few CUs, but pays a launch
-// and a pass over the kept rows.  Few tokens, and the gathering form ends before it is in the way.  Where the line is
-// best depends on which streams share a hardware queue.  12 blocks of 768 x 3072 at 614 to 2048 expected tokens (us):
-//                                         all packed    up to 1300    up to 2048
-//   a queue for each of three streams        1830          1808          1828
-//   sampler and gemm stream on one           2424          2286          2083
-//   gemm stream on the main one's            2632          2545          2390
-//   sampler stream on the main one's         2702          2682          2703
-//   several stacks in turn, mappings mixed   2072          2017          1960
-//   the same, one stream further along       2169          2175          2217
-// 1300 gains 1 to 6 % and loses at most 0.5, 2048 loses 2 % in the last.  2 blocks of 1024 x 4096 at 4096 expected tokens: packed 960,
-// gathered 985.  A matrix of fewer than 16 tiles of 128x128 takes those of 64x64, as the packed form does for a launch.
-static WgradForm beside_others(const vcas_shape &s, int64_t tokens)
+// and a pass over the kept rows.  Few tokens, and the gathering form ends before it is in the way.  How much it gains
+// depends on which streams share a hardware queue; us a pass, mean over four such mappings, packed and gathering (blocks, width x
+// ffn width, most 128x128 tiles of a layer, expected tokens):
+//    6,  512x2048,   64,  150 to  512    755   710        2, 1536x4608,  432, 1280           775   716
+//    8,  256x1024,   16,  300 to 1024   1021   946        2, 1536x6144,  576,  640           604   586
+//   12,  768x3072,  144,  614 to 2048   2197  2150        2, 2048x6144,  768,  128 to  256   505   505
+//    6,  768x3072,  144,  307 to 1024    976   965        2, 2048x6144,  768,  256 to  512   585   604
+//    4, 1024x4096,  256,  307 to 1024    764   761        2, 2048x6144,  768,  512 to 1024   739   766
+//    4, 1024x4096,  256, 1280            898   895        2, 2048x6144,  768, 1280           980  1002
+// So up to 640 tiles in the widest layer, beyond which the packed form's 256x256 tiles have come to a CU each, and up to 1300 tokens (2
+// blocks of 1024x4096 at 4096: packed 960, gathering 985).  All of a group or none: with the wide layers of a block packed and its others
+// gathering, 2048x6144 at 512 to 1024 tokens takes 791.  Slices, and a launch more to add them up, lose what gathering gains:
+// 256x1024 946 -> 1120, 512x2048 710 -> 758.
+static bool gather_beside_others(const vcas_layer_args *layers, int l0, int l1)
 {
-    if (!offsets_fit(s) || tokens <= 0 || tokens > 1300) return {true, kSmallTile, 1};
-    return {false, gather_tiles(VCAS_BF16, s.K_out, s.K_in, kLargeTile) < 16 ? kMidTile : kLargeTile, 1};
+    for (int l = l0; l < l1; ++l) {
+        const vcas_layer_args &b = layers[l];
+        if (!b.dW || b.shape.dtype != VCAS_BF16 || b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill) continue;
+        if (!offsets_fit(b.shape) || expected_tokens(b.shape, b.rho, b.nu, b.token_sampling) > 1300 ||
+            gather_tiles(VCAS_BF16, b.shape.K_out, b.shape.K_in, kLargeTile) > 640)
+            return false;
+    }
+    return true;
 }
 
 // Weight gradients of the layers [l0, l1) of a stack that want one (bf16 layers in batched launches, fp32 layers
 // one by one).  A layer with wgrad_fill == 0 gets the form, the tile and the slices a call on its own would
-// pick, hence that call's bits; the others gather (beside_others) or are planned per launch: the tiles of every layer
+// pick, hence that call's bits; the others gather (gather_beside_others) or are planned per launch: the tiles of every layer
 // of the batch count towards `fill`, so a block's weight gradients fill the chip together and are rarely sliced at all.
 // Layers that gather with one tile size share a launch too: one by one, each left most CUs empty (four layers of
 // 768x768 and 2048 tokens are 144 workgroups each).
 static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1, hipStream_t st)
 {
+    const bool gather = gather_beside_others(layers, l0, l1);
     for (int l = l0; l < l1;) {
         const vcas_layer_args &a = layers[l];
         if (!a.dW) {
@@ -655,9 +664,10 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
         // fp32 has no forms: "packed" stands for "not in this run" there
         auto own = [](const vcas_layer_args &b) { return b.wgrad_fill == 0 || b.wgrad_fill >= kWgradFill; };
         auto form_of = [&](const vcas_layer_args &b) {
-            if (b.shape.dtype != VCAS_BF16) return WgradForm{true, kSmallTile, 1};
-            const int64_t tokens = expected_tokens(b.shape, b.rho, b.nu, b.token_sampling);
-            return own(b) ? wgrad_form(b.shape, tokens) : beside_others(b.shape, tokens);
+            if (b.shape.dtype != VCAS_BF16 || (!own(b) && !gather)) return WgradForm{true, kSmallTile, 1};
+            if (own(b)) return wgrad_form(b.shape, expected_tokens(b.shape, b.rho, b.nu, b.token_sampling));
+            // a matrix of fewer than 16 tiles of 128x128 takes those of 64x64, as the packed form does for a launch
+            return WgradForm{false, gather_tiles(VCAS_BF16, b.shape.K_out, b.shape.K_in, kLargeTile) < 16 ? kMidTile : kLargeTile, 1};
         };
         const WgradForm form = form_of(a);
         if (!form.packed) {

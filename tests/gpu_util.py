@@ -107,3 +107,15 @@ def blocks_from_device_layout(dev, nb):
     """The inverse: [groups, R, 4] -> [R, nb]."""
     a = dev.cpu().numpy() if hasattr(dev, "cpu") else np.asarray(dev)
     return np.stack([a[b // 4, :, b % 4] for b in range(nb)], axis=1)
+
+
+def packs_the_kept_rows(ws, run, plan_only) -> bool:
+    """Which form of the bf16 weight gradient run() takes, from what it leaves in the workspace: the packed form's operand lies behind
+    everything that plan_only() (the same call without dW) writes, the partial tiles of either form lie in front of it."""
+    def end(call):
+        ws[8192:] = 0x5A      # all but the control words
+        call()
+        torch.cuda.synchronize()
+        return int((ws != 0x5A).nonzero()[-1])
+    without = end(plan_only)
+    return end(run) > without

@@ -164,32 +164,39 @@ def test_form_of_a_small_weight_gradient(vb, K_in, K_out, tokens, packed):
 
 
 def test_gathering_layers_of_a_stack_share_launches(vb):
-    """Twenty siblings that gather (sixteen to a launch), one in the middle without a dW and one that takes the packed
-    form: three gathering launches around one packed launch, each dW the bits of a call of its own."""
+    """Twenty siblings that gather (sixteen to a launch), one in the middle without a dW and one of more than 1300 expected tokens
+    that takes the packed form: three gathering launches around one packed launch, each dW the bits of a call of its own."""
+    from tests.gpu_util import packs_the_kept_rows
     N, T, K = 8, 32, 128
-    shape = vb.shape_of(N, T, K, K, vb.VCAS_BF16)
     gen = torch.Generator(device="cuda").manual_seed(6)
     one = lambda *size: torch.randn(size, generator=gen, device="cuda").bfloat16()
     entries, keep = [], []
     for l in range(22):
-        G, X, W = one(N * T, K), one(N * T, K), one(K, K)
-        plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+        tokens, ratios = (8 * T, (0.9, 0.9)) if l == 4 else (T, (0.7, 0.5))
+        shape = vb.shape_of(N, tokens, K, K, vb.VCAS_BF16)
+        G, X, W = one(N * tokens, K), one(N * tokens, K), one(K, K)
+        plan, ws = vb.Plan.allocate(N, tokens), vb.make_workspace(shape)
         dX, dW = torch.empty_like(X), torch.full((K, K), float("nan"), device="cuda")
-        entries.append(vb.layer_args(shape, G, X, W, 0.7, 0.5, vb.Rng(2, l, 0), True, plan, dX, None if l == 2 else dW, ws,
+        entries.append(vb.layer_args(shape, G, X, W, *ratios, vb.Rng(2, l, 0), True, plan, dX, None if l == 2 else dW, ws,
                                      sibling=l > 0, wgrad_fill=64 if l == 4 else 0))
-        keep.append((G, X, W, plan, ws, dX, dW))
+        keep.append((shape, ratios, G, X, W, plan, ws, dX, dW))
     streams = torch.cuda.Stream(), torch.cuda.Stream()
+    shape, ratios, G, X, W, plan, ws, dX, dW = keep[4]
+    alone = lambda dW: vb.vcas_backward_stack(vb.make_stack([vb.layer_args(
+        shape, G, X, W, *ratios, vb.Rng(2, 4, 0), True, plan, dX, dW, ws, wgrad_fill=64)]), 1, *streams)
+    assert packs_the_kept_rows(ws, lambda: alone(dW), lambda: alone(None))
+    dW.fill_(float("nan"))
     stack = vb.make_stack(entries)
     vb.vcas_profile_begin()
     vb.vcas_backward_stack(stack, 22, *streams)
     torch.cuda.synchronize()
     assert vb.vcas_profile_end()[1][1] == 4
-    for l, (G, X, W, plan, ws, dX, dW) in enumerate(keep):
+    for l, (shape, ratios, G, X, W, plan, ws, dX, dW) in enumerate(keep):
         if l in (2, 4):
             assert bool(torch.isnan(dW).any()) == (l == 2)
             continue
         want = torch.full((K, K), float("nan"), device="cuda")
-        vb.vcas_linear_backward(shape, G, X, W, 0.7, 0.5, vb.Rng(2, l, 0), True, plan, dX, want, ws)
+        vb.vcas_linear_backward(shape, G, X, W, *ratios, vb.Rng(2, l, 0), True, plan, dX, want, ws)
         assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
 
 

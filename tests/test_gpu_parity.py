@@ -849,10 +849,11 @@ def test_sibling_layers_inside_a_sparse_chain(vb, N, T):
 def test_weight_gradient_slices_are_a_choice_of_the_caller(vb, fill):
     """vcas_layer_args.wgrad_fill sets how far the contraction of a weight gradient is cut into split-K slices.
     Whatever it is, the plan is the oracle's bit for bit and dW within tolerance; 384 and anything above are the
-    stand-alone call's choice, hence its bits; the same value twice gives the same bits."""
+    stand-alone call's choice, hence its bits; the same value twice gives the same bits.  More than 1300 expected tokens in bf16:
+    with fewer the values below 384 are one."""
     from tests.gpu_util import to_device, from_device, plan_to_numpy, compare_plan, rel_l2, rel_l2_rows, rel_l2_tiles
-    specs = [workloads.LayerSpec("wf0", BF16, 16, 128, 264, 136, 0.8, 0.7, layer=0, seed=14, gen_seed=71, token_sigma=0.5),
-             workloads.LayerSpec("wf1", BF16, 16, 128, 264, 136, 0.6, 0.9, layer=1, seed=14, gen_seed=72, token_sigma=0.5),
+    specs = [workloads.LayerSpec("wf0", BF16, 16, 128, 264, 136, 0.9, 0.8, layer=0, seed=14, gen_seed=71, token_sigma=0.5),
+             workloads.LayerSpec("wf1", BF16, 16, 128, 264, 136, 0.8, 0.95, layer=1, seed=14, gen_seed=72, token_sigma=0.5),
              workloads.LayerSpec("wf2", F32, 8, 128, 136, 72, 0.7, 0.8, layer=2, seed=14, gen_seed=73, token_sigma=0.5)]
     runs = []
     for rep in range(2):
@@ -888,6 +889,26 @@ def test_weight_gradient_slices_are_a_choice_of_the_caller(vb, fill):
             vb.vcas_linear_backward(shape, g, x, w, sp.rho, sp.nu, vb.Rng(sp.seed, sp.layer, 3), True, plan_r, None, dW_r, ws_r)
             torch.cuda.synchronize()
             assert torch.equal(dW.view(torch.int32), dW_r.view(torch.int32))
+
+
+@pytest.mark.parametrize("N,T,rho,nu,cut", [(16, 128, 0.9, 0.9, True), (16, 128, 0.8, 0.79, False), (4, 180, 0.9, 0.9, False)])
+def test_workgroups_of_a_weight_gradient_in_its_bits(vb, N, T, rho, nu, cut):
+    """The bits of dW say in how many slices it was added up.  15 tiles of 64x64 in one slice, in three and in as many as there may
+    be; up to 1300 expected tokens in one, whatever the caller asks for below 384."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    shape = vb.shape_of(N, T, 264, 136, BF16)
+    G, X = (torch.randn((N * T, K), generator=gen, device="cuda").bfloat16() for K in (136, 264))
+    got = []
+    for fill in (1, 40, 128):
+        plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+        dW = torch.full((136, 264), float("nan"), device="cuda")
+        entry = vb.layer_args(shape, G, X, None, rho, nu, vb.Rng(4, 1, 0), True, plan, None, dW, ws, wgrad_fill=fill)
+        vb.vcas_backward_stack(vb.make_stack([entry]), 1, torch.cuda.Stream(), torch.cuda.Stream())
+        torch.cuda.synchronize()
+        got.append(dW)
+    for i, dW in enumerate(got[1:], 1):
+        assert all(torch.equal(dW, other) != cut for other in got[:i])
+        assert float((dW - got[0]).norm() / got[0].norm()) <= 1e-5      # fp32 sums of the same terms
 
 
 @pytest.mark.parametrize("streams", [1, 3])

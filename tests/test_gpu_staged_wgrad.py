@@ -52,18 +52,24 @@ def test_scaled_on_the_way(R, K_in, K_out, kept):
         assert float((off.norm(dim=dim) / want.norm(dim=dim)).max()) <= 4 * bound   # a row has its own spread
 
 
-@pytest.mark.parametrize("N,T,widths", [
-    # either side of the line at 1300 expected tokens in tiles of 128x128 and 64x64, more tokens (packed), few, a mixture that ends
-    # one launch and starts the next
-    (2, 650, ((768, 776), (72, 200))), (2, 651, ((768, 776), (72, 200))), (2, 1025, ((768, 776), (72, 200))), (4, 513, ((768, 776), (72, 200))), (3, 5, ((512, 512), (520, 384), (8, 8))),
-    (4, 64, ((512, 1032), (64, 64), (1032, 512), (504, 512)))])
-def test_beside_the_dgrads_of_a_stack(N, T, widths):
-    """Entries of a stack with wgrad_fill 64: dW of every layer against 64 bits on what its plan kept."""
+@pytest.mark.parametrize("packed,N,T,widths", [
+    # either side of the line at 1300 expected tokens, of tiles of 128x128 and 64x64; few tokens, mixtures that end one launch and start the next
+    (False, 2, 650, ((768, 776), (72, 200))), (True, 2, 651, ((768, 776), (72, 200))), (False, 3, 5, ((512, 512), (520, 384), (8, 8))),
+    (False, 4, 64, ((512, 1032), (64, 64), (1032, 512), (504, 512))),
+    # either side of 640 tiles of 128x128; one wide layer packs all of its group (two layers; the third is the next group)
+    (False, 2, 100, ((2056, 4600),)), (True, 2, 100, ((2056, 4872),)), ((True, True, False), 1, 300, ((264, 136), (2056, 4872), (520, 520))),
+    # packed, ragged columns and last steps: 64x64 tiles (fewer than sixteen of 128x128 in the launch), 128x128 in slices, 256x256 (64 of
+    # them and more), either operand the packed one
+    (True, 2, 1025, ((264, 136),)), (True, 3, 700, ((8, 8), (136, 264))), (True, 2, 1025, ((768, 776), (72, 200))), (True, 4, 513, ((768, 776), (72, 200))),
+    (True, 1, 2333, ((1544, 3080), (2056, 2120))), (True, 3, 777, ((3080, 1544), (2120, 2056)))])
+def test_beside_the_dgrads_of_a_stack(packed, N, T, widths):
+    """Entries of a stack with wgrad_fill 64: dW of every layer against 64 bits on what its plan kept, and the form they take."""
+    from tests.gpu_util import packs_the_kept_rows
     from paper_2402_17227_amd import binding as vb
     vb.lib()
     gen = torch.Generator(device="cuda").manual_seed(N * T)
     R = N * T
-    entries, keep = [], []
+    entries, without, keep = [], [], []
     for l, (K_in, K_out) in enumerate(widths):
         shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
         G = torch.randn((R, K_out), generator=gen, device="cuda").bfloat16()
@@ -71,13 +77,14 @@ def test_beside_the_dgrads_of_a_stack(N, T, widths):
         W = torch.randn((K_out, K_in), generator=gen, device="cuda").bfloat16()
         plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
         dX, dW = torch.empty_like(X), torch.full((K_out, K_in), float("nan"), device="cuda")
-        entries.append(vb.layer_args(shape, G, X, W, 1.0, 0.999, vb.Rng(2, l, 0), True, plan, dX, dW, ws, wgrad_fill=64))
+        for some, out in ((entries, dW), (without, None)):
+            some.append(vb.layer_args(shape, G, X, W, 1.0, 0.999, vb.Rng(2, l, 0), True, plan, dX, out, ws, wgrad_fill=64))
         keep.append((G, X, W, plan, ws, dX, dW))
     streams = torch.cuda.Stream(), torch.cuda.Stream()
-    stack = vb.make_stack(entries)
-    vb.vcas_backward_stack(stack, len(entries), *streams)
-    torch.cuda.synchronize()
-    for G, X, W, plan, ws, dX, dW in keep:
+    stack, plans = vb.make_stack(entries), vb.make_stack(without)
+    call = lambda stack: vb.vcas_backward_stack(stack, len(entries), *streams)
+    for l, (G, X, W, plan, ws, dX, dW) in enumerate(keep):
+        assert packs_the_kept_rows(ws, lambda: call(stack), lambda: call(plans)) == (packed if isinstance(packed, bool) else packed[l]), l
         cnt = int(plan.cntW)
         rows = plan.idxW[:cnt].long()
         scale = plan.scaleW[rows]
