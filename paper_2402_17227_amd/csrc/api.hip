@@ -169,48 +169,40 @@ static WgradItem wgrad_item(const vcas_shape &s, const void *G, const void *X, c
 
 // How the weight gradient of a bf16 layer on its own is computed, by the tokens it is expected to keep (0: unknown, as if
 // it were all R).  The gathering kernel (wgrad_staged.hpp) is one launch, two with slices; the packed form takes two or three (pack,
-// GEMM, reduction of slices), 4 to 6 us each, and has 256x256 tiles where there are enough.  Alone, everything included, us: packed;
-// 64x64 tiles; 128x128 tiles (how many; best number of slices behind s):
-//             tokens    256                    1024                        4096                           16384
-//   136x264 (15,   6)  10.2   5.9   8.0       10.6   8.9 s6  8.3  9.8     13.9  s8 10.0  s8 13.1         28.2  s8 16.1  s8 26.1
-//   512x512 (64,  16)  13.0   5.9   9.1       17.1   9.0     13.5         22.3  s4 14.0  s6 18.5         40.1  s8 26.6  s8 30.2
-//   768x768 (144, 36)  14.9   6.2   9.3       24.4   9.4     15.6         28.3  s3 21.2  s6 22.8         46.3  s3 51.2  s6 39.6
-//  1024x1024 (256,64)  16.9   6.4   9.5       27.2   9.9     15.9         29.6  26.6     s4 26.2         61.0  s2 74.9  s4 56.7
-//  2304x768 (432,108)  21.1   8.7  10.0       27.7  13.9     16.6         33.9  35.9     s2 32.8         78.6  130      s4 90.6
-//   768x3072 (576,144) 24.6  10.0   9.2       27.6  17.5     16.2         39.7  50.3     41.4            98.1  195      s3 115
-//  1024x4096 (1024,256) 25.6 12.5  10.5       30.6  23.1     18.2         53.1  70.0     49.6             150  295      181
-//  4096x4096 (4096,1024) 27.9 34.7 26.5       49.4  76.3     54.5          134  268      177
-// The least of these costs, which follow the table within about a tenth where the forms are close.  64x64 tiles come in two kernels
-// of one speed: two wavefronts to a block, each with half of a step (the launch that computes both halves of a layer has eight
-// wavefronts a workgroup), for as many tokens as two_share says, else one, whose order of sums is that of every other form.
+// GEMM, reduction of slices), 4 to 6 us each, and has 256x256 tiles where there are enough.  Alone, everything included, half of
+// the rows kept, us with operands in cache / touched for the first time: packed; 64x64 tiles; 128x128 tiles (in slices behind s):
+//   tokens        256                           1024                         4096                                    16384
+//   136x264    20/17   9.9/9.5  9.6/9.3     18/17  9.4/11   14/15        18/17  s8 13/13  s8 14/14           30/37    s8 17/24  s8 26/28
+//   512x512    18/16   9.6/9.6  9.7/10      19/19  9.2/11   15/16        24/26  s3 15/20  s8 19/20           41/52    s8 27/32  s8 30/32
+//   768x768    18/18   9.6/9.3  9.7/10      26/26  9.6/11   15/16        30/31  s3 21/23  s4 23/25           46/56    s8 50/57  s8 47/48
+//  1024x1024   20/21   9.4/9.4  9.8/10      28/28  9.9/13   16/17        30/33  26/36     s4 26/27           60/75    s3 77/92  s4 56/57
+//  2304x768    25/24   9.5/9.4  10/11       29/30  14/16    16/18        34/40  36/43     s2 33/35           80/96    130/153   s8 88/95
+//   768x3072   27/26   10/11    9.4/11      29/31  17/20    16/17        39/49  49/55     s4 40/46, 41/46    96/121   190/206   s8 112/130
+//  1024x4096   26/28   13/14    10/12       32/34  24/28    18/20        52/66  72/83     51/52              167/182  300/317   177/187
+//  4096x4096   28/31   37/40    27/33       48/51  81/86    54/63        134/137  271/280  174/178           502/494  1328/1443 659/667
+// The least of these costs, fitted to the means of both: over the table and 2048 tokens 1.8 % above the best form (fitted in cache alone
+// 4.5 %).
 struct WgradForm {
     bool packed;
     GatherTile tile;
     int splits;
 };
-static bool two_share(const vcas_shape &s, int64_t tokens)
-{
-    const int64_t small = gather_tiles(VCAS_BF16, s.K_out, s.K_in, kSmallTile), large = gather_tiles(VCAS_BF16, s.K_out, s.K_in, kLargeTile);
-    if (small <= 512) return tokens <= (small > 256 ? 1024 : small > 181 ? 2048 : 600 + 8 * small);
-    return tokens <= 1024 && large * (tokens < 64 ? 64 : tokens) <= 160 * 1024;
-}
 static WgradForm wgrad_form(const vcas_shape &s, int64_t tokens)
 {
     WgradForm best = {true, kSmallTile, 1};
     if (!offsets_fit(s)) return best;
-    const bool share = tokens > 0 && two_share(s, tokens);
     if (tokens <= 0) tokens = (int64_t)s.N * s.T;
     const double t = (double)tokens, large = gather_tiles(VCAS_BF16, s.K_out, s.K_in, kLargeTile);
     const int whole = wgrad_tiles_bf16(s.K_out, s.K_in, 256);
-    double least = 20.0 + t * (whole >= 192 && whole <= 256 ? 0.0069 : 0.0086) * (large > 64 ? large : 64) / 256;
+    double least = 21.0 + t * (whole >= 192 && whole <= 256 ? 0.0069 : 0.0098) * (large > 64 ? large : 64) / 256;
     const int most = wgrad_split(&s);
     for (int tile = 0; tile < 2; ++tile) {
-        const GatherTile which = tile ? kLargeTile : share ? kSmallTile : kMidTile;
+        const GatherTile which = tile ? kLargeTile : kSmallTile;
         const double tiles = gather_tiles(VCAS_BF16, s.K_out, s.K_in, which), round = tile ? 200 : 256;
-        for (int n = 1; n <= (share ? 1 : most) && (n == 1 || tokens >= n * kGatherMinTokens); ++n) {
-            double us = (tile ? 7.5 : 5.0) + (tile ? 0.0092 : 0.0050) * t / n * (tiles * n > round ? tiles * n / round : 1.0);
+        for (int n = 1; n <= most && (n == 1 || tokens >= n * kGatherMinTokens); ++n) {
+            double us = (tile ? 7.5 : 5.0) + (tile ? 0.0092 : 0.0058) * t / n * (tiles * n > round ? tiles * n / round : 1.0);
             if (!tile && tiles * n > 256) us += 0.0035 * (tiles * n - 256);   // workgroups beyond one to a CU
-            if (n > 1) us += 4.0 + (double)n * s.K_out * s.K_in / 875e3;   // the reduction
+            if (n > 1) us += 5.0 + (double)n * s.K_out * s.K_in / 875e3;   // the reduction
             if (us < least) {
                 least = us;
                 best = {false, which, n};
@@ -667,7 +659,7 @@ static vcas_status wgrad_of_layers(const vcas_layer_args *layers, int l0, int l1
             if (b.shape.dtype != VCAS_BF16 || (!own(b) && !gather)) return WgradForm{true, kSmallTile, 1};
             if (own(b)) return wgrad_form(b.shape, expected_tokens(b.shape, b.rho, b.nu, b.token_sampling));
             // a matrix of fewer than 16 tiles of 128x128 takes those of 64x64, as the packed form does for a launch
-            return WgradForm{false, gather_tiles(VCAS_BF16, b.shape.K_out, b.shape.K_in, kLargeTile) < 16 ? kMidTile : kLargeTile, 1};
+            return WgradForm{false, gather_tiles(VCAS_BF16, b.shape.K_out, b.shape.K_in, kLargeTile) < 16 ? kSmallTile : kLargeTile, 1};
         };
         const WgradForm form = form_of(a);
         if (!form.packed) {
@@ -731,7 +723,7 @@ static Together halves_together(const vcas_shape &s, int64_t rows, int64_t token
     if (s.dtype == VCAS_BF16) {
         const WgradForm form = wgrad_form(s, tokens);
         t.tile = form.tile;
-        t.yes = !form.packed && form.tile != kMidTile && form.splits == 1 && layer_fits_bf16(s, rows, t.tile);
+        t.yes = !form.packed && form.splits == 1 && layer_fits_bf16(s, rows, t.tile);
     } else {
         t.yes = layer_fits_f32(s, rows, tokens, wgrad_split(&s), kWgradFill, t.dm, t.dw);
     }

@@ -97,7 +97,6 @@ vcas_status wgrad_gather(GatherTask *tasks, int n, int dtype, GatherTile tile, b
     if (dtype == VCAS_BF16) {
         if (tile == kLargeTile) return diff ? launch_staged<128, 128, 2, 4, 1, true>(batch, (int)grid, st)
                                             : launch_staged<128, 128, 2, 4, 1, false>(batch, (int)grid, st);
-        if (tile == kMidTile) return diff ? VCAS_EINVAL : launch_staged<64, 64, 2, 2, 1, false>(batch, (int)grid, st);
         return diff ? launch_staged<64, 64, 2, 2, 2, true>(batch, (int)grid, st)
                     : launch_staged<64, 64, 2, 2, 2, false>(batch, (int)grid, st);
     }

@@ -298,7 +298,7 @@ struct GatherBatch {
 
 // Edges of the output tiles: bf16 64 and 128 columns; fp32 32 (fp32 matrix instructions, the wavefronts of a workgroup share the
 // contraction), 64 and 128 (bf16 parts, f32_split.hpp).
-enum GatherTile { kSmallTile, kMidTile, kLargeTile };   // bf16: small and middle are 64 columns, with two wavefronts to a block and one
+enum GatherTile { kSmallTile, kMidTile, kLargeTile };   // bf16 has no middle one
 inline int gather_edge(int dtype, GatherTile tile)
 {
     return dtype == VCAS_BF16 ? (tile == kLargeTile ? 128 : 64) : tile == kLargeTile ? 128 : tile == kMidTile ? 64 : 32;

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     # bf16, dW in 64x64 tiles: a tile or two of each, ragged; contractions of one step and of many; beyond the line
     (BF16, 5, 37, 264, 136, 0.6, 0.5), (BF16, 1, 1, 8, 8, 1.0, 1.0), (BF16, 4, 33, 72, 8, 0.02, 0.02), (BF16, 16, 65, 520, 2056, 0.7, 0.6),
     (BF16, 9, 233, 776, 264, 1.0, 0.3), (BF16, 13, 300, 1032, 520, 1.0, 0.2), (BF16, 70, 60, 264, 264, 0.3, 0.3),
+    (BF16, 10, 300, 520, 520, 0.5, 0.9),
     # bf16, dW in 128x128 tiles, either operand the narrower one; beyond the line
     (BF16, 3, 67, 1480, 1544, 0.7, 0.7), (BF16, 32, 40, 776, 3080, 0.5, 0.5), (BF16, 12, 50, 3080, 776, 0.4, 0.4), (BF16, 12, 300, 1480, 1544, 0.7, 0.2),
     # fp32: 64x64 and 64x64 tiles, 64x64 and 128x128, 128x128 and 64x64, 128x128 and 128x128; beyond the line

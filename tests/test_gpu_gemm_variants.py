@@ -41,15 +41,15 @@ def test_fp32_kernels_at_their_edges(vb, case):
 BF16_CASES = [
     # wgrad gathering with 64x64 tiles: fewer than 32 of them, 256, ragged; G scaled, X scaled
     (3, 11, 8, 8, 0.5, 0.5), (9, 233, 264, 136, 0.6, 0.7), (9, 233, 136, 264, 0.7, 0.7), (8, 256, 1024, 1024, 1.0, 0.99),
-    # nothing kept, one token; 1024 and 1025 tokens of fewer than 32 tiles (gathering, packed)
-    (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1024, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
-    # 18 x 19 tiles, ragged, either side scaled; beyond 1024 tokens the packed form; 128x128 tiles, ragged, either side scaled
+    # nothing kept, one token; whole and in slices
+    (2, 5, 72, 200, 0.02, 0.02), (1, 1, 72, 200, 1.0, 1.0), (1, 1000, 64, 72, 1.0, 1.0), (1, 1025, 64, 72, 1.0, 1.0),
+    # 18 x 19 tiles, ragged, either side scaled; 128x128 tiles, ragged, either side scaled
     (3, 67, 1096, 1160, 0.7, 0.7), (3, 67, 1160, 1096, 0.7, 0.7), (8, 257, 1096, 1160, 1.0, 0.9),
     (3, 67, 1480, 1544, 0.7, 0.7), (3, 67, 1544, 1480, 0.7, 0.7), (1, 129, 1480, 1544, 1.0, 1.0), (1, 321, 1480, 1544, 1.0, 1.0),
     # gathering over whole, partial and single steps of 64 tokens, with 64x64 tiles; 17 x 17 tiles of 128x128
     (1, 64, 264, 264, 1.0, 1.0), (1, 65, 264, 264, 1.0, 1.0), (1, 200, 264, 264, 1.0, 1.0), (1, 257, 264, 264, 1.0, 1.0),
     (1, 513, 264, 264, 1.0, 1.0), (1, 129, 1096, 1160, 1.0, 1.0), (1, 321, 1096, 1160, 1.0, 1.0), (3, 67, 2056, 2120, 0.7, 0.7),
-    # packed, 256x256 tiles: 15 x 15 of them on a layer's own; below 192 and beyond 256 of them (13 x 14, 17 x 16) as before
+    # 128x128 tiles of wide matrices
     (1, 300, 3592, 3688, 1.0, 1.0), (2, 200, 3688, 3592, 1.0, 0.8), (2, 300, 3464, 3208, 1.0, 0.9), (2, 300, 3848, 4104, 1.0, 0.9),
 ]
 
@@ -57,6 +57,22 @@ BF16_CASES = [
 @pytest.mark.parametrize("case", BF16_CASES, ids=lambda c: "x".join(map(str, c)))
 def test_bf16_kernels_at_their_edges(vb, case):
     _against_oracle(BF16, *case)
+
+
+# The packed form of a layer on its own, ragged in columns and tokens, either side the packed one: 128x128 tiles in slices; 256x256
+# tiles, 15 x 15 of them (one for nearly every CU); below 192 and beyond 256 of those (14 x 13, 16 x 17) 128x128 tiles again
+@pytest.mark.parametrize("case", [
+    (1, 4101, 1304, 1496, 1.0, 1.0), (3, 1501, 1496, 1304, 1.0, 0.93), (1, 877, 3592, 3688, 1.0, 1.0), (2, 501, 3688, 3592, 1.0, 0.9),
+    (1, 2501, 3464, 3208, 1.0, 1.0), (2, 907, 3848, 4104, 1.0, 0.97)], ids=lambda c: "x".join(map(str, c)))
+def test_packed_weight_gradients_at_their_edges(vb, case):
+    from tests.gpu_util import packs_the_kept_rows
+    _against_oracle(BF16, *case)
+    N, T, K_in, K_out, rho, nu = case
+    shape = vb.shape_of(N, T, K_in, K_out, BF16)
+    G, X = (torch.randn((N * T, K), device="cuda").bfloat16() for K in (K_out, K_in))
+    plan, ws, dW = vb.Plan.allocate(N, T), vb.make_workspace(shape), torch.empty((K_out, K_in), device="cuda")
+    call = lambda out: vb.vcas_linear_backward(shape, G, X, None, rho, nu, vb.Rng(3, 1, 0), True, plan, None, out, ws)
+    assert packs_the_kept_rows(ws, lambda: call(dW), lambda: call(None))
 
 
 def _against_oracle(dtype, N, T, K_in, K_out, rho, nu):
@@ -138,15 +154,15 @@ def test_dgrad_last_round_in_quarters(vb, K_out, kept):
         assert float(((rows - (got * got).sum(1)).abs() / (got * got).sum(1).clamp_min(1e-30))[~dropped].max()) <= 1e-5
 
 
-# On both sides of the lines between the two forms of a small weight gradient: 64x64 tiles by their number (16, 32, 64, 144, 192,
-# 306 and 504 of them), 128x128 tiles (135).  vcas_sampled_wgrad, which knows no expected count, always takes the packed form: its
-# bits are those of the same form, and the gathering kernel adds in another order.
+# On both sides of the lines between the forms of a weight gradient: 64x64 tiles whole and in slices (16 and 64 of them), in two
+# slices and 128x128 tiles in five (768x768), 64x64 and 128x128 tiles whole, 128x128 tiles and the packed form, with and without slices
 @pytest.mark.parametrize("K_in,K_out,tokens,packed", [
-    (256, 256, 512, False), (256, 256, 1024, True), (512, 256, 768, False), (512, 256, 1280, True),
-    (512, 512, 1024, False), (512, 512, 1536, True), (768, 768, 1752, False), (768, 768, 1760, True), (1024, 768, 2048, False),
-    (1024, 768, 2056, True), (1096, 1032, 1024, False), (1096, 1032, 1280, True), (1304, 1496, 1024, False), (1304, 1496, 1032, True),
-    (1112, 1864, 1024, False), (1112, 1864, 1032, True)])
+    (256, 256, 1096, False), (256, 256, 1104, False), (512, 512, 1424, False), (512, 512, 1432, False), (768, 768, 3096, False),
+    (768, 768, 3104, False), (1304, 1496, 728, False), (1304, 1496, 736, False), (1304, 1496, 3960, False), (1304, 1496, 3968, True),
+    (1096, 1032, 7392, False), (1096, 1032, 7400, True), (776, 3080, 5392, False), (776, 3080, 5400, True), (3400, 3456, 968, False),
+    (3400, 3456, 976, True)])
 def test_form_of_a_small_weight_gradient(vb, K_in, K_out, tokens, packed):
+    from tests.gpu_util import packs_the_kept_rows
     N, T = 8, tokens // 8
     shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_BF16)
     gen = torch.Generator(device="cuda").manual_seed(tokens)
@@ -154,13 +170,15 @@ def test_form_of_a_small_weight_gradient(vb, K_in, K_out, tokens, packed):
     X = torch.randn((tokens, K_in), generator=gen, device="cuda").bfloat16()
     plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
     dW = torch.full((K_out, K_in), float("nan"), device="cuda")
-    vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(3, 1, 0), True, plan, None, dW, ws)
+    call = lambda out: vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(3, 1, 0), True, plan, None, out, ws)
+    assert packs_the_kept_rows(ws, lambda: call(dW), lambda: call(None)) == packed
+    want = G.double().t() @ X.double()
+    # fp32 sums of exact products, in any order: sqrt(7400) 2^-24 = 5e-6
+    assert float((dW.double() - want).norm() / want.norm()) <= 1e-5
+    # vcas_sampled_wgrad, which knows no expected count, takes all rows for kept: here that is so
     other = torch.full((K_out, K_in), float("nan"), device="cuda")
     vb.vcas_sampled_wgrad(shape, G, X, plan.scaleW, plan.idxW, plan.cntW, other, ws)
-    want = G.double().t() @ X.double()
-    # fp32 sums of exact products, in any order: sqrt(2048) 2^-24 = 3e-6
-    assert float((dW.double() - want).norm() / want.norm()) <= 1e-5 and float((other.double() - want).norm() / want.norm()) <= 1e-5
-    assert torch.equal(dW, other) == packed
+    assert torch.equal(dW, other)
 
 
 def test_gathering_layers_of_a_stack_share_launches(vb):
@@ -202,8 +220,9 @@ def test_gathering_layers_of_a_stack_share_launches(vb):
 
 def test_layers_of_one_big_tile_per_cu_in_a_stack(vb):
     """Two layers of 14 x 14 tiles of 256x256 and one of 13 x 14 in a stack with wgrad_fill 0: the bits of calls of their
-    own, whichever tile either side takes."""
-    N, T = 2, 100
+    own, all of them packed."""
+    from tests.gpu_util import packs_the_kept_rows
+    N, T = 2, 1301
     entries, keep = [], []
     gen = torch.Generator(device="cuda").manual_seed(8)
     one = lambda *size: torch.randn(size, generator=gen, device="cuda").bfloat16()
@@ -218,7 +237,8 @@ def test_layers_of_one_big_tile_per_cu_in_a_stack(vb):
     torch.cuda.synchronize()
     for l, (shape, G, X, plan, ws, dW) in enumerate(keep):
         want = torch.full_like(dW, float("nan"))
-        vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(2, l, 0), True, plan, None, want, ws)
+        call = lambda out: vb.vcas_linear_backward(shape, G, X, None, 1.0, 1.0, vb.Rng(2, l, 0), True, plan, None, out, ws)
+        assert packs_the_kept_rows(ws, lambda: call(want), lambda: call(None))
         assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
 
 

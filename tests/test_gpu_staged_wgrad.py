@@ -1,4 +1,4 @@
-"""The bf16 weight gradient whose operands are scaled on their way to LDS: 64x64 tiles with one wavefront to a block and 128x128
+"""The bf16 weight gradient whose operands are scaled on their way to LDS: 64x64 tiles with two wavefronts to a block and 128x128
 tiles, whole and in slices of which all, some, one or none have tokens, either operand the scaled one, ragged columns and last steps,
 against 64 bits on the rounded operand."""
 import math
