@@ -486,7 +486,9 @@ vcas_status vcas_controller_update(const vcas_controller_params *prm, int32_t L,
  * Sec. 4.2's grad_W) is bracketed by HIP events stamped by the kernel's own
  * dispatch.  vcas_profile_end waits for them and returns, in HOST arrays of two
  * entries ([0] dgrad, [1] wgrad), the summed kernel durations in milliseconds
- * and the number of launches.  Not for use under graph capture; creates and
+ * and the number of launches.  In between, a small layer on one stream, whose two
+ * products vcas_linear_backward otherwise forms in one launch, takes two (the same
+ * bits), so that each half has its figure.  Not for use under graph capture; creates and
  * destroys HIP events (the only calls of the library that do).
  */
 vcas_status vcas_profile_begin(void);

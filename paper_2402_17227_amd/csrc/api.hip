@@ -738,7 +738,8 @@ static vcas_status linear_backward_impl(const vcas_shape &s, const void *G, cons
     const bool forked = side && side != st;
     const int64_t rows = (int64_t)((double)R * rho + 0.5), tokens = expected_tokens(s, rho, nu, token_sampling);
     if (!forked) {
-        const Together t = dX && dW ? halves_together(s, rows, tokens) : Together{};
+        // the kernel timer has a figure for each half: two launches while it is on
+        const Together t = dX && dW && !kernel_timer().on ? halves_together(s, rows, tokens) : Together{};
         void *const own_dX = t.yes ? nullptr : dX;
         float *const own_dW = t.yes ? nullptr : dW;
         // Small layers with short vectors: norms, SampleA and SampleW in ONE launch (the workgroup that finishes its rows

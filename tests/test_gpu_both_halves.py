@@ -53,6 +53,28 @@ def test_one_launch_is_the_two(dtype, N, T, K_in, K_out, rho, nu):
         assert bool(dX_a.isfinite().all()) and bool(dW_a.isfinite().all())
 
 
+@pytest.mark.parametrize("dtype", [BF16, F32])
+def test_the_timer_tells_the_halves_apart(dtype):
+    """A layer that goes out in one launch: while the kernel timer is on either half is launched and counted, and the bits are the same."""
+    from paper_2402_17227_amd import binding as vb
+    N, T, K_in, K_out = 20, 200, 776, 520
+    real = torch.bfloat16 if dtype == BF16 else torch.float32
+    G, X, W = (torch.randn(size, device="cuda").to(real) for size in ((N * T, K_out), (N * T, K_in), (K_out, K_in)))
+    shape = vb.shape_of(N, T, K_in, K_out, dtype)
+    plan, ws = vb.Plan.allocate(N, T), vb.make_workspace(shape)
+    got = []
+    for timed in (False, True):
+        dX, dW = torch.empty_like(X), torch.empty((K_out, K_in), device="cuda")
+        if timed:
+            vb.vcas_profile_begin()
+        vb.vcas_linear_backward(shape, G, X, W, 0.5, 0.5, vb.Rng(7, 2, 0), True, plan, dX, dW, ws)
+        if timed:
+            (ms_x, n_x), (ms_w, n_w) = vb.vcas_profile_end()
+            assert n_x == n_w == 1 and ms_x > 0.0 and ms_w > 0.0
+        got.append((dX, dW))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 # fp32 sums that bf16 parts cannot hold (2^90) in single 32x32 blocks of dX and dW, which are formed again in plain fp32: beside
 # them the blocks keep their bits whatever tile either way takes (dX 128x128 in one launch; apart 64x64, 64x128, 128x128)
 @pytest.mark.parametrize("N,T,K_in,K_out", [(10, 100, 520, 520), (20, 200, 776, 520), (20, 200, 776, 2200), (30, 64, 520, 2568)])
