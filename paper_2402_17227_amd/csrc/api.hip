@@ -903,8 +903,9 @@ static vcas_status variance_probe(const vcas_shape &s, const void *G, const void
         GatherTile tile = kLargeTile;
         if (fits) {
             // bf16: the larger tile moves half the bytes per product; the smaller one where that would leave CUs
-            // empty (768x768, 2836 tokens: sixteen products 91 and 110 us, three of 1024 tokens 17.5 and 14.6).  fp32: the lines of
-            // wgrad_f32 with the tiles of all products
+            // empty (768x768, 2836 tokens: sixteen products 91 and 110 us, three of 1024 tokens 17.5 and 14.6).  fp32: 128x128 from 100 of
+            // them up (768x768, 1024 and 512 tokens, four products, 144 of them: a probe 104 us; 576x512, 80 of them: 94, with
+            // 64x64 tiles 78), 32x32 up to 64 tiles of 64x64
             auto all = [&](GatherTile t) { return 2 * n * gather_tiles(s.dtype, s.K_out, s.K_in, t); };
             if (s.dtype == VCAS_BF16) tile = all(kLargeTile) >= 192 ? kLargeTile : kSmallTile;
             else tile = all(kLargeTile) >= 100 ? kLargeTile : all(kMidTile) > 64 ? kMidTile : kSmallTile;

@@ -592,16 +592,23 @@ int wgrad_slices_large_f32(int K_out, int K_in, int64_t R, int fill)
 //   768x768,   4096      77        55 / 51    123 / 38       77
 //  1024x1024,  2048      53        34.8        65 / 35.2     53
 //   768x3072,  1024      72        54.7        44.0          72
-//  1608x1928,   170                28.2        15.2          24.1
+//  1608x1928,   170                28.2         15.2          24.1
 //  4096x4096,   128                88          42.6          58.6
-// So 32x32 up to 64 tiles of 64x64 (100 where the tokens are few), 128x128 unsliced from 100 tiles up (a CU each for half of them is enough); in between
-// by what a token costs: a 128x128 tile takes 2.2 times as long for one as a 64x64 tile (which takes two rounds beyond
-// 256 of them), and its slices and their reduction as long as 900 tokens.
+//  1536x768,    150      14.7      15.2         11.8, in three slices 15.4
+//               400      22.5      21.9         19.2                  20.7
+//               600                27.0         24.8                  23.1
+//              1500                51.4         51.4                  31.8
+//  2048x1024,   256      23.6      18.1         15.4, in two slices   23.4
+//               600                30.4         27.2                  29.8
+//               900                41.5         37.9                  35.1
+//              3000               105           99.6                  77.2
+// So 32x32 up to 64 tiles of 64x64 (100 where the tokens are few).  From 257 of those up (a second round of them) 128x128, in slices
+// where what they save, 0.031 us a token, is more than adding them up costs.  In between by what a token costs: a 128x128 tile takes 2.2
+// times as long for one as a 64x64 tile, and its slices and their reduction as long as 900 tokens.
 static void wgrad_f32_form(const vcas_shape &s, int fill, int max_splits, int64_t tokens, GatherTile &tile, int32_t &splits)
 {
     const int64_t R = (int64_t)s.N * s.T, t = tokens > 0 && tokens < R ? tokens : R;
-    const int small = gather_tiles(VCAS_F32, s.K_out, s.K_in, kSmallTile), mid = gather_tiles(VCAS_F32, s.K_out, s.K_in, kMidTile),
-              large = gather_tiles(VCAS_F32, s.K_out, s.K_in, kLargeTile);
+    const int small = gather_tiles(VCAS_F32, s.K_out, s.K_in, kSmallTile), mid = gather_tiles(VCAS_F32, s.K_out, s.K_in, kMidTile);
     int slices = wgrad_slices_large_f32(s.K_out, s.K_in, R, fill);
     if (slices > max_splits) slices = max_splits;
     tile = kMidTile;
@@ -610,7 +617,11 @@ static void wgrad_f32_form(const vcas_shape &s, int fill, int max_splits, int64_
         tile = kSmallTile;
         splits = (fill + fill / 3 + small - 1) / small;
         if (splits > max_splits) splits = max_splits;
-    } else if (large >= 100 || (double)t * ((mid > 256 ? 2.0 : 1.0) - 2.2 / slices) > 900.0) {
+    } else if (mid > 256) {
+        tile = kLargeTile;
+        const double saved = 0.031 * (double)t * (slices - 1) / slices, reduction = 4.5 + (double)slices * s.K_out * s.K_in / 600e3;
+        if (saved > reduction) splits = slices;
+    } else if ((double)t * (1.0 - 2.2 / slices) > 900.0) {
         tile = kLargeTile;
         splits = slices;
     }

@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     # fp32: 64x64 and 64x64 tiles, 64x64 and 128x128, 128x128 and 64x64, 128x128 and 128x128; beyond the line
     (F32, 10, 100, 520, 520, 1.0, 1.0), (F32, 30, 64, 520, 2568, 0.5, 0.9), (F32, 20, 200, 776, 520, 0.5, 0.5),
     (F32, 20, 200, 776, 2200, 0.5, 0.5), (F32, 20, 200, 776, 3080, 1.0, 0.5), (F32, 8, 128, 768, 768, 0.5, 0.5),
+    (F32, 20, 64, 520, 2568, 0.75, 0.5), (F32, 20, 200, 776, 2200, 0.5, 0.25),
 ], ids=lambda c: str(c))
 def test_one_launch_is_the_two(dtype, N, T, K_in, K_out, rho, nu):
     from paper_2402_17227_amd import binding as vb

@@ -35,12 +35,14 @@ def _bound(k):
 
 
 # 64x64 tiles (from 65 of them, 101 for few tokens), then, from about 1250 rows on, 128x128 tiles in eight slices: all active, some, one, none;
-# steps of 64 and of 32 tokens that are full, ragged, single; 128x128 unsliced from 100 tiles up
+# steps of 64 and of 32 tokens that are full, ragged, single; 128x128 tiles from 257 of 64x64 up, whole up to some 600 tokens, in two
+# and three slices beyond, whole at any number from 129 of them up
 @pytest.mark.parametrize("R,K_in,K_out,kept", [
     (1200, 520, 520, 1200), (1200, 520, 584, 65), (700, 584, 520, 1), (700, 520, 520, 0), (192, 520, 520, 64), (140, 776, 520, 140),
     (4001, 520, 520, 4001), (4001, 520, 584, 1025), (4001, 584, 520, 1023), (4001, 520, 520, 257), (4001, 520, 520, 129),
     (4001, 520, 520, 127), (4001, 520, 520, 1), (4001, 520, 520, 0), (1500, 768, 768, 1500),
-    (300, 1288, 1160, 300), (300, 1160, 1288, 33), (300, 1288, 1160, 31), (40, 1288, 1160, 1)])
+    (300, 1288, 1160, 300), (300, 1160, 1288, 33), (300, 1288, 1160, 31), (40, 1288, 1160, 1),
+    (300, 776, 1544, 300), (1500, 1288, 1160, 1500), (1500, 1160, 1288, 257), (1500, 1288, 1160, 127), (1200, 776, 1416, 1111), (1500, 1288, 1672, 1500)])
 def test_wgrad_tiles_and_slices(vb, R, K_in, K_out, kept):
     gen = torch.Generator(device="cuda").manual_seed(R + kept)
     G = torch.randn((R, K_out), generator=gen, device="cuda")
