@@ -4,7 +4,7 @@
 
 namespace vcas {
 
-template <int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF>
+template <int SK, int WM, int WN, int WK, bool DIFF>
 __global__ __launch_bounds__(WM *WN *WK * 64) void wgrad_gather_kernel(GatherBatch batch)
 {
     // the task whose range holds this workgroup (ranges ascend)
@@ -12,7 +12,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void wgrad_gather_kernel(GatherBat
     for (int i = 1; i < batch.n; ++i)
         if ((int)blockIdx.x >= batch.task[i].first_wg) p = i;
     const GatherTask &q = batch.task[p];
-    wgrad_gather_body<PA, PB, SK, WM, WN, WK, DIFF>(q, (int)blockIdx.x - q.first_wg);
+    wgrad_gather_body<SK, WM, WN, WK, DIFF>(q, (int)blockIdx.x - q.first_wg);
 }
 
 // bf16 (STAGED), or fp32 from the bf16 parts of its operands.
@@ -63,11 +63,11 @@ static vcas_status launch_staged(const GatherBatch &batch, int grid, hipStream_t
     return launch_tiles(wgrad_staged_kernel<BM, BN, WM, WN, WK, DIFF>, WM * WN * WK * 64, staged_lds(BM, BN), allowed, batch, grid, st);
 }
 
-template <int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF>
+template <int SK, int WM, int WN, int WK, bool DIFF>
 static vcas_status launch_gather(const GatherBatch &batch, int grid, hipStream_t st)
 {
-    const size_t lds = 2 * SK * (PA + PB) + 2048;
-    auto kern = wgrad_gather_kernel<PA, PB, SK, WM, WN, WK, DIFF>;
+    const size_t lds = 2 * SK * 256 + 2048;   // two stages of both tiles, tokens and scales
+    auto kern = wgrad_gather_kernel<SK, WM, WN, WK, DIFF>;
     static bool allowed = false;
     if (!allowed) {
         if (!allow_lds(kern, lds)) return VCAS_EHIP;
@@ -104,8 +104,8 @@ vcas_status wgrad_gather(GatherTask *tasks, int n, int dtype, GatherTile tile, b
                                           : launch_split<128, 128, 2, 4, 1, false>(batch, (int)grid, st);
     if (tile == kMidTile) return diff ? launch_split<64, 64, 2, 2, 2, true>(batch, (int)grid, st)
                                         : launch_split<64, 64, 2, 2, 2, false>(batch, (int)grid, st);
-    return diff ? launch_gather<128, 128, 64, 1, 1, 4, true>(batch, (int)grid, st)
-                : launch_gather<128, 128, 64, 1, 1, 4, false>(batch, (int)grid, st);
+    return diff ? launch_gather<64, 1, 1, 4, true>(batch, (int)grid, st)
+                : launch_gather<64, 1, 1, 4, false>(batch, (int)grid, st);
 }
 
 }  // namespace vcas

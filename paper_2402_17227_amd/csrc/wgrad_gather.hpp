@@ -97,15 +97,15 @@ __device__ __forceinline__ void gather_finish(const GatherTask &q, const f32x16 
     }
 }
 
-// fp32, on the fp32 matrix instruction.  Both tiles of a step lie in LDS as [64 tokens][PA or PB bytes of columns], written by
+// fp32, on the fp32 matrix instruction.  Both tiles of a step lie in LDS as [64 tokens][128 bytes of columns], written by
 // LDS-direct loads one step ahead; a step's tokens come from a 64-entry table in LDS that is itself fetched four steps ahead, its
 // token scales from a second table, gathered with the tiles, and are multiplied into G's fragments.  Two stages, one barrier per step.
 // WM x WN wavefronts share the tile, WK of them each block: they take different parts of every step
 // and their sums meet in LDS at the end, in wavefront order.
-template <int PA, int PB, int SK, int WM, int WN, int WK, bool DIFF>
+template <int SK, int WM, int WN, int WK, bool DIFF>
 __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local_id)
 {
-    constexpr int NW = WM * WN * WK, E = 4;
+    constexpr int NW = WM * WN * WK, E = 4, PA = 128, PB = 128;   // bytes of columns in a row of either tile
     constexpr int BM = PA / E, BN = PB / E;                       // columns of a tile
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int AI = SK * PA / 1024 / NW, BI = SK * PB / 1024 / NW;   // LDS-direct loads per wavefront and step
@@ -138,23 +138,22 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
     const i32x4 descI = raw_descriptor(q.idx, (uint32_t)cnt * 4u);        // entries past the count read as zero
     const i32x4 descS = raw_descriptor(q.row_scale, (uint32_t)R * 4u);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    // the two halves of a wavefront read tokens k and k + 4 at once (see below): rows of 256 bytes
-    // exchange their halves, rows of 128 bytes their neighbour, wherever bit 2 of k is set
-    auto place = [](int k, int pitch) { return pitch == 128 ? k ^ ((k >> 2) & 1) : k; };
-    auto flip = [](int k, int pitch) { return pitch == 256 ? ((k >> 2) & 1) * 8 : 0; };
+    // the two halves of a wavefront read tokens k and k + 4 at once (see below): neighbouring rows change places wherever bit 2 of k
+    // is set
+    auto place = [](int k) { return k ^ ((k >> 2) & 1); };
     // load j of this wavefront fills 1024 / pitch rows; lane's row and the column bytes it fetches there
     uint32_t a_col[AI], b_col[BI];
     int a_k[AI], b_k[BI];
 #pragma unroll
     for (int j = 0; j < AI; ++j) {
-        a_k[j] = place((wave * AI + j) * (1024 / PA) + lane / (PA / 16), PA);
-        const int col = o0 + ((lane % (PA / 16)) ^ flip(a_k[j], PA)) * (16 / E);
+        a_k[j] = place((wave * AI + j) * (1024 / PA) + lane / (PA / 16));
+        const int col = o0 + lane % (PA / 16) * (16 / E);
         a_col[j] = col < K_out ? (uint32_t)col * E : kOutside;
     }
 #pragma unroll
     for (int j = 0; j < BI; ++j) {
-        b_k[j] = place((wave * BI + j) * (1024 / PB) + lane / (PB / 16), PB);
-        const int col = c0 + ((lane % (PB / 16)) ^ flip(b_k[j], PB)) * (16 / E);
+        b_k[j] = place((wave * BI + j) * (1024 / PB) + lane / (PB / 16));
+        const int col = c0 + lane % (PB / 16) * (16 / E);
         b_col[j] = col < K_in ? (uint32_t)col * E : kOutside;
     }
     auto load_tokens = [&](int st) {   // wavefront 0: the tokens of step st into their table
@@ -224,7 +223,7 @@ __device__ __forceinline__ void wgrad_gather_body(const GatherTask &q, int local
         // is free, and the four scales of a half are then one 16-byte read
         const int r32 = lane & 31, h = lane >> 5;
         auto cell = [&](const unsigned char *t, int pitch, int col, int k) {
-            return *reinterpret_cast<const float *>(t + place(k, pitch) * pitch + (((col >> 2) ^ flip(k, pitch)) << 4) + (col & 3) * 4);
+            return *reinterpret_cast<const float *>(t + place(k) * pitch + col * E);
         };
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

@@ -79,7 +79,7 @@ __device__ __forceinline__ void wgrad_staged_tile(const GatherTask &q, int local
         *reinterpret_cast<u32x4 *>(smem + set * STAGE + (n < AQ ? a_put + n * (A_K * BM * 2) : b_put + (n - AQ) * (B_K * BN * 2))) = w;
     };
 
-    const int lane = tid & 63, wave = tid >> 6, wk = wave / (WM * WN), blk = wave % (WM * WN);
+    const int wave = tid >> 6, wk = wave / (WM * WN), blk = wave % (WM * WN);
     const int wm0 = (blk / WN) * (BM / WM), wn0 = (blk % WN) * (BN / WN);
     f32x16 acc[TM][TN];
 #pragma unroll
