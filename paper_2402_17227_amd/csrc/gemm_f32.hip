@@ -1,8 +1,8 @@
 // fp32 gather-GEMMs of the VCAS backward pass (the fp32 configuration): small tiles on v_mfma_f32_32x32x2_f32, larger ones from
 // bf16 parts.
 // dgrad (Eq. 2, upper line) here and in f32_split.hpp, wgrad (Sec. 4.2) in wgrad_gather.hpp and f32_split.hpp.
-// dgrad_f32_staged_kernel and wgrad_f32_far_kernel serve tensors that 32-bit buffer offsets do not reach: 64x64 output tiles, four wavefronts, operands staged through registers into k-major LDS tiles
-// ([k][row], pitch 68 floats, so that fragment reads are 32 consecutive floats), contraction in steps of 16.
+// dgrad_f32_staged_kernel and wgrad_f32_far_kernel serve tensors that 32-bit buffer offsets do not reach: 64x64 output tiles, four
+// wavefronts, operands staged through registers into k-major LDS tiles ([k][row], pitch 68 floats, so that fragment reads are 32 consecutive floats), contraction in steps of 16.
 #include "f32_split.hpp"
 
 namespace vcas {
@@ -229,7 +229,8 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(DgradF32 q)
     else dgrad_direct_body<BM, BN, WM, WN, WK, 2, WK == 8 ? 3 : 2>(q);
 }
 
-// Wide tiles from bf16 parts, eight wavefronts, OCC of them to a SIMD.
+// Wide tiles from bf16 parts, eight wavefronts, OCC of them to a SIMD.  64x128 tiles are two workgroups to a CU, 128 VGPRs a wavefront: three
+// values wait in scratch while the loops run, which do not touch it.
 template <int BM, int BN, int OCC>
 __global__ __launch_bounds__(512, OCC) void dgrad_f32_wide_kernel(DgradF32 q)
 {

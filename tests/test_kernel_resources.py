@@ -66,6 +66,38 @@ def test_256x256_dgrad_leaves_registers_for_side_streams(kernels):
         assert vgprs <= 224 and scratch == 0, (name, vgprs, scratch)
 
 
+def test_gemms_that_share_a_cu_do_not_spill(objects, kernels):
+    """The staged and split weight gradients, the fp32 dgrads and the kernels of both halves: registers for as many wavefronts as their
+    tiles want to a SIMD (of 512 VGPRs), none in scratch.  64x128 tiles of dgrad, two workgroups of eight wavefronts to a CU, keep
+    three registers there, which no loop with matrix instructions touches."""
+    wanted = {"wgrad_staged_kernel<": 128, "wgrad_split_kernel<": 256, "layer_bf16_kernel<": 256, "layer_f32_kernel<": 256,
+              "dgrad_f32_kernel<": 256, "dgrad_f32_wide_kernel<128, 128": 256, "dgrad_f32_wide_kernel<64, 128": 128}
+    for part, most in wanted.items():
+        some = {n: r for n, r in kernels.items() if part in n}
+        assert some, part
+        for name, (vgprs, scratch) in some.items():
+            assert vgprs <= most and scratch <= (16 if "wide_kernel<64, 128" in part else 0), (name, vgprs, scratch)
+    seen = 0
+    for obj in objects:
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True,
+                              text=True).stdout
+        for body in re.split(r"\n(?=[0-9a-f]+ <)", text):
+            if "dgrad_f32_wide_kernelILi64ELi128" not in body.split("\n", 1)[0]:
+                continue
+            code = [(int(m.group(3), 16), m.group(1), m.group(2))
+                    for m in re.finditer(r"^\s+(\S+)(.*?)//\s*([0-9A-F]+):", body, re.M)]
+            for at, op, args in code:
+                if not op.startswith(("s_cbranch", "s_branch")):
+                    continue
+                words = int(args.split()[0])
+                to = at + 4 + 4 * (words - 65536 if words > 32767 else words)
+                loop = [o for a, o, _ in code if to <= a <= at]
+                if to <= at and any("mfma" in o for o in loop):
+                    assert not any(o.startswith("scratch_") for o in loop), hex(to)
+                    seen += 1
+    assert seen >= 2      # the loop of whole steps and that of the last ones
+
+
 def test_fp32_dgrad_gives_a_stage_back_when_it_has_been_read(objects):
     """Behind a barrier of the main loop the next loads go into the stage of the step before: at every barrier of the
     LDS-direct fp32 dgrad kernels the wavefront's own LDS reads have been waited for in so many words, not only because the
