@@ -26,9 +26,9 @@ F32_CASES = [
     (3, 11, 8, 8, 0.5, 0.5), (3, 33, 264, 72, 0.7, 0.6), (7, 40, 96, 520, 0.6, 0.5), (40, 64, 64, 136, 1.0, 1.0),
     # dgrad with 32x64 tiles
     (5, 131, 552, 200, 1.0, 0.3),
-    # the same where 64x64 tiles would be 264, a second one for eight CUs (those tiles: test_fp32_dgrad_tiles)
+    # 264 tiles of 64x64, so 64x128 (those and the other tiles from bf16 parts: test_fp32_dgrad_tiles)
     (9, 233, 456, 72, 1.0, 0.5),
-    # wgrad with 64x64 tiles (768 of them and more): full, remainder and single steps of 32 tokens, nothing kept
+    # wgrad with 128x128 tiles from bf16 parts: full, remainder and single steps of 32 tokens, nothing kept
     (4, 47, 1608, 1928, 0.5, 0.5), (2, 16, 1608, 1928, 1.0, 1.0), (2, 5, 1608, 1928, 0.02, 0.02),
 ]
 
@@ -86,9 +86,11 @@ def _against_oracle(dtype, N, T, K_in, K_out, rho, nu):
     assert rel_l2_rows(dX, want_dX) <= 2 * TOL[dtype] and rel_l2_tiles(dW, want_dW) <= 2 * TOL[dtype]
 
 
-def test_fp32_tensors_beyond_32_bit_offsets(vb):
-    """G of more than 2 GiB: rows at both ends of it against a product in double precision."""
-    N, T, K_in, K_out = 16, 4096, 8, 8200
+@pytest.mark.parametrize("T,K_in,jacobian", [(4096, 8, False), (4099, 200, True)])
+def test_fp32_tensors_beyond_32_bit_offsets(vb, T, K_in, jacobian):
+    """G of more than 2 GiB: rows at both ends of it against a product in double precision; one column tile, and four, the last one
+    ragged, with tiles of rows that straddle two samples and a Jacobian."""
+    N, K_out = 16, 8200
     R = N * T
     shape = vb.shape_of(N, T, K_in, K_out, vb.VCAS_F32)
     gen = torch.Generator(device="cuda").manual_seed(1)
@@ -99,10 +101,18 @@ def test_fp32_tensors_beyond_32_bit_offsets(vb):
     idxA = torch.tensor([0, N - 1] + [0] * (N - 2), dtype=torch.int32, device="cuda")
     cntA = torch.tensor([2], dtype=torch.int32, device="cuda")
     dX = torch.full((R, K_in), float("nan"), device="cuda")
-    vb.vcas_sampled_dgrad(shape, G, W, p, idxA, cntA, dX)
     kept = torch.cat([torch.arange(T, device="cuda"), torch.arange(R - T, R, device="cuda")])
     want = 2.0 * (G[kept].double() @ W.double())
-    assert float((dX[kept].double() - want).norm() / want.norm()) <= 1e-5
+    if jacobian:
+        J = torch.rand((R, K_in), generator=gen, device="cuda")
+        vb.vcas_sampled_dgrad_jac(shape, G, W, p, idxA, cntA, J, dX)
+        want *= J[kept].double()
+    else:
+        vb.vcas_sampled_dgrad(shape, G, W, p, idxA, cntA, dX)
+    off = dX[kept].double() - want
+    # sums of 8200 fp32 products: sqrt(8200) 2^-24 = 5e-6, a row or a column alike
+    assert float((off.norm(dim=1) / want.norm(dim=1)).max()) <= 3e-5 and float((off.norm(dim=0) / want.norm(dim=0)).max()) <= 1e-5
+    assert float(off.norm() / want.norm()) <= 1e-5
     assert float(dX[T:R - T].abs().max()) == 0.0
     tokens = torch.cat([kept[:200], kept[-57:]]).to(torch.int32)
     idxW = torch.zeros(R, dtype=torch.int32, device="cuda")
@@ -242,10 +252,9 @@ def test_layers_of_one_big_tile_per_cu_in_a_stack(vb):
         assert torch.equal(dW.view(torch.int32), want.view(torch.int32)), l
 
 
-# fp32 dgrad where few 64x64 tiles cover more than 256 CUs' worth of smaller ones (8 x 31 tiles of 64x64), with contractions
-# of less than, exactly and just beyond a step of 64, and the register-staged kernel (more than 512 tiles, contractions that are
-# short or ragged; 1025 to 2047 tiles, shorter or more ragged ones) on both sides of its lines; samples dropped, Jacobians,
-# rows and columns ragged
+# fp32 dgrad from bf16 parts: 64x64 tiles (8 x 31 of them), with contractions of less than, exactly and just beyond a step of 64;
+# 64x128 tiles up to 256 of them, and for contractions of up to 128 beyond; 128x128 tiles, with steps of 32 that are full, half and single;
+# samples dropped, Jacobians, rows and columns ragged
 @pytest.mark.parametrize("N,T,K_in,K_out,kept,jacobian", [
     (9, 215, 456, 40, 9, False), (9, 215, 456, 64, 9, True), (9, 215, 456, 72, 9, False), (9, 215, 456, 200, 9, True),
     (12, 215, 456, 72, 9, True), (5, 413, 1000, 8, 5, False), (5, 413, 1000, 136, 4, True), (5, 413, 1000, 256, 5, False),
@@ -381,8 +390,8 @@ def test_dgrad_tile_where_few_tiles_cannot_become_a_second_round(vb):
 
 
 def test_fp32_dgrad_of_a_ragged_contraction(vb):
-    """816 tiles of 64x64: a contraction of 272 took as long as one of 320 where it went in steps of 64 (0.99 of it; in steps
-    of 16 0.91)."""
+    """8 x 26 tiles of 128x128: a contraction of 272 takes less than one of 320 (nine steps of 32 and ten; in steps of 64 it took 0.99
+    of it)."""
     N, T, K_in = 8, 121, 3264
     R = N * T
 
