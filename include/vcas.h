@@ -161,8 +161,15 @@ vcas_status vcas_row_scale(const vcas_shape *shape, const float *p, const float 
  *   dX[r,:] = (1/p[i]) * G[r,:] W   for the T rows r of every kept sample i,
  *   dX[r,:] = 0                     for rows of dropped samples.
  * idxA/cntA: kept samples ascending and their count (device).  dX [R,K_in] in
- * the layer dtype is written completely.  bf16: MFMA with fp32 accumulation;
- * fp32: fp32 MFMA.
+ * the layer dtype is written completely.  bf16: MFMA with fp32 accumulation.
+ * fp32, here and in the weight gradient: products and sums of fp32 precision over
+ * the whole range of the type, on the fp32 matrix instruction, or, for all but
+ * small matrices, on the bf16 one from three bf16 parts of every value (a product's
+ * terms of at most 2^-24 of it are left out, sums are rounded less often, so errors
+ * are no larger).  There, sums of 32 rows by 32 columns among which one is not
+ * finite or beyond 2^82 are formed again on the fp32 instruction: infinities and
+ * NaN come out as fp32 gives them, and a call in which all of them are takes two
+ * to twelve times as long.
  */
 vcas_status vcas_sampled_dgrad(const vcas_shape *shape, const void *G, const void *W, const float *p,
                                const int32_t *idxA, const int32_t *cntA, void *dX, void *stream);

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(WM *WN *WK * 64) void dgrad_f32_kernel(DgradF32 q)
     else dgrad_direct_body<BM, BN, WM, WN, WK, 2, WK == 8 ? 3 : 2>(q);
 }
 
-// Wide tiles from bf16 parts, eight wavefronts, OCC of them to a SIMD.  64x128 tiles are two workgroups to a CU, 128 VGPRs a wavefront: three
+// Wide tiles from bf16 parts, eight wavefronts, OCC of them to a SIMD.  64x128 tiles are two workgroups to a CU, 128 VGPRs a wavefront: two
 // values wait in scratch while the loops run, which do not touch it.
 template <int BM, int BN, int OCC>
 __global__ __launch_bounds__(512, OCC) void dgrad_f32_wide_kernel(DgradF32 q)

@@ -69,7 +69,7 @@ def test_256x256_dgrad_leaves_registers_for_side_streams(kernels):
 def test_gemms_that_share_a_cu_do_not_spill(objects, kernels):
     """The staged and split weight gradients, the fp32 dgrads and the kernels of both halves: registers for as many wavefronts as their
     tiles want to a SIMD (of 512 VGPRs), none in scratch.  64x128 tiles of dgrad, two workgroups of eight wavefronts to a CU, keep
-    three registers there, which no loop with matrix instructions touches."""
+    two registers there, which no loop with matrix instructions touches."""
     wanted = {"wgrad_staged_kernel<": 128, "wgrad_split_kernel<": 256, "layer_bf16_kernel<": 256, "layer_f32_kernel<": 256,
               "dgrad_f32_kernel<": 256, "dgrad_f32_wide_kernel<128, 128": 256, "dgrad_f32_wide_kernel<64, 128": 128}
     for part, most in wanted.items():
